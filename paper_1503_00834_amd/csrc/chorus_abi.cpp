@@ -1,6 +1,7 @@
 // extern "C" entry points of the SD library (declared in include/chorus.h).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -1268,20 +1269,16 @@ int chorus_closure_infer(chorus_mesh_t mesh, const chorus_physics *phys, const d
 }
 
 struct TrainLayout {
-    size_t H1, H2, dZ1, dZ2, dY, lossv, part, flag, total;
+    size_t part, flag, total;
 };
 
+// one partial gradient per 16 samples, kTrainPartials at most: it never
+// shrinks as the batch grows, so a workspace serves every smaller batch
 static TrainLayout train_layout(int64_t B) {
     TrainLayout L;
     size_t off = 0;
-    const size_t row = sizeof(float) * 64 * (size_t)B;
-    L.H1 = off;  off = align256(off + row);
-    L.H2 = off;  off = align256(off + row);
-    L.dZ1 = off; off = align256(off + row);
-    L.dZ2 = off; off = align256(off + row);
-    L.dY = off;  off = align256(off + sizeof(float) * 16 * (size_t)B);
-    L.lossv = off; off = align256(off + sizeof(float) * (size_t)B);
-    L.part = off;  off = align256(off + sizeof(float) * (kMlpParams + 1) * (size_t)((B + 63) / 64));
+    const int64_t rows = std::min<int64_t>((B + 15) / 16, kTrainPartials);
+    L.part = off;  off = align256(off + sizeof(float) * (kMlpParams + 1) * (size_t)rows);
     L.flag = off;  off = align256(off + sizeof(int));
     L.total = off;
     return L;
@@ -1289,12 +1286,6 @@ static TrainLayout train_layout(int64_t B) {
 
 static TrainBufs train_bufs(const TrainLayout &L, unsigned char *W, int64_t n_mean) {
     TrainBufs T;
-    T.H1 = (float *)(W + L.H1);
-    T.H2 = (float *)(W + L.H2);
-    T.dZ1 = (float *)(W + L.dZ1);
-    T.dZ2 = (float *)(W + L.dZ2);
-    T.dY = (float *)(W + L.dY);
-    T.lossv = (float *)(W + L.lossv);
     T.part = (float *)(W + L.part);
     T.n_mean = n_mean;
     return T;

@@ -6,21 +6,17 @@
 //
 // Training is a sequence of small fixed-order kernels (no atomics), so a
 // run is bitwise reproducible:
-//   k_fwd_bwd    one wave per 16 samples, every layer on the FP32 matrix
-//                cores: forward pass, loss terms, and the pre-activation
-//                gradients dZ1, dZ2, dY (activations and gradients kept per
-//                sample, [t][64] rows; the GELU derivatives stay in
-//                registers)
-//   k_wgrad      one block per chunk of 64 samples: the chunk's partial
-//                weight and bias gradients and its loss as matrix-core
-//                products over the chunk's samples
-//   k_wgrad_sum  chunk partials summed (the gradient alone)
-//   k_wgrad_sum_adam  chunk partials summed and the Adam update (Kingma &
-//                Ba 2015, with bias correction) applied at once (training)
+//   k_train      forward pass, loss, backward pass and weight gradients of
+//                16-sample groups, every product on the FP32 matrix cores;
+//                one partial sum of each gradient (and the loss) per block
+//   k_wgrad_sum  the blocks' partials summed (the gradient alone)
+//   k_wgrad_sum_adam  the partials summed and the Adam update (Kingma & Ba
+//                2015, with bias correction) applied at once (training)
 // (every sum in a fixed order: the matrix-core products in their instruction
-// order, the other sums as four interleaved running sums, then pairwise)
+// order, the partials as eight interleaved running sums, then pairwise)
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "launch.hpp"
@@ -101,309 +97,245 @@ __device__ __forceinline__ void gelu_and_prime(float z, float &h, float &gp) {
     gp = fmaf(z * 0.39894228040143268f, e, Phi);
 }
 
-// One wave per 16 samples: every layer as FP32 matrix-core products
-// (v_mfma_f32_16x16x4f32) with hidden units as rows and the wave's samples as
-// columns.  Operand layout of the instruction (A 16 x 4, B 4 x 16, C 16 x
-// 16): lane l holds A[l % 16][l / 16], B[l / 16][l % 16] and C[4 (l / 16) +
-// i][l % 16], i = 0..3.  A layer's accumulator (lane l: units 16 mt + 4 (l /
-// 16) + i of sample l % 16) serves as the next product's B operand when the
-// K steps run over (mt, i): the step (mt, i) takes unit 16 mt + 4 (l / 16) + i
-// from lane group l / 16, and the weight operand is read at the same unit,
-// so no data moves between lanes.
-__global__ __launch_bounds__(64) void k_fwd_bwd(const float *__restrict__ X, const float *__restrict__ Y,
-                                                const int32_t *__restrict__ idx, int64_t base, int nb,
-                                                const float *__restrict__ W, TrainBufs T) {
-    const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
-    const int t = blockIdx.x * 16 + c;  // this lane's sample (column)
-    const bool ok = t < nb;
-    // lanes past the batch compute on its first sample and store nothing
-    const int64_t s = idx ? (int64_t)idx[base + (ok ? t : 0)] : base + (ok ? t : 0);
-    // layer 1: z1[mt][i] = unit 16 mt + 4 g + i; K = the 20 features
-    f32x4_t h1[4], gp1[4];
+// Four values of a lane from four consecutive floats at any float alignment.
+__device__ __forceinline__ f32x4_t load4(const float *p) {
+    f32x4_t v;
+    __builtin_memcpy(&v, p, sizeof(v));
+    return v;
+}
+
+// LDS image of a [64 units][16 samples] block of activations or gradients:
+// the accumulator of the wave that owns row tile mt (lane l = 16 g + c: units
+// 16 mt + 4 g + i of sample c) as one 16-byte slot per lane; 16 floats of
+// padding per lane group spread the transposed reads (unit c of samples
+// 4 ks + g) over all banks.
+constexpr int kGrpStride = 80, kTileStride = 4 * kGrpStride;
+__device__ __forceinline__ int slot_of(int tile, int g, int c) { return tile * kTileStride + g * kGrpStride + 4 * c; }
+__device__ __forceinline__ int slot_unit(int tile, int u, int t) {
+    return tile * kTileStride + (u >> 2) * kGrpStride + 4 * t + (u & 3);
+}
+
+// Forward, backward and weight gradients of one mini-batch.  A block of four
+// waves takes 16 samples at a time (blocks stride over the 16-sample groups);
+// wave w owns the hidden units 16 w .. 16 w + 15 of both hidden layers, so a
+// layer is one 16 x 16 tile per wave and the four waves exchange activations
+// and pre-activation gradients through LDS.  Everything is an FP32
+// matrix-core product (v_mfma_f32_16x16x4f32: lane l holds A[l % 16][l / 16],
+// B[l / 16][l % 16] and C[4 (l / 16) + i][l % 16], i = 0..3), hidden units as
+// rows and samples as columns.  An accumulator (lane l: units 16 mt + 4 (l /
+// 16) + i of sample l % 16) is the next product's B operand as it is when the
+// K steps run over (mt, i), with the weight operand read at the same unit.
+// The weight gradients are products over the group's samples (K = 16),
+// accumulated in registers over the block's groups: dW2 = dZ2^T H1, dW1 =
+// dZ1^T X, dW3 = dY^T H2 (row tile w each; dW3: column tile w), the bias
+// gradients with a column of ones (feature 20 of the padded X; one more
+// column tile for dW2 and dW3), the loss in the padding row 15 of dY^T.  Each
+// block writes its partial sums part[block][kMlpParams + 1].
+//
+// What bounds it: a batch of 4,096 is 256 groups, one block per CU, and each
+// layer waits for the one before, so it is a chain of about 80 matrix
+// products per wave.  One wave per 16 samples that walked all four row tiles
+// (320 products in a chain on a quarter of the SIMDs), the activations and
+// gradients sent through memory to a second kernel for the weight gradients,
+// took 13.4 + 11.6 us at batch 4,096; an iteration with its partial sums and
+// Adam went from 28.0 to 14.3 us.
+__global__ __launch_bounds__(256) void k_train(const float *__restrict__ X, const float *__restrict__ Y,
+                                               const int32_t *__restrict__ idx, int64_t base, int nb,
+                                               const float *__restrict__ W, float *__restrict__ part_all,
+                                               int64_t n_mean) {
+    __shared__ __align__(16) float sH1[4 * kTileStride], sH2[4 * kTileStride], sZ1[4 * kTileStride],
+        sZ2[4 * kTileStride], sYp[4 * 256], sdY[kTileStride], sloss[16];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+    const int ngrp = (nb + 15) / 16;
+    // weights of this wave's row tile, read once per block
+    float a1[5], a2b[16], a3b[4];
+    f32x4_t a2f[4], a3f;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int ks = 0; ks < 5; ++ks) a1[ks] = W[kW1 + (16 * w + c) * kMlpIn + 4 * ks + g];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) h1[mt][i] = W[kB1 + 16 * mt + 4 * g + i];
-#pragma unroll
-    for (int ks = 0; ks < kMlpIn / 4; ++ks) {
-        const float b = X[s * kMlpIn + 4 * ks + g];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-            h1[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(W[kW1 + (16 * mt + c) * kMlpIn + 4 * ks + g], b, h1[mt],
-                                                        0, 0, 0);
-    }
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float h, gp;
-            gelu_and_prime(h1[mt][i], h, gp);
-            h1[mt][i] = h;
-            gp1[mt][i] = gp;
-        }
-    // layer 2: K steps over the layer-1 units
-    f32x4_t h2[4], gp2[4];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) h2[mt][i] = W[kB2 + 16 * mt + 4 * g + i];
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-        for (int ki = 0; ki < 4; ++ki) {
-            const int k = 16 * kt + 4 * g + ki;
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
-                h2[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(W[kW2 + (16 * mt + c) * kMlpHid + k], h1[kt][ki], h2[mt],
-                                                            0, 0, 0);
-        }
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float h, gp;
-            gelu_and_prime(h2[mt][i], h, gp);
-            h2[mt][i] = h;
-            gp2[mt][i] = gp;
-        }
-    // layer 3: outputs 4 g + i (row 15 padding)
-    f32x4_t y;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) y[i] = (4 * g + i < kMlpOut) ? W[kB3 + 4 * g + i] : 0.0f;
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-        for (int ki = 0; ki < 4; ++ki) {
-            const int k = 16 * kt + 4 * g + ki;
-            const float a = (c < kMlpOut) ? W[kW3 + c * kMlpHid + k] : 0.0f;
-            y = __builtin_amdgcn_mfma_f32_16x16x4f32(a, h2[kt][ki], y, 0, 0, 0);
-        }
-    // loss terms and dY
-    const float sc = 2.0f / ((float)T.n_mean * (float)kMlpOut);
-    f32x4_t dy;
-    float l = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int k = 4 * g + i;
-        const float e = (k < kMlpOut) ? y[i] - Y[s * kMlpOut + (k < kMlpOut ? k : 0)] : 0.0f;
-        l += e * e;
-        dy[i] = sc * e;
-    }
-    // the sample's loss: the four lane groups summed in a fixed order
-    const float l1 = __shfl_xor(l, 16), l2 = __shfl_xor(l, 32), l3 = __shfl_xor(l, 48);
-    const float lsum = (g == 0) ? (l + l1) + (l2 + l3) : 0.0f;
-    // back through layer 3: dH2 = W3^T dY, K = the 16 (15 + padding) outputs
-    f32x4_t dz2[4];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) dz2[mt] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int kt = 0; kt < 4; ++kt) a2f[kt] = load4(W + kW2 + (16 * w + c) * kMlpHid + 16 * kt + 4 * g);
+    a3f = load4(W + kW3 + (c < kMlpOut ? c : 0) * kMlpHid + 16 * w + 4 * g);
+    if (c >= kMlpOut) a3f = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int ki = 0; ki < 4; ++ki) {
         const int k = 4 * g + ki;
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            const float a = (k < kMlpOut) ? W[kW3 + (k < kMlpOut ? k : 0) * kMlpHid + 16 * mt + c] : 0.0f;
-            dz2[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, dy[ki], dz2[mt], 0, 0, 0);
-        }
+        a3b[ki] = W[kW3 + (k < kMlpOut ? k : 0) * kMlpHid + 16 * w + c];
+        if (k >= kMlpOut) a3b[ki] = 0.0f;
     }
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) dz2[mt][i] *= gp2[mt][i];
-    // back through layer 2: dH1 = W2^T dZ2
-    f32x4_t dz1[4];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) dz1[mt] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-        for (int ki = 0; ki < 4; ++ki) {
-            const int k = 16 * kt + 4 * g + ki;
+        for (int ki = 0; ki < 4; ++ki) a2b[4 * kt + ki] = W[kW2 + (16 * kt + 4 * g + ki) * kMlpHid + 16 * w + c];
+    const f32x4_t b1 = load4(W + kB1 + 16 * w + 4 * g), b2 = load4(W + kB2 + 16 * w + 4 * g);
+    f32x4_t b3;
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
-                dz1[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(W[kW2 + k * kMlpHid + 16 * mt + c], dz2[kt][ki], dz1[mt],
-                                                             0, 0, 0);
+    for (int i = 0; i < 4; ++i) b3[i] = (4 * g + i < kMlpOut) ? W[kB3 + 4 * g + i] : 0.0f;
+    const f32x4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4_t gW2[5], gW1[2], gW3[2];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) gW2[q] = zero;
+    gW1[0] = gW1[1] = gW3[0] = gW3[1] = zero;
+    const float sc = 2.0f / ((float)n_mean * (float)kMlpOut);
+    for (int grp = blockIdx.x; grp < ngrp; grp += gridDim.x) {
+        // this lane's sample as a column (t) and, for dW1, as a K step;
+        // lanes past the batch compute on its first sample with zero weight
+        const int t = 16 * grp + c;
+        const bool ok = t < nb;
+        const int64_t s = idx ? (int64_t)idx[base + (ok ? t : 0)] : base + (ok ? t : 0);
+        int64_t sk[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const int tk = 16 * grp + 4 * ks + g;
+            sk[ks] = idx ? (int64_t)idx[base + (tk < nb ? tk : 0)] : base + (tk < nb ? tk : 0);
         }
+        float x1[5], xk[4][2], yt[4];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+        for (int ks = 0; ks < 5; ++ks) x1[ks] = X[s * kMlpIn + 4 * ks + g];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) dz1[mt][i] *= gp1[mt][i];
-    if (!ok) return;
-    // [t][64] rows: four consecutive units per lane and row tile
-    const int64_t r64 = (int64_t)t * 64 + 4 * g;
+        for (int i = 0; i < 4; ++i) yt[i] = Y[s * kMlpOut + (4 * g + i < kMlpOut ? 4 * g + i : 0)];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-        *reinterpret_cast<f32x4_t *>(T.H1 + r64 + 16 * mt) = h1[mt];
-        *reinterpret_cast<f32x4_t *>(T.H2 + r64 + 16 * mt) = h2[mt];
-        *reinterpret_cast<f32x4_t *>(T.dZ1 + r64 + 16 * mt) = dz1[mt];
-        *reinterpret_cast<f32x4_t *>(T.dZ2 + r64 + 16 * mt) = dz2[mt];
-    }
-    *reinterpret_cast<f32x4_t *>(T.dY + (int64_t)t * 16 + 4 * g) = dy;
-    if (g == 0) T.lossv[t] = lsum;
-}
-
-// partial sums over chunk c (samples 64c .. 64c+63) of each parameter's
-// gradient and (q = kMlpParams) of the losses: part[c][q].  The weight
-// gradients are products over the chunk's samples on the FP32 matrix cores
-// (operand layout as in k_fwd_bwd; K = the samples, 16 steps of 4): dW2 =
-// dZ2^T H1 (waves 0 and 1, 8 tiles each), dW1 = dZ1^T X (wave 2, features
-// padded to 32), dW3 = dY^T H2 (wave 3, outputs padded to 16).  The bias
-// gradients are the same products with a column of ones (feature 20 of the
-// padded X; one more column tile for dW2 and dW3), and the loss rides in
-// the padding row 15 of dY^T.  Samples past the batch enter as zeros.
-__global__ __launch_bounds__(256) void k_wgrad(const float *__restrict__ X, const int32_t *__restrict__ idx,
-                                               int64_t base, int nb, TrainBufs T) {
-    const int c = blockIdx.x, w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
-    const int t0 = 64 * c, t1 = min(nb, t0 + 64);
-    float *part = T.part + (int64_t)c * (kMlpParams + 1);
-    // operand of sample t0 + 4 ks + g: row t of a [t][ld] array at column col
-    auto opnd = [&](const float *A, int ld, int ks, int col) {
-        const int t = t0 + 4 * ks + g;
-        return (t < t1) ? A[(int64_t)t * ld + col] : 0.0f;
-    };
-    if (w < 2) {
-        // dW2[j][k] = sum_t dZ2[t][j] H1[t][k], rows j in tiles 2w, 2w + 1;
-        // column tile 4: a column of ones (db2)
-        f32x4_t acc[2][5];
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int nt = 0; nt < 5; ++nt) acc[a][nt] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        // every operand of the chunk first (one wait), then the products
-        float av[16][2], bv[16][4];
-#pragma unroll
-        for (int ks = 0; ks < 16; ++ks) {
-#pragma unroll
-            for (int a = 0; a < 2; ++a) av[ks][a] = opnd(T.dZ2, 64, ks, 16 * (2 * w + a) + r);
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) bv[ks][nt] = opnd(T.H1, 64, ks, 16 * nt + r);
+        for (int ks = 0; ks < 4; ++ks) {
+            xk[ks][0] = X[sk[ks] * kMlpIn + c];
+            xk[ks][1] = X[sk[ks] * kMlpIn + (c < 4 ? 16 + c : 0)];
+            if (c >= 4) xk[ks][1] = (c == 4) ? 1.0f : 0.0f;
         }
+        // layer 1
+        f32x4_t h1 = b1, p1, h2 = b2, p2;
 #pragma unroll
-        for (int ks = 0; ks < 16; ++ks) {
-            const float one = (r == 0 && t0 + 4 * ks + g < t1) ? 1.0f : 0.0f;
+        for (int ks = 0; ks < 5; ++ks) h1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[ks], x1[ks], h1, 0, 0, 0);
 #pragma unroll
-            for (int a = 0; a < 2; ++a) {
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt)
-                    acc[a][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks][a], bv[ks][nt], acc[a][nt], 0, 0, 0);
-                acc[a][4] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks][a], one, acc[a][4], 0, 0, 0);
-            }
+        for (int i = 0; i < 4; ++i) {
+            float h, gp;
+            gelu_and_prime(h1[i], h, gp);
+            h1[i] = h;
+            p1[i] = gp;
         }
+        *reinterpret_cast<f32x4_t *>(sH1 + slot_of(w, g, c)) = h1;
+        __syncthreads();
+        // layer 2
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+        for (int kt = 0; kt < 4; ++kt) {
+            const f32x4_t b = *reinterpret_cast<const f32x4_t *>(sH1 + slot_of(kt, g, c));
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int j = 16 * (2 * w + a) + 4 * g + i;
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt) part[kW2 + j * kMlpHid + 16 * nt + r] = acc[a][nt][i];
-                if (r == 0) part[kB2 + j] = acc[a][4][i];
-            }
-    } else if (w == 2) {
-        // dW1[j][i] = sum_t dZ1[t][j] X[s_t][i]
-        f32x4_t acc[4][2];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        // every operand of the chunk first (sample indices, then the rest)
-        int64_t smp[16];
-#pragma unroll
-        for (int ks = 0; ks < 16; ++ks) {
-            const int t = t0 + 4 * ks + g;
-            const int tc = (t < t1) ? t : t0;
-            smp[ks] = idx ? (int64_t)idx[base + tc] : base + tc;
-        }
-        float av[16][4], bv[16][2];
-#pragma unroll
-        for (int ks = 0; ks < 16; ++ks) {
-            const bool in = t0 + 4 * ks + g < t1;
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) av[ks][mt] = opnd(T.dZ1, 64, ks, 16 * mt + r);
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                const int f = 16 * nt + r;
-                bv[ks][nt] = !in ? 0.0f : (f < kMlpIn) ? X[smp[ks] * kMlpIn + f] : (f == kMlpIn) ? 1.0f : 0.0f;
-            }
-        }
-#pragma unroll
-        for (int ks = 0; ks < 16; ++ks)
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < 2; ++nt)
-                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks][mt], bv[ks][nt], acc[mt][nt], 0, 0, 0);
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int f = 16 * nt + r, j = 16 * mt + 4 * g + i;
-                    if (f < kMlpIn) part[kW1 + j * kMlpIn + f] = acc[mt][nt][i];
-                    else if (f == kMlpIn) part[kB1 + j] = acc[mt][nt][i];
-                }
-    } else {
-        // dW3[k][j] = sum_t dY[t][k] H2[t][j]; row 15 carries the sample
-        // losses, column tile 4 a column of ones (db3 and the loss)
-        f32x4_t acc[5];
-#pragma unroll
-        for (int nt = 0; nt < 5; ++nt) acc[nt] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        float av[16], bv[16][4];
-#pragma unroll
-        for (int ks = 0; ks < 16; ++ks) {
-            av[ks] = (r < kMlpOut) ? opnd(T.dY, 16, ks, r) : opnd(T.lossv, 1, ks, 0);
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) bv[ks][nt] = opnd(T.H2, 64, ks, 16 * nt + r);
-        }
-#pragma unroll
-        for (int ks = 0; ks < 16; ++ks) {
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
-                acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks], bv[ks][nt], acc[nt], 0, 0, 0);
-            const float one = (r == 0 && t0 + 4 * ks + g < t1) ? 1.0f : 0.0f;
-            acc[4] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks], one, acc[4], 0, 0, 0);
+            for (int ki = 0; ki < 4; ++ki) h2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a2f[kt][ki], b[ki], h2, 0, 0, 0);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int k = 4 * g + i;
-            if (k < kMlpOut) {
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt) part[kW3 + k * kMlpHid + 16 * nt + r] = acc[nt][i];
-                if (r == 0) part[kB3 + k] = acc[4][i];
-            } else if (r == 0) {
-                part[kMlpParams] = acc[4][i];
-            }
+            float h, gp;
+            gelu_and_prime(h2[i], h, gp);
+            h2[i] = h;
+            p2[i] = gp;
         }
+        *reinterpret_cast<f32x4_t *>(sH2 + slot_of(w, g, c)) = h2;
+        // layer 3: each wave its own units' part of the outputs 4 g + i (row
+        // 15 padding), summed over the waves in a fixed order
+        f32x4_t yp = zero;
+#pragma unroll
+        for (int ki = 0; ki < 4; ++ki) yp = __builtin_amdgcn_mfma_f32_16x16x4f32(a3f[ki], h2[ki], yp, 0, 0, 0);
+        *reinterpret_cast<f32x4_t *>(sYp + 256 * w + 4 * lane) = yp;
+        __syncthreads();
+        f32x4_t q[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const f32x4_t *>(sYp + 256 * u + 4 * lane);
+        const f32x4_t y = ((q[0] + q[1]) + (q[2] + q[3])) + b3;
+        f32x4_t dy;
+        float l = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float e = (ok && 4 * g + i < kMlpOut) ? y[i] - yt[i] : 0.0f;
+            l += e * e;
+            dy[i] = sc * e;
+        }
+        if (w == 0) {
+            // the sample's loss: the four lane groups in a fixed order
+            const float l1 = __shfl_xor(l, 16), l2 = __shfl_xor(l, 32), l3 = __shfl_xor(l, 48);
+            *reinterpret_cast<f32x4_t *>(sdY + slot_of(0, g, c)) = dy;
+            if (g == 0) sloss[c] = (l + l1) + (l2 + l3);
+        }
+        // back through layer 3 and layer 2
+        f32x4_t dz2 = zero, dz1 = zero;
+#pragma unroll
+        for (int ki = 0; ki < 4; ++ki) dz2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a3b[ki], dy[ki], dz2, 0, 0, 0);
+        dz2 *= p2;
+        *reinterpret_cast<f32x4_t *>(sZ2 + slot_of(w, g, c)) = dz2;
+        __syncthreads();
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) {
+            const f32x4_t b = *reinterpret_cast<const f32x4_t *>(sZ2 + slot_of(kt, g, c));
+#pragma unroll
+            for (int ki = 0; ki < 4; ++ki)
+                dz1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a2b[4 * kt + ki], b[ki], dz1, 0, 0, 0);
+        }
+        dz1 *= p1;
+        // (read back by this wave alone)
+        *reinterpret_cast<f32x4_t *>(sZ1 + slot_of(w, g, c)) = dz1;
+        __builtin_amdgcn_wave_barrier();
+        // weight gradients over the group's samples
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const int tk = 4 * ks + g;
+            const float z2 = sZ2[slot_unit(w, c, tk)], one = (c == 0) ? 1.0f : 0.0f;
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt)
+                gW2[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(z2, sH1[slot_unit(nt, c, tk)], gW2[nt], 0, 0, 0);
+            gW2[4] = __builtin_amdgcn_mfma_f32_16x16x4f32(z2, one, gW2[4], 0, 0, 0);
+            const float ys = (c < kMlpOut) ? sdY[slot_unit(0, c, tk)] : sloss[tk];
+            gW3[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(ys, sH2[slot_unit(w, c, tk)], gW3[0], 0, 0, 0);
+            if (w == 0) gW3[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(ys, one, gW3[1], 0, 0, 0);
+            const float z1 = sZ1[slot_unit(w, c, tk)];
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt)
+                gW1[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(z1, xk[ks][nt], gW1[nt], 0, 0, 0);
+        }
+        __syncthreads();  // the next group rewrites the LDS images
+    }
+    float *part = part_all + (int64_t)blockIdx.x * (kMlpParams + 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int j = 16 * w + 4 * g + i;
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) part[kW2 + j * kMlpHid + 16 * nt + c] = gW2[nt][i];
+        if (c == 0) part[kB2 + j] = gW2[4][i];
+        part[kW1 + j * kMlpIn + c] = gW1[0][i];
+        if (c < 4) part[kW1 + j * kMlpIn + 16 + c] = gW1[1][i];
+        if (c == 4) part[kB1 + j] = gW1[1][i];
+        const int k = 4 * g + i;
+        if (k < kMlpOut) part[kW3 + k * kMlpHid + 16 * w + c] = gW3[0][i];
+        if (w == 0 && c == 0) part[k < kMlpOut ? kB3 + k : kMlpParams] = gW3[1][i];
     }
 }
 
-// sum over the chunks of quantity q in a fixed order: four running sums on
-// four lanes (lane 4 q' + r sums chunks r, r + 4, ... in turn), combined
-// pairwise as (s0 + s1) + (s2 + s3)
-__device__ __forceinline__ float chunk_sum(int nchunk, const float *__restrict__ part, int q) {
-    const int r = threadIdx.x & 3;
+// sum over the blocks' partials of 64 consecutive quantities (one per lane:
+// whole cache lines) in a fixed order: wave r of the block sums partials r,
+// r + 8, ... in turn, the eight sums combined pairwise; valid in wave 0
+__device__ __forceinline__ float partial_sum(int nchunk, const float *__restrict__ part, int q, float (*red)[64]) {
+    const int r = threadIdx.x >> 6, lane = threadIdx.x & 63;
     float a = 0.0f;
-    // 16 chunks per lane and round, every load of a round issued first
-    for (int c0 = r; c0 < nchunk; c0 += 64) {
+    // 16 partials per wave and round, every load of a round issued first
+    for (int c0 = r; c0 < nchunk; c0 += 128) {
         float v[16];
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
-            const int c = c0 + 4 * u;
-            v[u] = part[(int64_t)(c < nchunk ? c : r) * (kMlpParams + 1) + q];
+            const int c = c0 + 8 * u;
+            v[u] = part[(int64_t)(c < nchunk ? c : c0) * (kMlpParams + 1) + q];
         }
 #pragma unroll
         for (int u = 0; u < 16; ++u)
-            if (c0 + 4 * u < nchunk) a += v[u];
+            if (c0 + 8 * u < nchunk) a += v[u];
     }
-    const float p = a + __shfl_xor(a, 1);
-    return p + __shfl_xor(p, 2);
+    red[r][lane] = a;
+    __syncthreads();
+    return ((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane])) +
+           ((red[4][lane] + red[5][lane]) + (red[6][lane] + red[7][lane]));
 }
 
-// four lanes per quantity (parameter, or the loss for q = kMlpParams)
-__global__ __launch_bounds__(64) void k_wgrad_sum(int nchunk, const float *__restrict__ part, int64_t n_mean,
-                                                  float *__restrict__ grad, float *__restrict__ loss) {
-    const int qq = (blockIdx.x * 64 + (int)threadIdx.x) >> 2, q = qq <= kMlpParams ? qq : kMlpParams;
-    const float s = chunk_sum(nchunk, part, q);
-    if ((threadIdx.x & 3) != 0 || qq > kMlpParams) return;
+// one lane per quantity (parameter, or the loss for q = kMlpParams)
+__global__ __launch_bounds__(512) void k_wgrad_sum(int nchunk, const float *__restrict__ part, int64_t n_mean,
+                                                   float *__restrict__ grad, float *__restrict__ loss) {
+    __shared__ float red[8][64];
+    const int qq = blockIdx.x * 64 + (int)(threadIdx.x & 63), q = qq <= kMlpParams ? qq : kMlpParams;
+    const float s = partial_sum(nchunk, part, q, red);
+    if (threadIdx.x >= 64 || qq > kMlpParams) return;
     if (q < kMlpParams) grad[q] = s;
     else loss[0] = s / ((float)n_mean * (float)kMlpOut);
 }
@@ -417,12 +349,13 @@ __device__ __forceinline__ void adam_update(float *__restrict__ W, float *__rest
     W[q] -= a.lr * (mq * a.inv_bc1) / (sqrtf(vq * a.inv_bc2) + a.eps);
 }
 
-__global__ __launch_bounds__(64) void k_wgrad_sum_adam(int nchunk, const float *__restrict__ part, int64_t n_mean,
-                                                       float *__restrict__ W, float *__restrict__ m,
-                                                       float *__restrict__ v, AdamArgs a, float *__restrict__ loss) {
-    const int qq = (blockIdx.x * 64 + (int)threadIdx.x) >> 2, q = qq <= kMlpParams ? qq : kMlpParams;
-    const float s = chunk_sum(nchunk, part, q);
-    if ((threadIdx.x & 3) != 0 || qq > kMlpParams) return;
+__global__ __launch_bounds__(512) void k_wgrad_sum_adam(int nchunk, const float *__restrict__ part, int64_t n_mean,
+                                                        float *__restrict__ W, float *__restrict__ m,
+                                                        float *__restrict__ v, AdamArgs a, float *__restrict__ loss) {
+    __shared__ float red[8][64];
+    const int qq = blockIdx.x * 64 + (int)(threadIdx.x & 63), q = qq <= kMlpParams ? qq : kMlpParams;
+    const float s = partial_sum(nchunk, part, q, red);
+    if (threadIdx.x >= 64 || qq > kMlpParams) return;
     if (q < kMlpParams) adam_update(W, m, v, s, a, q);
     else loss[0] = s / ((float)n_mean * (float)kMlpOut);
 }
@@ -501,32 +434,30 @@ hipError_t launch_pack(const float *W, const float *norm, unsigned char *model, 
     return hipGetLastError();
 }
 
-// forward/backward and the chunk partials of the gradient and the loss
-static hipError_t launch_train_partials(const float *X, const float *Y, const int32_t *idx, int64_t base, int nb,
-                                        const float *W, const TrainBufs &T, hipStream_t s) {
-    const int nchunk = (nb + 63) / 64;
-    hipLaunchKernelGGL(k_fwd_bwd, dim3((nb + 15) / 16), dim3(64), 0, s, X, Y, idx, base, nb, W, T);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wgrad, dim3(nchunk), dim3(256), 0, s, X, idx, base, nb, T);
-    return hipGetLastError();
-}
+// blocks of k_train for a mini-batch: one per 16 samples up to
+// kTrainPartials, beyond which a block takes several groups in turn
+static int train_blocks(int nb) { return std::min((nb + 15) / 16, kTrainPartials); }
+static constexpr int kSumBlocksMlp = (kMlpParams + 1 + 63) / 64;
 
 hipError_t launch_train_grad(const float *X, const float *Y, const int32_t *idx, int64_t base, int nb,
                              const float *W, const TrainBufs &T, float *grad, float *loss, hipStream_t s) {
-    hipError_t e = launch_train_partials(X, Y, idx, base, nb, W, T, s);
+    const int nblk = train_blocks(nb);
+    hipLaunchKernelGGL(k_train, dim3(nblk), dim3(256), 0, s, X, Y, idx, base, nb, W, T.part, T.n_mean);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wgrad_sum, dim3((4 * (kMlpParams + 1) + 63) / 64), dim3(64), 0, s, (nb + 63) / 64,
-                       (const float *)T.part, T.n_mean, grad, loss);
+    hipLaunchKernelGGL(k_wgrad_sum, dim3(kSumBlocksMlp), dim3(512), 0, s, nblk, (const float *)T.part, T.n_mean, grad,
+                       loss);
     return hipGetLastError();
 }
 
 hipError_t launch_train_step(const float *X, const float *Y, const int32_t *idx, int64_t base, int nb, float *W,
                              float *m, float *v, const TrainBufs &T, const AdamArgs &a, float *loss, hipStream_t s) {
-    hipError_t e = launch_train_partials(X, Y, idx, base, nb, W, T, s);
+    const int nblk = train_blocks(nb);
+    hipLaunchKernelGGL(k_train, dim3(nblk), dim3(256), 0, s, X, Y, idx, base, nb, W, T.part, T.n_mean);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wgrad_sum_adam, dim3((4 * (kMlpParams + 1) + 63) / 64), dim3(64), 0, s, (nb + 63) / 64,
-                       (const float *)T.part, T.n_mean, W, m, v, a, loss);
+    hipLaunchKernelGGL(k_wgrad_sum_adam, dim3(kSumBlocksMlp), dim3(512), 0, s, nblk, (const float *)T.part, T.n_mean, W,
+                       m, v, a, loss);
     return hipGetLastError();
 }
 

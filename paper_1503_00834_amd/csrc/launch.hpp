@@ -67,13 +67,11 @@ hipError_t launch_flux64(const Mesh &m, const Geo &G, const PhysParams &P, const
 hipError_t launch_lift64(const Mesh &m, const Geo &G, const double *TV, const StageArgs &sa, bool closure,
                          hipStream_t s);
 
-// closure training buffers for a mini-batch of nb samples (rows of 64 or 16)
+// closure training: the partial gradients and losses of one mini-batch
+constexpr int kTrainPartials = 512;  // partials at most (blocks of k_train)
 struct TrainBufs {
-    float *H1, *H2, *dZ1, *dZ2;  // [nb][64]: activations and pre-activation gradients
-    float *dY;                   // [nb][16]
-    float *lossv;                // [nb]
-    float *part;                 // [ceil(nb/64)][6480] chunk partial gradients and losses
-    int64_t n_mean;              // samples the loss is averaged over
+    float *part;     // [min(ceil(nb / 16), kTrainPartials)][6480]
+    int64_t n_mean;  // samples the loss is averaged over
 };
 
 struct AdamArgs {

@@ -295,6 +295,29 @@ def test_grad_matches_oracle(ch, cl, torch_dev, n):
         assert err <= 1e-4 * np.linalg.norm(g_want[lo:hi]), (lo, err)
 
 
+@pytest.mark.parametrize("n", [15, 16, 33, 8192, 8209])
+def test_grad_at_group_edges(ch, cl, torch_dev, n):
+    """One group of 16 samples and its neighbours; the largest batch with one
+    group per block (8,192) and one where blocks take a second group."""
+    torch = torch_dev
+    rng = np.random.default_rng(61 + n)
+    X = rng.normal(size=(n, 20)).astype(np.float32)
+    T = rng.normal(size=(n, 15)).astype(np.float32)
+    p = (mlp_init(14) * 1.2).astype(np.float32)
+    g_want = cl.grad(p, X, T)
+    ws = ch.closure_train_workspace(n)
+    grad = torch.zeros(6479, dtype=torch.float32, device="cuda")
+    loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+    ch.chorus_closure_grad(_dev(torch, X, torch.float32), _dev(torch, T, torch.float32),
+                           _dev(torch, p, torch.float32), grad, loss, ws)
+    torch.cuda.synchronize()
+    g = grad.cpu().numpy().astype(np.float64)
+    assert abs(loss.item() - cl.loss(p, X, T)) <= 1e-5 * loss.item()
+    for lo, hi in ((0, 1280), (1280, 1344), (1344, 5440), (5440, 5504), (5504, 6464), (6464, 6479)):
+        err = np.linalg.norm(g[lo:hi] - g_want[lo:hi])
+        assert err <= 1e-4 * np.linalg.norm(g_want[lo:hi]), (lo, err)
+
+
 def test_train_matches_oracle_and_is_deterministic(ch, cl, torch_dev):
     torch = torch_dev
     rng = np.random.default_rng(31)
