@@ -374,55 +374,131 @@ __device__ __forceinline__ void cart_flux(const double q[5], double gm1, double 
     }
 }
 
+// Elements per block of one wave: a lane takes one xi line of an element in
+// the first contraction, NF^2 lines per element.
+template <int NF>
+constexpr int filter_epb() { return 64 / (NF * NF); }
+
+// Bound by its HBM bytes (6 doubles per fine point read, 20 per coarse point
+// written: 180 MB from order 6 to 3 on 12,288 hexes).  The 20 products |J| Q
+// and |J| F(Q) of a fine point never reach memory: the lane of a xi line forms
+// them point by point and adds each into its NC projected values, so LDS
+// first holds them contracted (20 NC NF^2 doubles per element, 17 KB at 6 ->
+// 3, nine waves per CU; the eta and zeta contractions are written over it
+// after a barrier).  With the orders as run-time values, every product in
+// LDS (61 KB per element, two waves per CU) and an index division per
+// multiply-add, the filter took 1,005 us; a pass of filter and features went
+// from 1,038 to 99 us.
+template <int NF, int NC>
 __global__ __launch_bounds__(64) void k_filter(FilterArgs A) {
-    constexpr int MAXF = 6, MAXC = 3;
-    __shared__ double U[20][MAXF * MAXF * MAXF];   // |J| Q (5) and |J| F(Q) (15) at the fine points
-    __shared__ double T1[20][MAXC * MAXF * MAXF];  // after the xi pass
-    __shared__ double T2[20][MAXC * MAXC * MAXF];  // after the eta pass
-    const int64_t e = blockIdx.x;
-    const int nf = A.nf, nc = A.nc, NPF = nf * nf * nf, NPC = nc * nc * nc;
+    constexpr int EPB = filter_epb<NF>(), L2 = NF * NF, NPF = NF * NF * NF, NPC = NC * NC * NC;
+    constexpr int S1 = 20 * NC * L2, IT_ETA = 20 * NC * NF, IT_ZETA = 20 * NC * NC;
+    constexpr int R_ETA = (EPB * IT_ETA + 63) / 64, R_ZETA = (EPB * IT_ZETA + 63) / 64;
+    __shared__ double T[EPB][S1];
+    const int64_t e0 = (int64_t)blockIdx.x * EPB;
     const double gm1 = A.gamma - 1.0;
-    for (int p = threadIdx.x; p < NPF; p += 64) {
-        double q[5], F[15];
-        for (int v = 0; v < 5; ++v) q[v] = A.Qf[((int64_t)v * A.E + e) * NPF + p];
-        const double J = 1.0 / A.solgeo_f[(e * 13 + 9) * NPF + p];
-        cart_flux(q, gm1, F);
-        for (int v = 0; v < 5; ++v) U[v][p] = J * q[v];
-        for (int k = 0; k < 15; ++k) U[5 + k][p] = J * F[k];
-    }
-    __syncthreads();
     // xi: (a, j, k) <- sum_i P[a][i] U(i, j, k)
-    for (int it = threadIdx.x; it < 20 * nc * nf * nf; it += 64) {
-        const int f = it / (nc * nf * nf), r = it % (nc * nf * nf), a = r % nc, jk = r / nc;
-        double s = 0.0;
-        for (int i = 0; i < nf; ++i) s += A.P[a][i] * U[f][i + nf * jk];
-        T1[f][a + nc * jk] = s;
-    }
-    __syncthreads();
-    // eta: (a, b, k) <- sum_j P[b][j] T1(a, j, k)
-    for (int it = threadIdx.x; it < 20 * nc * nc * nf; it += 64) {
-        const int f = it / (nc * nc * nf), r = it % (nc * nc * nf), a = r % nc, b = (r / nc) % nc, k = r / (nc * nc);
-        double s = 0.0;
-        for (int j = 0; j < nf; ++j) s += A.P[b][j] * T1[f][a + nc * (j + nf * k)];
-        T2[f][a + nc * (b + nc * k)] = s;
-    }
-    __syncthreads();
-    // zeta, divide by the coarse |J|, subgrid flux
-    for (int p = threadIdx.x; p < NPC; p += 64) {
-        const int a = p % nc, b = (p / nc) % nc, c = p / (nc * nc);
-        double g[20];
-        for (int f = 0; f < 20; ++f) {
-            double s = 0.0;
-            for (int k = 0; k < nf; ++k) s += A.P[c][k] * T2[f][a + nc * (b + nc * k)];
-            g[f] = s;
+    {
+        const int el = threadIdx.x / L2, jk = threadIdx.x % L2;
+        if (el < EPB && e0 + el < A.E) {
+            const int64_t e = e0 + el;
+            double acc[20][NC];
+#pragma unroll
+            for (int f = 0; f < 20; ++f)
+#pragma unroll
+                for (int a = 0; a < NC; ++a) acc[f][a] = 0.0;
+            // the whole line first: one wait for memory
+            double ql[NF][5], iJ[NF];
+#pragma unroll
+            for (int i = 0; i < NF; ++i) {
+                const int p = i + NF * jk;
+                for (int v = 0; v < 5; ++v) ql[i][v] = A.Qf[((int64_t)v * A.E + e) * NPF + p];
+                iJ[i] = A.solgeo_f[(e * 13 + 9) * NPF + p];
+            }
+#pragma unroll
+            for (int i = 0; i < NF; ++i) {
+                const double J = 1.0 / iJ[i];
+                double F[15];
+                cart_flux(ql[i], gm1, F);
+#pragma unroll
+                for (int f = 0; f < 20; ++f) {
+                    const double u = J * (f < 5 ? ql[i][f < 5 ? f : 0] : F[f < 5 ? 0 : f - 5]);
+#pragma unroll
+                    for (int a = 0; a < NC; ++a) acc[f][a] += A.P[a][i] * u;
+                }
+            }
+#pragma unroll
+            for (int f = 0; f < 20; ++f)
+#pragma unroll
+                for (int a = 0; a < NC; ++a) T[el][(f * L2 + jk) * NC + a] = acc[f][a];
         }
+    }
+    __syncthreads();
+    // eta: (a, b, k) <- sum_j P[b][j] T(a, j, k); a thread forms the NC
+    // values b of one (field, a, k)
+    double r[R_ETA][NC];
+#pragma unroll
+    for (int q = 0; q < R_ETA; ++q) {
+        const int it = threadIdx.x + 64 * q;
+        const int el = it / IT_ETA, x = it % IT_ETA, f = x / (NC * NF), ak = x % (NC * NF), a = ak % NC, k = ak / NC;
+#pragma unroll
+        for (int b = 0; b < NC; ++b) r[q][b] = 0.0;
+        if (el >= EPB || e0 + el >= A.E) continue;
+#pragma unroll
+        for (int j = 0; j < NF; ++j) {
+            const double t = T[el][(f * L2 + j + NF * k) * NC + a];
+#pragma unroll
+            for (int b = 0; b < NC; ++b) r[q][b] += A.P[b][j] * t;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < R_ETA; ++q) {
+        const int it = threadIdx.x + 64 * q;
+        const int el = it / IT_ETA, x = it % IT_ETA, f = x / (NC * NF), ak = x % (NC * NF), a = ak % NC, k = ak / NC;
+        if (el >= EPB) continue;
+#pragma unroll
+        for (int b = 0; b < NC; ++b) T[el][f * (NC * NC * NF) + a + NC * (b + NC * k)] = r[q][b];
+    }
+    __syncthreads();
+    // zeta: (a, b, c) <- sum_k P[c][k] T(a, b, k)
+    double z[R_ZETA][NC];
+#pragma unroll
+    for (int q = 0; q < R_ZETA; ++q) {
+        const int it = threadIdx.x + 64 * q;
+        const int el = it / IT_ZETA, x = it % IT_ZETA, f = x / (NC * NC), ab = x % (NC * NC);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) z[q][c] = 0.0;
+        if (el >= EPB || e0 + el >= A.E) continue;
+#pragma unroll
+        for (int k = 0; k < NF; ++k) {
+            const double t = T[el][f * (NC * NC * NF) + ab + NC * NC * k];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) z[q][c] += A.P[c][k] * t;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < R_ZETA; ++q) {
+        const int it = threadIdx.x + 64 * q;
+        const int el = it / IT_ZETA, x = it % IT_ZETA, f = x / (NC * NC), ab = x % (NC * NC);
+        if (el >= EPB) continue;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) T[el][f * NPC + ab + NC * NC * c] = z[q][c];
+    }
+    __syncthreads();
+    // divide by the coarse |J|, subgrid flux
+    for (int it = threadIdx.x; it < EPB * NPC; it += 64) {
+        const int el = it / NPC, p = it % NPC;
+        const int64_t e = e0 + el;
+        if (e >= A.E) continue;
         const double iJ = A.solgeo_c[(e * 13 + 9) * NPC + p];
         double qb[5], F[15];
-        for (int v = 0; v < 5; ++v) qb[v] = g[v] * iJ;
+        for (int v = 0; v < 5; ++v) qb[v] = T[el][v * NPC + p] * iJ;
         cart_flux(qb, gm1, F);
         for (int v = 0; v < 5; ++v) A.Qbar[((int64_t)v * A.E + e) * NPC + p] = qb[v];
         for (int k = 0; k < 15; ++k)
-            A.tau[((int64_t)k * A.E + e) * NPC + p] = (k < 3) ? 0.0 : g[5 + k] * iJ - F[k];
+            A.tau[((int64_t)k * A.E + e) * NPC + p] = (k < 3) ? 0.0 : T[el][(5 + k) * NPC + p] * iJ - F[k];
     }
 }
 
@@ -477,9 +553,24 @@ hipError_t launch_check_idx(const int32_t *idx, int64_t count, int64_t n, int *f
     return hipGetLastError();
 }
 
-hipError_t launch_filter(const FilterArgs &A, hipStream_t s) {
-    hipLaunchKernelGGL(k_filter, dim3((unsigned)A.E), dim3(64), 0, s, A);
+template <int NF, int NC>
+static hipError_t launch_filter_t(const FilterArgs &A, hipStream_t s) {
+    constexpr int EPB = filter_epb<NF>();
+    hipLaunchKernelGGL((k_filter<NF, NC>), dim3((unsigned)((A.E + EPB - 1) / EPB)), dim3(64), 0, s, A);
     return hipGetLastError();
+}
+
+hipError_t launch_filter(const FilterArgs &A, hipStream_t s) {
+    switch (10 * A.nf + A.nc) {
+        case 32: return launch_filter_t<3, 2>(A, s);
+        case 42: return launch_filter_t<4, 2>(A, s);
+        case 43: return launch_filter_t<4, 3>(A, s);
+        case 52: return launch_filter_t<5, 2>(A, s);
+        case 53: return launch_filter_t<5, 3>(A, s);
+        case 62: return launch_filter_t<6, 2>(A, s);
+        case 63: return launch_filter_t<6, 3>(A, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace chorus

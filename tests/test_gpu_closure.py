@@ -433,3 +433,33 @@ def test_closure_call_errors(ch, cl, oracle_mod, torch_dev):
     with pytest.raises(ch.ChorusError) as ei:
         ch.chorus_sd_residual(cm4, p0, Q4, torch.empty_like(Q4), ws)
     assert ei.value.status == -1
+
+
+@pytest.mark.parametrize("nf,nc", [(3, 2), (4, 2), (5, 2), (6, 2), (4, 3), (5, 3), (6, 3)])
+def test_filter_every_order_pair(ch, cl, oracle_mod, torch_dev, nf, nc):
+    """Every pair of orders on a box of 15 elements (a last block of the
+    kernel that holds several elements is partly empty); FP64 on both sides,
+    relative 1e-12 of each component's norm."""
+    torch = torch_dev
+    m = box_mesh(5, 3, 1, lengths=(1.0, 1.1, 0.9), curve=0.03)
+    of, oc = oracle_mod.OracleMesh(m, nf), oracle_mod.OracleMesh(m, nc)
+    rng = np.random.default_rng(10 * nf + nc)
+    n = of.n_solpts
+    Q = np.empty((5, n))
+    Q[0] = 1.0 + 0.2 * rng.random(n)
+    Q[1:4] = 0.3 * rng.standard_normal((3, n))
+    Q[4] = 2.5 + 0.2 * rng.random(n)
+    Qb_w, tau_w = cl.sgs_target(Q.reshape(5, of.E, -1), of.geometry()[0], oc.geometry()[0], nf, nc,
+                                oracle_mod.basis(nf)[0], oracle_mod.basis(nc)[0], 5 / 3)
+    mf, mc = ch.mesh_from_arrays(m, nf).upload(), ch.mesh_from_arrays(m, nc).upload()
+    Qb = torch.empty((5, mc.n_solpts), dtype=torch.float64, device="cuda")
+    tau = torch.empty((15, mc.n_solpts), dtype=torch.float64, device="cuda")
+    ch.chorus_closure_filter(mf, mc, 5 / 3, _dev(torch, Q), Qb, tau)
+    torch.cuda.synchronize()
+    Qb_w, tau_w = Qb_w.reshape(5, -1), tau_w.reshape(15, -1)
+    for v in range(5):
+        assert np.linalg.norm(Qb[v].cpu().numpy() - Qb_w[v]) <= 1e-12 * np.linalg.norm(Qb_w[v]), v
+    got = tau.cpu().numpy()
+    assert np.all(got[0:3] == 0.0)
+    for k in range(3, 15):
+        assert np.linalg.norm(got[k] - tau_w[k]) <= 1e-12 * np.linalg.norm(tau_w[k]), k
