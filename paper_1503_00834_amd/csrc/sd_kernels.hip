@@ -10,6 +10,7 @@
 //                 (pushed to the neighbours), fluxes at the interior flux
 //                 points, divergence, source, and the stage combination with
 //                 this partial residual
+//              (order 4: k_flux64_n4, the line operators as matrix products)
 //   k_lift64   neighbours' viscous face fluxes -> the missing residual part
 //              added in place; face traces of the new state pushed to the
 //              neighbours for the next stage.
@@ -259,7 +260,7 @@ struct Cfg64;
 template <> struct Cfg64<2> { static constexpr int EPB = 8, NT = 64, MINW = 1; };
 template <> struct Cfg64<3> { static constexpr int EPB = 2, NT = 64, MINW = 1; };
 template <> struct Cfg64<4> { static constexpr int EPB = 1, NT = 64, MINW = 3; };
-template <> struct Cfg64<5> { static constexpr int EPB = 1, NT = 128, MINW = 1; };
+template <> struct Cfg64<5> { static constexpr int EPB = 1, NT = 128, MINW = 3; };
 template <> struct Cfg64<6> { static constexpr int EPB = 1, NT = 256, MINW = 1; };
 
 // face traces of the element block's state (LDS) pushed to the neighbours
@@ -321,6 +322,121 @@ __device__ __forceinline__ double line_interp_s(const Ops<N> &op, const T *fld, 
     return t;
 }
 
+// common interface solution at a face point with the own values fo (BR1
+// average with the neighbour trace nq, wall state, or average with the
+// far-field state)
+__device__ __forceinline__ void common_value64(const double fo[5], int32_t nb, int32_t info, const double nq[5],
+                                               const double Sf[3], const PhysParams &P, double qs[5]) {
+    const int bc = (info >> 6) - 1;
+    if (nb >= 0) {
+        for (int v = 0; v < 5; ++v) qs[v] = 0.5 * (fo[v] + nq[v]);
+    } else if (bc == CHORUS_BC_INNER || bc == CHORUS_BC_OUTER) {
+        wall_state(fo, Sf, bc == CHORUS_BC_OUTER, P, qs);  // (the same along +-S)
+    } else {
+        for (int v = 0; v < 5; ++v) qs[v] = 0.5 * (fo[v] + P.bc_state[v]);
+    }
+}
+
+// the same at point pp of face f from the element's state sq in LDS
+template <int N>
+__device__ __forceinline__ void common_point64(const Ops<N> &op, const double (*sq)[N * N * N], int f, int pp,
+                                               int32_t nb, int32_t info, const double nq[5], const double Sf[3],
+                                               const PhysParams &P, double qs[5]) {
+    const int d = f >> 1, m = (f & 1) ? N : 0;
+    const int base = sol_of<N>(d, 0, pp % N, pp / N), st = stride_of<N>(d);
+    double fo[5];
+    for (int v = 0; v < 5; ++v) fo[v] = line_interp_s<N>(op, sq[v], m, base, st);
+    common_value64(fo, nb, info, nq, Sf, P, qs);
+}
+
+// own-side common flux ffc along the outward Sf at a face point with the own
+// values fo, gradients g and (CL) subgrid flux ts(v) along Sf of variable v;
+// the own viscous flux to the neighbour's mailbox TV (pp: the point, kr: the
+// radiative diffusivity)
+template <int N, bool CL, typename TS>
+__device__ __forceinline__ void face_flux64(const double fo[5], const double g[5][3], TS &&ts, int pp,
+                                            int32_t nb, int32_t info, const double nq[5], const double Sf[3],
+                                            const PhysParams &P, double kr, double *__restrict__ TV, double ffc[5]) {
+    constexpr int NF2 = N * N;
+    const int bc = (info >> 6) - 1;
+    double fv[5];
+    if (nb >= 0) {
+        flux_viscous(fo, g, Sf, P, kr, fv);
+        if constexpr (CL)  // the own-side subgrid flux enters the trace with the sign of -F_v
+            for (int v = 0; v < 5; ++v) fv[v] -= ts(v);
+        // the viscous mass flux is zero: four components per point
+        // unless the subgrid flux (with a mass part) rides along
+        constexpr int NV = CL ? 5 : 4;
+        double *tv = TV + mailbox_slot<N, NV>(nb, info, pp);
+        for (int v = 5 - NV; v < 5; ++v) st_once(&tv[(v - (5 - NV)) * NF2], fv[v]);
+        flux_rusanov(fo, nq, Sf, P, ffc);
+        for (int v = 0; v < 5; ++v) ffc[v] -= 0.5 * fv[v];
+    } else if (bc == CHORUS_BC_INNER || bc == CHORUS_BC_OUTER) {
+        flux_wall(fo, g, Sf, bc == CHORUS_BC_OUTER, P, kr, ffc);
+    } else {
+        flux_viscous(fo, g, Sf, P, kr, fv);
+        flux_rusanov(fo, P.bc_state, Sf, P, ffc);
+        for (int v = 0; v < 5; ++v) ffc[v] -= 0.5 * fv[v];
+    }
+}
+
+// the same at point pp of face f from the element's state, gradients and
+// (CL) subgrid flux in LDS
+template <int N, bool CL, typename GT>
+__device__ __forceinline__ void face_point64(const Ops<N> &op, const double (*sq)[N * N * N],
+                                             const GT (*sgr)[N * N * N], const float *stau, int f, int pp,
+                                             int32_t nb, int32_t info, const double nq[5], const double Sf[3],
+                                             const PhysParams &P, double kr, double *__restrict__ TV, double ffc[5]) {
+    constexpr int NP = N * N * N;
+    const int d = f >> 1, m = (f & 1) ? N : 0;
+    const int base = sol_of<N>(d, 0, pp % N, pp / N), st = stride_of<N>(d);
+    double fo[5], g[5][3];
+    for (int v = 0; v < 5; ++v) {
+        fo[v] = line_interp_s<N>(op, sq[v], m, base, st);
+        for (int c = 0; c < 3; ++c) g[v][c] = line_interp_s<N>(op, sgr[v * 3 + c], m, base, st);
+    }
+    auto ts = [&](int v) {
+        double x = 0.0;
+        for (int c = 0; c < 3; ++c) x += line_interp<N>(op, stau + (v * 3 + c) * NP, m, base, st) * Sf[c];
+        return x;
+    };
+    face_flux64<N, CL>(fo, g, ts, pp, nb, info, nq, Sf, P, kr, TV, ffc);
+}
+
+// transformed flux along S at the interior flux point m of line (t1, t2) of
+// direction d
+template <int N, bool CL, typename GT>
+__device__ __forceinline__ void interior_point64(const Ops<N> &op, const double (*sq)[N * N * N],
+                                                 const GT (*sgr)[N * N * N], const float *stau, int d, int m,
+                                                 int tt, const double S[3], const PhysParams &P, double kr,
+                                                 double out[5]) {
+    constexpr int NP = N * N * N;
+    const int base = sol_of<N>(d, 0, tt % N, tt / N), st = stride_of<N>(d);
+    double qf[5], g[5][3], fi[5], fv[5];
+    for (int v = 0; v < 5; ++v) {
+        qf[v] = line_interp_s<N>(op, sq[v], m, base, st);
+        for (int c = 0; c < 3; ++c) g[v][c] = line_interp_s<N>(op, sgr[v * 3 + c], m, base, st);
+    }
+    flux_inviscid(qf, S, P.gamma - 1.0, fi);
+    flux_viscous(qf, g, S, P, kr, fv);
+    for (int v = 0; v < 5; ++v) {
+        double ts = 0.0;
+        if constexpr (CL)
+            for (int c = 0; c < 3; ++c) ts += line_interp<N>(op, stau + (v * 3 + c) * NP, m, base, st) * S[c];
+        out[v] = fi[v] - fv[v] + ts;
+    }
+}
+
+// source term M of variable v (gravity g = GM x / r^3, Coriolis) at a point
+__device__ __forceinline__ double source64(int v, double rho, double mx, double my, double mz, const double g[3],
+                                           double omega) {
+    if (v == 1) return rho * g[0] - 2.0 * omega * my;
+    if (v == 2) return rho * g[1] + 2.0 * omega * mx;
+    if (v == 3) return rho * g[2];
+    if (v == 4) return mx * g[0] + my * g[1] + mz * g[2];
+    return 0.0;
+}
+
 // PART 0: the flux pass; PART 1: only the learned subgrid flux (common
 // solution, gradients, network -> C.tau: chorus_closure_infer); PART 2: the
 // flux pass with the learned subgrid flux evaluated in the pass (network on
@@ -352,7 +468,6 @@ __global__ __launch_bounds__(NT, Cfg64<N>::MINW) void k_flux64(Ops<N> opa, Geo G
     __shared__ int32_t lk[EPB][6], inf[EPB][6];
     __shared__ Ops<N> op;
     const int64_t e0 = (int64_t)blockIdx.x * EPB, E = G.E;
-    const double gm1 = P.gamma - 1.0;
     // every global input of the element block before the first wait;
     // unpredicated loads through clamped indices (items past the end read
     // element 0 and are never stored)
@@ -417,20 +532,8 @@ __global__ __launch_bounds__(NT, Cfg64<N>::MINW) void k_flux64(Ops<N> opa, Geo G
         if (it >= EPB * 6 * NF2) break;
         const int el = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
         if (e0 + el >= E) continue;
-        const int d = f >> 1, m = (f & 1) ? N : 0;
-        const int base = sol_of<N>(d, 0, pp % N, pp / N), st = stride_of<N>(d);
-        double fo[5];
-        for (int v = 0; v < 5; ++v) fo[v] = line_interp_s<N>(op, sq[el][v], m, base, st);
-        const int32_t nb = lk[el][f];
-        const int bc = (inf[el][f] >> 6) - 1;
         double qs[5];
-        if (nb >= 0) {
-            for (int v = 0; v < 5; ++v) qs[v] = 0.5 * (fo[v] + nq[k][v]);
-        } else if (bc == CHORUS_BC_INNER || bc == CHORUS_BC_OUTER) {
-            wall_state(fo, Sf[k], bc == CHORUS_BC_OUTER, P, qs);  // (the same along +-S)
-        } else {
-            for (int v = 0; v < 5; ++v) qs[v] = 0.5 * (fo[v] + P.bc_state[v]);
-        }
+        common_point64<N>(op, sq[el], f, pp, lk[el][f], inf[el][f], nq[k], Sf[k], P, qs);
         for (int v = 0; v < 5; ++v) U.sqs[el][f][v][pp] = qs[v];
     }
     __syncthreads();
@@ -479,38 +582,9 @@ __global__ __launch_bounds__(NT, Cfg64<N>::MINW) void k_flux64(Ops<N> opa, Geo G
         if (it >= EPB * 6 * NF2) break;
         const int el = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
         if (e0 + el >= E) continue;
-        const int d = f >> 1, m = (f & 1) ? N : 0;
-        const int base = sol_of<N>(d, 0, pp % N, pp / N), st = stride_of<N>(d);
-        double fo[5], g[5][3];
-        for (int v = 0; v < 5; ++v) {
-            fo[v] = line_interp_s<N>(op, sq[el][v], m, base, st);
-            for (int c = 0; c < 3; ++c) g[v][c] = line_interp_s<N>(op, sgr[el][v * 3 + c], m, base, st);
-        }
-        const int32_t nb = lk[el][f];
-        const int bc = (inf[el][f] >> 6) - 1;
         const double kr = RAD ? kappa_r_at(P, krf[k]) : krf[k];
-        double fv[5];
-        if (nb >= 0) {
-            flux_viscous(fo, g, Sf[k], P, kr, fv);
-            if constexpr (CL) {
-                // the own-side subgrid flux enters the trace with the sign of -F_v
-                for (int v = 0; v < 5; ++v)
-                    for (int c = 0; c < 3; ++c) fv[v] -= line_interp<N>(op, stau[el][v * 3 + c], m, base, st) * Sf[k][c];
-            }
-            // the viscous mass flux is zero: four components per point
-            // unless the subgrid flux (with a mass part) rides along
-            constexpr int NV = CL ? 5 : 4;
-            double *tv = TV + mailbox_slot<N, NV>(nb, inf[el][f], pp);
-            for (int v = 5 - NV; v < 5; ++v) st_once(&tv[(v - (5 - NV)) * NF2], fv[v]);
-            flux_rusanov(fo, nq[k], Sf[k], P, ffc[k]);
-            for (int v = 0; v < 5; ++v) ffc[k][v] -= 0.5 * fv[v];
-        } else if (bc == CHORUS_BC_INNER || bc == CHORUS_BC_OUTER) {
-            flux_wall(fo, g, Sf[k], bc == CHORUS_BC_OUTER, P, kr, ffc[k]);
-        } else {
-            flux_viscous(fo, g, Sf[k], P, kr, fv);
-            flux_rusanov(fo, P.bc_state, Sf[k], P, ffc[k]);
-            for (int v = 0; v < 5; ++v) ffc[k][v] -= 0.5 * fv[v];
-        }
+        face_point64<N, CL>(op, sq[el], sgr[el], CL ? &stau[el][0][0] : nullptr, f, pp, lk[el][f], inf[el][f], nq[k],
+                            Sf[k], P, kr, TV, ffc[k]);
     }
     // per direction: transformed flux at the d-flux points, its derivative
     // added to the divergence at the solution points
@@ -529,21 +603,11 @@ __global__ __launch_bounds__(NT, Cfg64<N>::MINW) void k_flux64(Ops<N> opa, Geo G
             const int el = it / NINTD, q = it % NINTD;
             const int m = 1 + q % (N - 1), tt = q / (N - 1);
             if (e0 + el >= E) continue;
-            const int base = sol_of<N>(d, 0, tt % N, tt / N), st = stride_of<N>(d);
-            double qf[5], g[5][3], fi[5], fv[5];
-            for (int v = 0; v < 5; ++v) {
-                qf[v] = line_interp_s<N>(op, sq[el][v], m, base, st);
-                for (int c = 0; c < 3; ++c) g[v][c] = line_interp_s<N>(op, sgr[el][v * 3 + c], m, base, st);
-            }
-            flux_inviscid(qf, Si[cur][k], gm1, fi);
-            flux_viscous(qf, g, Si[cur][k], P, RAD ? kappa_r_at(P, kri[cur][k]) : kri[cur][k], fv);
-            double ts[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-            if constexpr (CL) {
-                for (int v = 0; v < 5; ++v)
-                    for (int c = 0; c < 3; ++c) ts[v] += line_interp<N>(op, stau[el][v * 3 + c], m, base, st) * Si[cur][k][c];
-            }
+            double fi[5];
+            interior_point64<N, CL>(op, sq[el], sgr[el], CL ? &stau[el][0][0] : nullptr, d, m, tt, Si[cur][k], P,
+                                    RAD ? kappa_r_at(P, kri[cur][k]) : kri[cur][k], fi);
             const int fl = m + (N + 1) * tt;
-            for (int v = 0; v < 5; ++v) U.F.sft[el][v][fl] = fi[v] - fv[v] + ts[v];
+            for (int v = 0; v < 5; ++v) U.F.sft[el][v][fl] = fi[v];
         }
 #pragma unroll
         for (int k = 0; k < Sh::IT_FACE; ++k) {
@@ -619,6 +683,222 @@ __global__ __launch_bounds__(NT, Cfg64<N>::MINW) void k_flux64(Ops<N> opa, Geo G
             if (useT) S_.Tout[gi] = S_.d0 * bv[k][v] + S_.d1 * (q + S_.d2 * R);
             S_.Qout[gi] = S_.c0 * av[k][v] + S_.c1 * (q + S_.c2 * R);
         }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// flux pass of order 4: line operators as 4 x 4 matrix products
+// ---------------------------------------------------------------------------
+// One wave per element.  At order 4 an operator applied along the 16 lines of
+// a direction is one v_mfma_f64_4x4x4 (four independent 4 x 4 x 4 products):
+// lane l = l0 + 4 l1 + 16 l2 supplies A[l0][l2] and B[l2][l0] of block l1 and
+// receives D[l2][l0].  With the lines (l0, l1) as columns and blocks, the
+// field values along a line as K and the operator as A, a field is read from
+// LDS once per direction, one value per lane, where the scalar form reads
+// the four values of its line in every lane; a lane receives its own point's
+// value, so the pointwise flux follows in place and its result is the K
+// operand of the divergence as it stands.
+//   zeta lines: operand lane (x, y, z) = natural point order, result natural
+//   xi lines:   operand lane (z, y, x); used as A with the operator as B the
+//               result is natural (gradients, divergence)
+//   eta lines:  operand lane (x, z, y), result in the same order: one exchange
+//               through LDS to natural order
+// The face points of a direction are 2 rows of the product: the xi and eta
+// faces fill one wave (lane group l2 = face), the zeta faces half of one.
+// FP64 matrix instructions issue at the rate of the vector unit's
+// multiply-adds (16 cycles for 4 x 64), so what is saved is LDS traffic and
+// its latency and the per-lane operator reads.  Sums run over the same terms
+// as the scalar form.
+// Measured on 41,472 hexes against the scalar form (one element per wave too,
+// 14.6 KB of LDS): 312 -> 222 us per launch, 411 -> 139 LDS and 2,245 -> 1,475
+// vector instructions per wave, 12.8 KB of LDS and 160 registers (three waves
+// per SIMD).  The pass has to move 27 KB per element: 5.0 TB/s, the rate of a
+// large copy, which bounds it now.
+__device__ __forceinline__ double mfma44(double a, double b, double c) {
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+
+template <bool RAD>
+__global__ __launch_bounds__(64, 3) void k_flux64_n4(Ops<4> op, Geo G, PhysParams P, const double *__restrict__ Q,
+                                                     const double *__restrict__ TQ, double *__restrict__ TV,
+                                                     StageArgs S_) {
+    constexpr int N = 4, NP = 64, NF2 = 16, NFL = 80;
+    __shared__ double sq[5][NP];
+    __shared__ union {
+        double g[15][NP];  // gradients
+        struct {
+            double qs[6][5][NF2];  // common solution by (face, variable, line), consumed by the gradients
+            double tr[5][NP];      // eta results on their way to natural order
+        } c;
+    } U;
+    __shared__ double sff[4][5][NF2];  // signed common fluxes: xi upper, eta lower, eta upper, zeta upper faces
+    const int64_t e = blockIdx.x, E = G.E;
+    const int l = threadIdx.x, l0 = l & 3, l1 = (l >> 2) & 3, l2 = l >> 4, s = l & 15;
+    // face points of the two rounds: xi and eta faces (f = l2), zeta faces
+    const int ppx = l1 + 4 * l0;  // face point of line slot s on the xi faces (t1 = y = l1, t2 = z = l0)
+    const int fa = l2, ppa = l2 < 2 ? ppx : s, fb = 4 + (l2 & 1), ppb = s;
+    // every global input of the element before the first wait
+    double qv[5], Gm[9], nqa[5], nqb[5], Sa[3], Sb[3], Si[2][3], kra, krb, kri[2];
+    for (int v = 0; v < 5; ++v) qv[v] = Q[((int64_t)v * E + e) * NP + l];
+    const int32_t lka = G.link[e * 6 + fa], lkb = G.link[e * 6 + fb];
+    const int32_t ina = G.info[e * 6 + fa], inb = G.info[e * 6 + fb];
+    for (int v = 0; v < 5; ++v) {
+        nqa[v] = TQ[((e * 6 + fa) * 5 + v) * NF2 + ppa];
+        nqb[v] = TQ[((e * 6 + fb) * 5 + v) * NF2 + ppb];
+    }
+    const double sga = (fa & 1) ? 1.0 : -1.0, sgb = (fb & 1) ? 1.0 : -1.0;
+    const int fla = ((fa & 1) ? N : 0) + (N + 1) * ppa, flb = ((fb & 1) ? N : 0) + (N + 1) * ppb;
+    for (int c = 0; c < 3; ++c) {
+        Sa[c] = sga * G.fluxgeo[((e * 3 + (fa >> 1)) * 3 + c) * NFL + fla];
+        Sb[c] = sgb * G.fluxgeo[((e * 3 + 2) * 3 + c) * NFL + flb];
+    }
+    kra = RAD ? G.rflux[(e * 3 + (fa >> 1)) * NFL + fla] : 0.0;
+    krb = RAD ? G.rflux[(e * 3 + 2) * NFL + flb] : 0.0;
+    for (int c = 0; c < 9; ++c) Gm[c] = G.solgeo[(e * 13 + c) * NP + l];
+    // flux-point metrics of one direction: lane (m = l2, line slot s)
+    auto load_si = [&](int d, int slot) {
+        const int fl = l2 + (N + 1) * (d == 0 ? ppx : s);
+        for (int c = 0; c < 3; ++c) Si[slot][c] = G.fluxgeo[((e * 3 + d) * 3 + c) * NFL + fl];
+        kri[slot] = RAD ? G.rflux[(e * 3 + d) * NFL + fl] : 0.0;
+    };
+    load_si(0, 0);
+    // operator entries of this lane
+    const double cB = op.B[l0][l2], cF = op.I[(l0 & 1) ? N : 0][l2];
+    // LDS slots of the lane's operand of each direction
+    const int nx = lds_sol<N>(l2 + 4 * l1 + 16 * l0), ny = lds_sol<N>(l0 + 4 * l2 + 16 * l1), nz = lds_sol<N>(l);
+    for (int v = 0; v < 5; ++v) sq[v][nz] = qv[v];
+    __syncthreads();
+    // common interface solution
+    double qx[5], qy[5];
+    {
+        double fo[5], qs[5];
+        for (int v = 0; v < 5; ++v) {
+            qx[v] = sq[v][nx];
+            qy[v] = sq[v][ny];
+            const double a = mfma44(cF, qx[v], 0.0), b = mfma44(cF, qy[v], 0.0);
+            fo[v] = l2 < 2 ? a : b;
+        }
+        common_value64(fo, lka, ina, nqa, Sa, P, qs);
+        for (int v = 0; v < 5; ++v) U.c.qs[fa][v][s] = qs[v];
+        for (int v = 0; v < 5; ++v) fo[v] = mfma44(cF, qv[v], 0.0);
+        if (l < 32) {
+            common_value64(fo, lkb, inb, nqb, Sb, P, qs);
+            for (int v = 0; v < 5; ++v) U.c.qs[fb][v][s] = qs[v];
+        }
+    }
+    __syncthreads();
+    // gradients at the solution points
+    {
+        const double w0 = op.D[l0][0], w4 = op.D[l0][N], u0 = op.D[l2][0], u4 = op.D[l2][N];
+        const int sx = l2 + 4 * l1;  // line slot of the natural point on the xi faces
+        double dx[5], dy[5], dz[5];
+        for (int v = 0; v < 5; ++v) {
+            dy[v] = mfma44(cB, qy[v], u0 * U.c.qs[2][v][s] + u4 * U.c.qs[3][v][s]);
+            dx[v] = mfma44(qx[v], cB, w0 * U.c.qs[0][v][sx] + w4 * U.c.qs[1][v][sx]);
+            dz[v] = mfma44(cB, qv[v], u0 * U.c.qs[4][v][s] + u4 * U.c.qs[5][v][s]);
+        }
+        for (int v = 0; v < 5; ++v) U.c.tr[v][ny] = dy[v];
+        __syncthreads();
+        for (int v = 0; v < 5; ++v) dy[v] = U.c.tr[v][nz];
+        __syncthreads();
+        for (int v = 0; v < 5; ++v)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) U.g[v * 3 + c][nz] = Gm[c] * dx[v] + Gm[3 + c] * dy[v] + Gm[6 + c] * dz[v];
+    }
+    __syncthreads();
+    // face points: own viscous flux to the neighbour, own-side common flux;
+    // the lower xi and zeta fluxes stay in the lanes that use them
+    const auto no_ts = [](int) { return 0.0; };
+    double fxl[5], fzl[5];
+    {
+        double fo[5], g[5][3], ff[5];
+        auto both = [&](const double *fld) {
+            const double a = mfma44(cF, fld[nx], 0.0), b = mfma44(cF, fld[ny], 0.0);
+            return l2 < 2 ? a : b;
+        };
+        for (int v = 0; v < 5; ++v) {
+            fo[v] = both(sq[v]);
+            for (int c = 0; c < 3; ++c) g[v][c] = both(U.g[v * 3 + c]);
+        }
+        face_flux64<N, false>(fo, g, no_ts, ppa, lka, ina, nqa, Sa, P, RAD ? kappa_r_at(P, kra) : P.kappa_r, TV, ff);
+        for (int v = 0; v < 5; ++v) {
+            fxl[v] = sga * ff[v];
+            if (l2 > 0) sff[l2 - 1][v][s] = fxl[v];
+        }
+    }
+    {
+        double fo[5], g[5][3], ff[5];
+        for (int v = 0; v < 5; ++v) {
+            fo[v] = mfma44(cF, sq[v][nz], 0.0);
+            for (int c = 0; c < 3; ++c) g[v][c] = mfma44(cF, U.g[v * 3 + c][nz], 0.0);
+            fzl[v] = 0.0;
+        }
+        if (l < 32) {
+            face_flux64<N, false>(fo, g, no_ts, ppb, lkb, inb, nqb, Sb, P, RAD ? kappa_r_at(P, krb) : P.kappa_r, TV, ff);
+            for (int v = 0; v < 5; ++v) {
+                fzl[v] = sgb * ff[v];
+                if (l2 == 1) sff[3][v][s] = fzl[v];
+            }
+        }
+    }
+    __syncthreads();
+    // per direction (xi, zeta, eta): transformed flux at the flux points
+    // (lane (m = l2, line slot s), the lower face's in place at m = 0), its
+    // derivative added to the divergence
+    double div[5];
+    const double cI = op.I[l0][l2], cD = op.D[l0][l2], w4 = op.D[l0][N], u4 = op.D[l2][N];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int d = q == 0 ? 0 : q == 1 ? 2 : 1, cur = q & 1, at = d == 0 ? nx : d == 1 ? ny : nz;
+        if (q < 2) load_si(q == 0 ? 2 : 1, cur ^ 1);
+        double qf[5], g[5][3], fi[5], fv[5], F[5];
+        for (int v = 0; v < 5; ++v) {
+            qf[v] = mfma44(cI, sq[v][at], 0.0);
+            for (int c = 0; c < 3; ++c) g[v][c] = mfma44(cI, U.g[v * 3 + c][at], 0.0);
+        }
+        flux_inviscid(qf, Si[cur], P.gamma - 1.0, fi);
+        flux_viscous(qf, g, Si[cur], P, RAD ? kappa_r_at(P, kri[cur]) : P.kappa_r, fv);
+        for (int v = 0; v < 5; ++v) {
+            const double lo = d == 0 ? fxl[v] : d == 2 ? fzl[v] : sff[1][v][s];
+            F[v] = l2 == 0 ? lo : fi[v] - fv[v];
+        }
+        if (d == 0) {
+            const int sx = l2 + 4 * l1;
+            for (int v = 0; v < 5; ++v) div[v] = mfma44(F[v], cD, 0.0) + w4 * sff[0][v][sx];
+        } else if (d == 2) {
+            for (int v = 0; v < 5; ++v) div[v] += mfma44(cD, F[v], 0.0) + u4 * sff[3][v][s];
+        } else {
+            double t[5];
+            for (int v = 0; v < 5; ++v) t[v] = mfma44(cD, F[v], 0.0) + u4 * sff[2][v][s];
+            __syncthreads();  // the gradients are consumed: their space takes the exchange
+            for (int v = 0; v < 5; ++v) U.c.tr[v][ny] = t[v];
+            __syncthreads();
+            for (int v = 0; v < 5; ++v) div[v] += U.c.tr[v][nz];
+        }
+    }
+    // source and the stage combination with the partial residual (operands
+    // loaded before the first store: the outputs may alias them)
+    const bool rk = S_.mode != 0;
+    const bool useA = rk && S_.c0 != 0.0, useT = rk && S_.Tout != nullptr, useB = useT && S_.d0 != 0.0;
+    double gq[4], av[5], bv[5];
+    for (int c = 0; c < 4; ++c) gq[c] = G.solgeo[(e * 13 + 9 + c) * NP + l];
+    for (int v = 0; v < 5; ++v) {
+        const int64_t gi = ((int64_t)v * E + e) * NP + l;
+        av[v] = useA ? S_.A[gi] : 0.0;
+        bv[v] = useB ? S_.B[gi] : 0.0;
+    }
+    double qn[5];
+    for (int v = 0; v < 5; ++v) qn[v] = sq[v][nz];
+    const double g[3] = {P.GM * gq[1], P.GM * gq[2], P.GM * gq[3]};
+    for (int v = 0; v < 5; ++v) {
+        const double R = -div[v] * gq[0] - source64(v, qn[0], qn[1], qn[2], qn[3], g, P.omega);
+        const int64_t gi = ((int64_t)v * E + e) * NP + l;
+        if (!rk) {
+            S_.Qout[gi] = R;
+            continue;
+        }
+        if (useT) S_.Tout[gi] = S_.d0 * bv[v] + S_.d1 * (qn[v] + S_.d2 * R);
+        S_.Qout[gi] = S_.c0 * av[v] + S_.c1 * (qn[v] + S_.c2 * R);
     }
 }
 
@@ -948,6 +1228,13 @@ static hipError_t launch_flux64_t(const Mesh &m, const Geo &G, const PhysParams 
         } else {
             return hipErrorInvalidValue;
         }
+    } else if constexpr (N == 4) {
+        if (rad)
+            hipLaunchKernelGGL((k_flux64_n4<true>), dim3((unsigned)m.E), dim3(64), 0, s, make_ops<4>(m.basis), G, P, Q,
+                               TQ, TV, sa);
+        else
+            hipLaunchKernelGGL((k_flux64_n4<false>), dim3((unsigned)m.E), dim3(64), 0, s, make_ops<4>(m.basis), G, P,
+                               Q, TQ, TV, sa);
     } else if (rad) {
         hipLaunchKernelGGL((k_flux64<N, EPB, NT, 0, true>), dim3(nb), dim3(NT), 0, s, make_ops<N>(m.basis), G, P, Q,
                            TQ, TV, sa, C);

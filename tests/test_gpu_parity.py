@@ -494,6 +494,38 @@ def test_residual_parity_fewer_elements_than_a_block(ch, oracle_mod, torch_dev, 
     assert_parity(Qd.cpu().numpy() - Q0, Qr - Q0, Qp - Q0, "rk3 E=%d N=%d" % (om.E, N))
 
 
+@pytest.mark.parametrize("N,dims", [
+    (2, (16, 16, 16)), (2, (17, 17, 15)), (2, (21, 21, 19)), (3, (16, 16, 8)), (3, (13, 13, 13)), (3, (13, 13, 17)),
+    (4, (8, 8, 4)), (4, (7, 7, 6)), (4, (13, 13, 11)), (5, (8, 8, 4)), (5, (7, 7, 6)), (5, (9, 9, 10)),
+    (6, (9, 9, 9)), (6, (9, 9, 10))])
+def test_parity_around_the_launch_rules(ch, oracle_mod, torch_dev, N, dims):
+    """Meshes on both sides of the sizes (elements per CU) where the FP64
+    passes change their launch shape, odd element counts among them: the
+    residual with radial kappa_r and one SSPRK(5,4) step (every stage form)."""
+    torch = torch_dev
+    m = box_mesh(*dims, lengths=(1.0, 1.1, 0.9), curve=0.02)
+    om = oracle_mod.OracleMesh(m, N)
+    rng = np.random.default_rng(N)
+    n = om.n_solpts
+    Q = np.stack([1.0 + 0.05 * rng.random(n), *(0.1 * rng.standard_normal((3, n))), 2.5 + 0.05 * rng.random(n)])
+    Q = Q.reshape(5, om.E, om.np)
+    phys = ch.physics(GM=0.3, omega=0.5, nu=1e-3, kappa=1e-3, kappa_r=1e-4, kappa_r1=2e-4, kappa_r2=1e-4,
+                      integrator=ch.CHORUS_SSPRK54)
+    cm = ch.mesh_from_arrays(m, N).upload()
+    R = gpu_residual(ch, torch, cm, phys, Q)
+    op = ora_phys(oracle_mod, phys)
+    Rr, op_m = om.residual(op, Q), perturbed_oracle(oracle_mod, m, N)
+    Qp = ulp_perturb(Q)
+    assert_parity(R, Rr, op_m.residual(op, Qp), "N=%d E=%d" % (N, om.E))
+    ws = cm.workspace(phys)
+    phys.kappa_r1 = phys.kappa_r2 = 0.0
+    op = ora_phys(oracle_mod, phys)
+    Qd = torch.from_numpy(np.ascontiguousarray(Q.reshape(5, -1))).cuda()
+    ch.chorus_rk_step(cm, phys, Qd, 1e-4, 1, ws)
+    torch.cuda.synchronize()
+    assert_parity(Qd.cpu().numpy(), om.ssp54(op, Q, 1e-4, 1), op_m.ssp54(op, Qp, 1e-4, 1), "step N=%d E=%d" % (N, om.E))
+
+
 @pytest.mark.parametrize("rot", range(24))
 def test_residual_parity_orientations(ch, oracle_mod, torch_dev, rot):
     m = two_element_mesh(rot)
