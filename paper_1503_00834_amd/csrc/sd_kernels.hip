@@ -1003,6 +1003,270 @@ __global__ __launch_bounds__(NT) void k_lift64(Ops<N> opa, Geo G, const double *
     push_traces64<N, EPB, NT, true>(op, G, e0, lk, inf, sq, S_.TQout);
 }
 
+// ---------------------------------------------------------------------------
+// wide passes: one element per block, the work of a phase spread over all
+// threads of the block
+// ---------------------------------------------------------------------------
+// On a small mesh a pass lasts as long as one block: the passes above walk
+// the phases of their elements in turn with one or a few waves, which fills
+// the chip when there are blocks for every wave slot but leaves most of it
+// idle when there are not.  Here a thread takes one variable of one solution
+// point (gradients, divergence, update) or one flux point (all three
+// directions and the faces at once; the fluxes of the three directions are
+// held in LDS together), so a phase is one round and the chain of a block is
+// a third as long: flux and lift pass of the 288-hex order-3 shell 12.7 + 4.8
+// -> 7.4 + 4.0 us, ten SSP-RK3 steps 531 -> 326 us.  The price is in the
+// larger meshes: fewer elements in flight per CU and the solution-point
+// metrics read by five threads instead of one.  The sums run over the same
+// terms in the same order.
+template <int N>
+struct Wide {
+    static constexpr int NP = N * N * N, NF2 = N * N, NFL = (N + 1) * N * N, NINT = 3 * (N - 1) * N * N;
+    static constexpr int NT = N == 2 ? 64 : N == 3 ? 192 : N == 4 ? 320 : N == 5 ? 640 : 768;
+    static constexpr int NFACE = 6 * NF2;
+    // first thread of the interior flux points: the face points keep waves
+    // of their own (their work differs) where the block has threads for it
+    static constexpr int FP = (NFACE + 63) / 64 * 64 + NINT <= NT ? (NFACE + 63) / 64 * 64 : NFACE;
+    static constexpr int IT_VP = (5 * NP + NT - 1) / NT;
+};
+
+template <int N, bool RAD>
+__global__ __launch_bounds__(Wide<N>::NT, 4) void k_flux64_wide(Ops<N> opa, Geo G, PhysParams P,
+                                                             const double *__restrict__ Q,
+                                                             const double *__restrict__ TQ, double *__restrict__ TV,
+                                                             StageArgs S_) {
+    using W = Wide<N>;
+    static_assert(W::NFACE <= W::NT && W::FP + W::NINT <= W::NT, "one flux point per thread");
+    constexpr int NP = W::NP, NF2 = W::NF2, NFL = W::NFL, NT = W::NT;
+    __shared__ double sq[5][NP], sgr[15][NP];
+    __shared__ union {
+        double sqs[6][5][NF2];
+        double sft[3][5][NFL];  // written after the common solution is consumed
+    } U;
+    __shared__ int32_t lk[6], inf[6];
+    __shared__ Ops<N> op;
+    const int64_t e = blockIdx.x, E = G.E;
+    const int t = threadIdx.x;
+    // this thread's flux point: face point (f, pp) or interior point (d, m, tt)
+    const bool isf = t < W::NFACE, isi = t >= W::FP && t < W::FP + W::NINT;
+    const int f = isf ? t / NF2 : 0, pp = isf ? t % NF2 : 0;
+    const int ii = isi ? t - W::FP : 0, dq = ii / ((N - 1) * NF2), iq = ii % ((N - 1) * NF2);
+    const int d = isf ? f >> 1 : dq, m = isf ? ((f & 1) ? N : 0) : 1 + iq % (N - 1), tt = isf ? pp : iq / (N - 1);
+    const int fl = m + (N + 1) * tt;
+    // every global input before the first wait (unpredicated, clamped)
+    double qv[W::IT_VP], Gm[W::IT_VP][9], nq[5], S[3];
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int it = t + k * NT < 5 * NP ? t + k * NT : 0, v = it / NP, p = it % NP;
+        qv[k] = Q[((int64_t)v * E + e) * NP + p];
+        for (int c = 0; c < 9; ++c) Gm[k][c] = G.solgeo[(e * 13 + c) * NP + p];
+    }
+    for (int v = 0; v < 5; ++v) nq[v] = TQ[((e * 6 + f) * 5 + v) * NF2 + pp];
+    const double sg = (isf && !(f & 1)) ? -1.0 : 1.0;
+    for (int c = 0; c < 3; ++c) S[c] = sg * G.fluxgeo[((e * 3 + d) * 3 + c) * NFL + fl];
+    const double rl = RAD ? G.rflux[(e * 3 + d) * NFL + fl] : 0.0;
+    {
+        const int32_t l = G.link[e * 6 + (t < 6 ? t : 0)], i = G.info[e * 6 + (t < 6 ? t : 0)];
+        if (t < 6) {
+            lk[t] = l;
+            inf[t] = i;
+        }
+    }
+    ops_to_lds(opa, op);
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int it = t + k * NT;
+        if (it < 5 * NP) sq[it / NP][lds_sol<N>(it % NP)] = qv[k];
+    }
+    __syncthreads();
+    if (isf) {
+        double qs[5];
+        common_point64<N>(op, sq, f, pp, lk[f], inf[f], nq, S, P, qs);
+        for (int v = 0; v < 5; ++v) U.sqs[f][v][pp] = qs[v];
+    }
+    __syncthreads();
+    // gradient of one variable at one solution point
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int it = t + k * NT;
+        if (it >= 5 * NP) break;
+        const int v = it / NP, p = it % NP;
+        double dd[3];
+#pragma unroll
+        for (int dir = 0; dir < 3; ++dir) {
+            int a, t1, t2;
+            split_sol<N>(dir, p, a, t1, t2);
+            const int base = sol_of<N>(dir, 0, t1, t2), st = stride_of<N>(dir), q = t1 + N * t2;
+            double s = op.D[a][0] * U.sqs[2 * dir][v][q] + op.D[a][N] * U.sqs[2 * dir + 1][v][q];
+#pragma unroll
+            for (int b = 0; b < N; ++b) s += op.B[a][b] * sq[v][lds_line<N>(base, b, st)];
+            dd[dir] = s;
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            sgr[v * 3 + c][lds_sol<N>(p)] = Gm[k][c] * dd[0] + Gm[k][3 + c] * dd[1] + Gm[k][6 + c] * dd[2];
+    }
+    __syncthreads();
+    // every flux point of the element at once
+    const double kr = RAD ? kappa_r_at(P, rl) : P.kappa_r;
+    if (isf) {
+        double ffc[5];
+        face_point64<N, false>(op, sq, sgr, nullptr, f, pp, lk[f], inf[f], nq, S, P, kr, TV, ffc);
+        for (int v = 0; v < 5; ++v) U.sft[d][v][fl] = sg * ffc[v];
+    } else if (isi) {
+        double fi[5];
+        interior_point64<N, false>(op, sq, sgr, nullptr, d, m, tt, S, P, kr, fi);
+        for (int v = 0; v < 5; ++v) U.sft[d][v][fl] = fi[v];
+    }
+    __syncthreads();
+    // divergence, source and stage combination of one variable at one
+    // solution point (operands loaded before the first store)
+    const bool rk = S_.mode != 0;
+    const bool useA = rk && S_.c0 != 0.0, useT = rk && S_.Tout != nullptr, useB = useT && S_.d0 != 0.0;
+    double gq[W::IT_VP][4], av[W::IT_VP], bv[W::IT_VP];
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int it = t + k * NT < 5 * NP ? t + k * NT : 0, v = it / NP, p = it % NP;
+        for (int c = 0; c < 4; ++c) gq[k][c] = G.solgeo[(e * 13 + 9 + c) * NP + p];
+        const int64_t gi = ((int64_t)v * E + e) * NP + p;
+        av[k] = useA ? S_.A[gi] : 0.0;
+        bv[k] = useB ? S_.B[gi] : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int it = t + k * NT;
+        if (it >= 5 * NP) break;
+        const int v = it / NP, p = it % NP, ps = lds_sol<N>(p);
+        double div = 0.0;
+#pragma unroll
+        for (int dir = 0; dir < 3; ++dir) {
+            int a, t1, t2;
+            split_sol<N>(dir, p, a, t1, t2);
+            const int fb = (N + 1) * (t1 + N * t2);
+            double s = 0.0;
+#pragma unroll
+            for (int mm = 0; mm <= N; ++mm) s += op.D[a][mm] * U.sft[dir][v][fb + mm];
+            div += s;
+        }
+        const double g[3] = {P.GM * gq[k][1], P.GM * gq[k][2], P.GM * gq[k][3]};
+        const double R = -div * gq[k][0] - source64(v, sq[0][ps], sq[1][ps], sq[2][ps], sq[3][ps], g, P.omega);
+        const int64_t gi = ((int64_t)v * E + e) * NP + p;
+        if (!rk) {
+            S_.Qout[gi] = R;
+            continue;
+        }
+        const double q = sq[v][ps];
+        if (useT) S_.Tout[gi] = S_.d0 * bv[k] + S_.d1 * (q + S_.d2 * R);
+        S_.Qout[gi] = S_.c0 * av[k] + S_.c1 * (q + S_.c2 * R);
+    }
+}
+
+// face traces of an element's state (LDS) pushed to the neighbours, one
+// variable of one face point per thread and round
+template <int N>
+__device__ __forceinline__ void push_traces64_wide(const Ops<N> &op, const int32_t *lk, const int32_t *inf,
+                                                   const double (*sq)[N * N * N], double *__restrict__ TQout) {
+    constexpr int NF2 = N * N;
+    for (int it = threadIdx.x; it < 30 * NF2; it += Wide<N>::NT) {
+        const int v = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
+        const int32_t nb = lk[f];
+        if (nb < 0) continue;
+        const int d = f >> 1, m = (f & 1) ? N : 0;
+        const double tr = line_interp_s<N>(op, sq[v], m, sol_of<N>(d, 0, pp % N, pp / N), stride_of<N>(d));
+        st_once(TQout + mailbox_slot<N>(nb, inf[f], pp) + v * NF2, tr);
+    }
+}
+
+template <int N>
+__global__ __launch_bounds__(Wide<N>::NT) void k_trace_push_wide(Ops<N> opa, Geo G, const double *__restrict__ Q,
+                                                                 double *__restrict__ TQ) {
+    constexpr int NP = N * N * N;
+    __shared__ double sq[5][NP];
+    __shared__ int32_t lk[6], inf[6];
+    __shared__ Ops<N> op;
+    const int64_t e = blockIdx.x;
+    ops_to_lds(opa, op);
+    if (threadIdx.x < 6) {
+        lk[threadIdx.x] = G.link[e * 6 + threadIdx.x];
+        inf[threadIdx.x] = G.info[e * 6 + threadIdx.x];
+    }
+    for (int it = threadIdx.x; it < 5 * NP; it += Wide<N>::NT)
+        sq[it / NP][lds_sol<N>(it % NP)] = Q[((int64_t)(it / NP) * G.E + e) * NP + it % NP];
+    __syncthreads();
+    push_traces64_wide<N>(op, lk, inf, sq, TQ);
+}
+
+template <int N, int NV>
+__global__ __launch_bounds__(Wide<N>::NT) void k_lift64_wide(Ops<N> opa, Geo G, const double *__restrict__ TV,
+                                                             StageArgs S_) {
+    using W = Wide<N>;
+    constexpr int NP = W::NP, NF2 = W::NF2, NT = W::NT, MBE = 6 * NV * NF2, IT_MB = (MBE + NT - 1) / NT;
+    __shared__ double nv[6][NV][NF2];  // neighbours' viscous flux at own face points, 0 off interfaces
+    __shared__ double sq[5][NP];       // the new state, for the traces
+    __shared__ int32_t lk[6], inf[6];
+    __shared__ Ops<N> op;
+    const int64_t e = blockIdx.x, E = G.E;
+    const int t = threadIdx.x;
+    const bool useT = S_.mode != 0 && S_.Tout != nullptr, bal = S_.R0 != nullptr;
+    // every global input first (unpredicated, clamped; the mailbox slots of
+    // boundary faces are never written and are selected away below)
+    double mb[IT_MB];
+    int32_t ml[IT_MB];
+#pragma unroll
+    for (int k = 0; k < IT_MB; ++k) {
+        const int it = t + k * NT < MBE ? t + k * NT : 0;
+        mb[k] = ld_once(&TV[e * MBE + it]);
+        ml[k] = G.link[e * 6 + it / (NV * NF2)];
+    }
+    double qo[W::IT_VP], to[W::IT_VP], iJ[W::IT_VP], r0[W::IT_VP];
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int it = t + k * NT < 5 * NP ? t + k * NT : 0, v = it / NP, p = it % NP;
+        const int64_t gi = ((int64_t)v * E + e) * NP + p;
+        iJ[k] = G.solgeo[(e * 13 + 9) * NP + p];
+        qo[k] = S_.Qout[gi];
+        to[k] = useT ? S_.Tout[gi] : 0.0;
+        r0[k] = bal ? S_.R0[gi] : 0.0;
+    }
+    if (t < 6) {
+        lk[t] = G.link[e * 6 + t];
+        inf[t] = G.info[e * 6 + t];
+    }
+    ops_to_lds(opa, op);
+#pragma unroll
+    for (int k = 0; k < IT_MB; ++k)
+        if (t + k * NT < MBE) (&nv[0][0][0])[t + k * NT] = (ml[k] >= 0) ? mb[k] : 0.0;
+    __syncthreads();
+    const double wP = (S_.mode == 0) ? 1.0 : S_.c1 * S_.c2, wT = S_.d1 * S_.d2;
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int it = t + k * NT;
+        if (it >= 5 * NP) break;
+        const int v = it / NP, p = it % NP;
+        double corr = 0.0;
+        if (v >= 5 - NV) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                int a, t1, t2;
+                split_sol<N>(d, p, a, t1, t2);
+                const int pp = t1 + N * t2;
+                const double wl = -0.5 * op.D[a][0], wu = 0.5 * op.D[a][N];
+                corr += wl * nv[2 * d][v - (5 - NV)][pp] + wu * nv[2 * d + 1][v - (5 - NV)][pp];
+            }
+        }
+        const int64_t gi = ((int64_t)v * E + e) * NP + p;
+        const double x = -iJ[k] * corr;
+        // (balanced mode as in k_lift64)
+        const double qn = bal ? (qo[k] + wP * x) - wP * r0[k] : qo[k] + wP * x;
+        S_.Qout[gi] = qn;
+        if (useT) S_.Tout[gi] = bal ? (to[k] + wT * x) - wT * r0[k] : to[k] + wT * x;
+        sq[v][lds_sol<N>(p)] = qn;
+    }
+    if (S_.mode == 0 || S_.TQout == nullptr) return;
+    __syncthreads();
+    push_traces64_wide<N>(op, lk, inf, sq, S_.TQout);
+}
+
 // entropy gradient of a state at rest along the flux-point metric:
 // out[e][d][fl] = grad S . (|J| grad xi_d) at the d-flux points, with the BR1
 // gradients of the FP64 path (S = c_p ln(p^(1/gamma)/rho), p = (gamma-1) E
@@ -1201,8 +1465,38 @@ static hipError_t launch_trace_t(const Mesh &m, const Geo &G, const double *Q, d
     return hipGetLastError();
 }
 
+// Largest meshes, in elements per CU (256), that run the wide passes: where
+// an SSP-RK3 step of a shell was no slower with them (us per step, element
+// passes / wide passes; the flux pass of order 4 is k_flux64_n4):
+//   flux  order 2: 62.2 / 56.2 at 3,600 hexes, 67.0 / 69.0 at 5,184
+//         order 3: 52.2 / 36.2 at 288, 77.8 / 74.6 at 2,304, 89.0 / 96.3 at 3,600
+//         order 4: 38.8 / 35.1 at 162, 40.8 / 44.7 at 288
+//         order 5: 56.7 / 45.7 at 162, 68.7 / 69.5 at 288
+//         order 6: 59.4 / 59.4 at 162, 82.2 / 101.6 at 288 (not used)
+//   lift and trace push
+//         order 2: 74.1 / 70.3 at 7,776, 95.0 / 99.4 at 12,288
+//         order 3: 77.8 / 75.5 at 2,304, 89.0 / 103.5 at 3,600
+//         order 4: 64.8 / 62.9 at 1,536, 84.3 / 85.5 at 2,304
+//         order 5: 83.4 / 80.7 at 648, 126.2 / 126.6 at 1,080
+//         order 6: 111.7 / 109.2 at 648, 168.8 / 167.8 at 1,080
+template <int N>
+static bool wide_flux64(const Mesh &m) {
+    constexpr int per_cu = N == 2 ? 16 : N == 3 ? 8 : N == 6 ? 0 : 1;
+    return m.E <= 256 * per_cu;
+}
+template <int N>
+static bool wide_lift64(const Mesh &m) {
+    constexpr int per_cu = N == 2 ? 32 : N == 3 ? 10 : N == 4 ? 7 : 3;
+    return m.E <= 256 * per_cu;
+}
+
 template <int N>
 static hipError_t launch_trace_push_t(const Mesh &m, const Geo &G, const double *Q, double *TQ, hipStream_t s) {
+    if (wide_lift64<N>(m)) {
+        hipLaunchKernelGGL((k_trace_push_wide<N>), dim3((unsigned)m.E), dim3(Wide<N>::NT), 0, s, make_ops<N>(m.basis), G,
+                           Q, TQ);
+        return hipGetLastError();
+    }
     constexpr int EPB = Cfg64<N>::EPB, NT = Cfg64<N>::NT;
     const unsigned nb = (unsigned)((m.E + EPB - 1) / EPB);
     hipLaunchKernelGGL((k_trace_push<N, EPB, NT>), dim3(nb), dim3(NT), 0, s, make_ops<N>(m.basis), G, Q, TQ);
@@ -1228,6 +1522,15 @@ static hipError_t launch_flux64_t(const Mesh &m, const Geo &G, const PhysParams 
         } else {
             return hipErrorInvalidValue;
         }
+    } else if (wide_flux64<N>(m)) {
+        if constexpr (N == 6)
+            return hipErrorInvalidValue;  // (never: see the rule)
+        else if (rad)
+            hipLaunchKernelGGL((k_flux64_wide<N, true>), dim3((unsigned)m.E), dim3(Wide<N>::NT), 0, s,
+                               make_ops<N>(m.basis), G, P, Q, TQ, TV, sa);
+        else
+            hipLaunchKernelGGL((k_flux64_wide<N, false>), dim3((unsigned)m.E), dim3(Wide<N>::NT), 0, s,
+                               make_ops<N>(m.basis), G, P, Q, TQ, TV, sa);
     } else if constexpr (N == 4) {
         if (rad)
             hipLaunchKernelGGL((k_flux64_n4<true>), dim3((unsigned)m.E), dim3(64), 0, s, make_ops<4>(m.basis), G, P, Q,
@@ -1250,6 +1553,15 @@ static hipError_t launch_lift64_t(const Mesh &m, const Geo &G, const double *TV,
                                   hipStream_t s) {
     constexpr int EPB = Cfg64<N>::EPB, NT = Cfg64<N>::NT;
     const unsigned nb = (unsigned)((m.E + EPB - 1) / EPB);
+    if (wide_lift64<N>(m)) {
+        if (closure)
+            hipLaunchKernelGGL((k_lift64_wide<N, 5>), dim3((unsigned)m.E), dim3(Wide<N>::NT), 0, s, make_ops<N>(m.basis),
+                               G, TV, sa);
+        else
+            hipLaunchKernelGGL((k_lift64_wide<N, 4>), dim3((unsigned)m.E), dim3(Wide<N>::NT), 0, s, make_ops<N>(m.basis),
+                               G, TV, sa);
+        return hipGetLastError();
+    }
     if (closure)
         hipLaunchKernelGGL((k_lift64<N, EPB, NT, 5>), dim3(nb), dim3(NT), 0, s, make_ops<N>(m.basis), G, TV, sa);
     else
