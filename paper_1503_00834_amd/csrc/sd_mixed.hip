@@ -195,7 +195,8 @@ __device__ __forceinline__ void dflux_viscous(const PtState &s, const float S[3]
 // ---------------------------------------------------------------------------
 // element phases (generic N; items per thread fixed at compile time)
 // ---------------------------------------------------------------------------
-template <int N>
+// (ND: directions whose fluxes are held together)
+template <int N, int ND = 1>
 struct MixedLds {
     static constexpr int NP = N * N * N, NF2 = N * N, NFL = (N + 1) * N * N;
     float f[NFIELD][NP];          // perturbation + background fields
@@ -203,7 +204,7 @@ struct MixedLds {
     float g[NGRAD][NP];           // gradients
     union {
         float cs[5][6][NF2];       // common values of the perturbation
-        float ft[5][NFL];          // transformed flux of one direction, written after cs is consumed
+        float ft[ND][5][NFL];      // transformed fluxes, written after cs is consumed
     } u;
     int32_t lk[6], inf[6];        // neighbour element and info word per face
 };
@@ -326,6 +327,34 @@ __device__ __forceinline__ float line_val(const OpsF<N> &op, const float *fld, i
     return s;
 }
 
+// BR1 common value of the perturbation at a face point with the own values pv
+// and background density r0: average with the neighbour trace nq, or the
+// wall state in perturbation form (rho' kept, normal momentum removed,
+// pressure kept; outer wall with T_top: p = rho R T_top).  The normal
+// projection is the same along +-S.  put(v, value) stores variable v.
+template <typename PUT>
+__device__ __forceinline__ void common_value(const float pv[5], float r0, int32_t nb, int32_t inf, const float nq[5],
+                                             const float S[3], const PhysF &F, PUT &&put) {
+    if (nb >= 0) {
+        for (int v = 0; v < 5; ++v) put(v, 0.5f * (pv[v] + nq[v]));
+        return;
+    }
+    const bool outer = ((inf >> 6) - 1) == CHORUS_BC_OUTER;
+    const float A2 = S[0] * S[0] + S[1] * S[1] + S[2] * S[2];
+    const float mn = (pv[1] * S[0] + pv[2] * S[1] + pv[3] * S[2]) * rcp(A2);
+    float mb[3];
+    for (int a = 0; a < 3; ++a) mb[a] = pv[1 + a] - mn * S[a];
+    const float irho = rcp(r0 + pv[0]), igm1 = rcp(F.gm1);
+    const float mm = pv[1] * pv[1] + pv[2] * pv[2] + pv[3] * pv[3];
+    const float mbb = mb[0] * mb[0] + mb[1] * mb[1] + mb[2] * mb[2];
+    float Eb;  // E_b - E0_b
+    if (outer && F.RT_top > 0.0f) Eb = F.RT_top * pv[0] * igm1 + 0.5f * mbb * irho;
+    else Eb = pv[4] + 0.5f * (mbb - mm) * irho;
+    put(0, pv[0]);
+    for (int a = 0; a < 3; ++a) put(1 + a, mb[a]);
+    put(4, Eb);
+}
+
 // BR1 common values of the perturbation at the 6 N^2 face points (the
 // background's gradients are computed once, in FP64, at set-up); the own
 // face values of the 7 fields at the thread's face items are kept in fo when
@@ -355,29 +384,7 @@ __device__ __forceinline__ void common_values(const OpsF<N> &op, const GeoF &G, 
             fo[k][F_E0] = E0;
         }
         const int32_t nb = l.lk[f], inf = l.inf[f];
-        if (nb >= 0) {
-            for (int v = 0; v < 5; ++v) l.u.cs[v][f][pp] = 0.5f * (pv[v] + R.nq[k][v]);
-        } else {
-            // wall state in perturbation form: rho' kept, normal momentum
-            // removed, pressure kept (outer wall with T_top: p = rho R T_top)
-            // (the normal projection is the same along +-S: the thread's
-            // flux-point metric Sf serves)
-            const bool outer = ((inf >> 6) - 1) == CHORUS_BC_OUTER;
-            const float *S = Sf[k];
-            const float A2 = S[0] * S[0] + S[1] * S[1] + S[2] * S[2];
-            const float mn = (pv[1] * S[0] + pv[2] * S[1] + pv[3] * S[2]) * rcp(A2);
-            float mb[3];
-            for (int a = 0; a < 3; ++a) mb[a] = pv[1 + a] - mn * S[a];
-            const float irho = rcp(r0 + pv[0]), igm1 = rcp(F.gm1);
-            const float mm = pv[1] * pv[1] + pv[2] * pv[2] + pv[3] * pv[3];
-            const float mbb = mb[0] * mb[0] + mb[1] * mb[1] + mb[2] * mb[2];
-            float Eb;  // E_b - E0_b
-            if (outer && F.RT_top > 0.0f) Eb = F.RT_top * pv[0] * igm1 + 0.5f * mbb * irho;
-            else Eb = pv[4] + 0.5f * (mbb - mm) * irho;
-            l.u.cs[0][f][pp] = pv[0];
-            for (int a = 0; a < 3; ++a) l.u.cs[1 + a][f][pp] = mb[a];
-            l.u.cs[4][f][pp] = Eb;
-        }
+        common_value(pv, r0, nb, inf, R.nq[k], Sf[k], F, [&](int v, float x) { l.u.cs[v][f][pp] = x; });
     }
 }
 
@@ -422,8 +429,8 @@ __device__ __forceinline__ void gradients(const OpsF<N> &op, const GeoF &G, int6
 // point state at the flux point m of the line (base, st); with vals given,
 // the 7 field values are taken from there and only the gradients are
 // interpolated
-template <int N>
-__device__ __forceinline__ void state_at(const OpsF<N> &op, const MixedLds<N> &l, int m, int base, int st,
+template <int N, typename LDS>
+__device__ __forceinline__ void state_at(const OpsF<N> &op, const LDS &l, int m, int base, int st,
                                          PtState &s, const float *vals = nullptr) {
     float w[N];
 #pragma unroll
@@ -682,7 +689,7 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed(OpsF<N> opa, GeoF G, Mi
             dflux_inviscid(s, Si[d][k], F, fi);
             dflux_viscous<KR>(s, Si[d][k], gSi[d][k], F, kr_of<KR>(F, kri[d][k]), 0, fv);
             const int fl = m + (N + 1) * tt;
-            for (int v = 0; v < 5; ++v) l.u.ft[v][fl] = fi[v] - fv[v];
+            for (int v = 0; v < 5; ++v) l.u.ft[0][v][fl] = fi[v] - fv[v];
         }
 #pragma unroll
         for (int k = 0; k < Sh::IT_FACE; ++k) {
@@ -694,7 +701,7 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed(OpsF<N> opa, GeoF G, Mi
             const int m = (f & 1) ? N : 0;
             const float sg = (f & 1) ? 1.0f : -1.0f;
             const int fl = m + (N + 1) * pp;
-            for (int v = 0; v < 5; ++v) l.u.ft[v][fl] = sg * ffc[k][v];
+            for (int v = 0; v < 5; ++v) l.u.ft[0][v][fl] = sg * ffc[k][v];
         }
         __syncthreads();
         if (d == 2) {
@@ -727,7 +734,7 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed(OpsF<N> opa, GeoF G, Mi
             for (int v = 0; v < 5; ++v) {
                 float sum = 0.0f;
 #pragma unroll
-                for (int mm = 0; mm <= N; ++mm) sum += op.D[a][mm] * l.u.ft[v][fb + mm];
+                for (int mm = 0; mm <= N; ++mm) sum += op.D[a][mm] * l.u.ft[0][v][fb + mm];
                 div[k][v] += sum;
             }
         }
@@ -879,6 +886,305 @@ __global__ __launch_bounds__(NT) void k_lift_mixed(OpsF<N> opa, GeoF G, const fl
     }
 }
 
+// ---------------------------------------------------------------------------
+// wide passes: one element per block, the work of a phase spread over all
+// threads of the block (small meshes)
+// ---------------------------------------------------------------------------
+// A thread takes one variable of one solution point (gradients, divergence,
+// update) or one flux point (faces and interior points of all directions in
+// one index range, the three directions' fluxes in LDS together): on a mesh
+// that leaves wave slots empty a pass lasts as long as one block, and this
+// shortens the block's chain (162 hexes of order 4, SSP-RK3: 43.5 -> 27.5 us
+// per step).  The sums run over the same terms in the same order as in the
+// element passes.
+template <int N, int NT>
+struct WideM {
+    static constexpr int NP = N * N * N, NF2 = N * N, NFL = (N + 1) * N * N, NINT = 3 * (N - 1) * N * N;
+    static constexpr int NFACE = 6 * NF2;
+    // first interior item: the face points keep waves of their own (but for
+    // blocks of one wave)
+    static constexpr int FP = NT == 64 ? NFACE : (NFACE + 63) / 64 * 64;
+    static constexpr int IT_VP = (5 * NP + NT - 1) / NT;
+    static constexpr int IT_FACE = (NFACE + NT - 1) / NT;
+    static constexpr int IT_FX = (FP + NINT + NT - 1) / NT;
+};
+
+template <int N, int NT, int MINW, int KR>
+__global__ __launch_bounds__(NT, MINW) void k_flux_mixed_wide(OpsF<N> opa, GeoF G, MixedBufs B, PhysParams P,
+                                                              const double *__restrict__ Pq,
+                                                              const float *__restrict__ TQ, float *__restrict__ TV,
+                                                              MixedStage S_) {
+    using W = WideM<N, NT>;
+    constexpr int NP = W::NP, NF2 = W::NF2, NFL = W::NFL;
+    __shared__ MixedLds<N, 3> L;
+    __shared__ OpsF<N> op;
+    const int64_t e = blockIdx.x, E = G.E;
+    const int t = threadIdx.x;
+    const PhysF F = physf_of(P);
+    // every global input before the first wait (unpredicated, clamped)
+    double pv[W::IT_VP];
+    float Gm[W::IT_VP][9], bg[W::IT_VP];
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int it = t + k * NT < 5 * NP ? t + k * NT : 0, v = it / NP, p = it % NP;
+        pv[k] = Pq[((int64_t)v * E + e) * NP + p];
+        // rows 0, 1: rho0, E0; rows 2..4: grad rho0
+        bg[k] = v < 2 ? B.bg[(e * 2 + v) * NP + p] : B.gbg[(e * 3 + v - 2) * NP + p];
+    }
+    float nq[W::IT_FACE][5], db[W::IT_FACE][2];
+#pragma unroll
+    for (int k = 0; k < W::IT_FACE; ++k) {
+        const int it = t + k * NT < W::NFACE ? t + k * NT : 0;
+        const int64_t base = e * 6 + it / NF2;
+        for (int v = 0; v < 5; ++v) nq[k][v] = TQ[(base * 5 + v) * NF2 + it % NF2];
+        for (int v = 0; v < 2; ++v) db[k][v] = B.dbg[(base * 2 + v) * NF2 + it % NF2];
+    }
+    // flux point of item x: direction d, position m along line tt
+    auto where = [&](int x, int &d, int &m, int &tt) {
+        if (x < W::NFACE) {
+            const int f = x / NF2;
+            d = f >> 1;
+            m = (f & 1) ? N : 0;
+            tt = x % NF2;
+        } else {
+            const int i = (x >= W::FP && x < W::FP + W::NINT) ? x - W::FP : 0, q = i % ((N - 1) * NF2);
+            d = i / ((N - 1) * NF2);
+            m = 1 + q % (N - 1);
+            tt = q / (N - 1);
+        }
+    };
+    float S[W::IT_FX][3], gS[W::IT_FX], krl[W::IT_FX];
+#pragma unroll
+    for (int k = 0; k < W::IT_FX; ++k) {
+        int d, m, tt;
+        where(t + k * NT, d, m, tt);
+        const int fl = m + (N + 1) * tt;
+        for (int c = 0; c < 3; ++c) S[k][c] = G.fluxgeo[((e * 3 + d) * 3 + c) * NFL + fl];
+        gS[k] = B.gS0[(e * 3 + d) * NFL + fl];
+        krl[k] = (KR == KR_RADIAL) ? G.rflux[(e * 3 + d) * NFL + fl] : 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int p = (t + k * NT) % NP;
+        for (int c = 0; c < 9; ++c) Gm[k][c] = G.solgeo[(e * 13 + c) * NP + p];
+    }
+    {
+        const int32_t lk = G.link[e * 6 + (t < 6 ? t : 0)], inf = G.info[e * 6 + (t < 6 ? t : 0)];
+        if (t < 6) {
+            L.lk[t] = lk;
+            L.inf[t] = inf;
+        }
+    }
+    ops_to_lds(opa, op);
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int it = t + k * NT;
+        if (it >= 5 * NP) break;
+        const int v = it / NP, p = it % NP;
+        const float hi = (float)pv[k];
+        L.f[v][p] = hi;
+        L.plo[v][p] = (float)(pv[k] - (double)hi);
+        if (v < 2) L.f[F_R0 + v][p] = bg[k];
+        else L.g[3 * F_R0 + v - 2][p] = bg[k];
+    }
+    __syncthreads();
+    // common values; the own face values of the 7 fields are kept
+    float fo[W::IT_FACE][NFIELD];
+#pragma unroll
+    for (int k = 0; k < W::IT_FACE; ++k) {
+        const int it = t + k * NT;
+        if (it >= W::NFACE) break;
+        const int f = it / NF2, pp = it % NF2, d = f >> 1, m = (f & 1) ? N : 0;
+        const int base = sol_of<N>(d, 0, pp % N, pp / N), st = stride_of<N>(d);
+        for (int v = 0; v < NFIELD; ++v) fo[k][v] = line_val<N>(op, L.f[v], m, base, st);
+        common_value(fo[k], fo[k][F_R0], L.lk[f], L.inf[f], nq[k], S[k], F,
+                     [&](int v, float x) { L.u.cs[v][f][pp] = x; });
+    }
+    __syncthreads();
+    // gradient of one variable at one solution point
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int it = t + k * NT;
+        if (it >= 5 * NP) break;
+        const int v = it / NP, p = it % NP;
+        float dq[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            int a, t1, t2;
+            split_sol<N>(d, p, a, t1, t2);
+            const int base = sol_of<N>(d, 0, t1, t2), st = stride_of<N>(d), pp = t1 + N * t2;
+            float s = op.D[a][0] * L.u.cs[v][2 * d][pp] + op.D[a][N] * L.u.cs[v][2 * d + 1][pp];
+#pragma unroll
+            for (int b = 0; b < N; ++b) s += op.B[a][b] * L.f[v][base + b * st];
+            dq[d] = s;
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            L.g[3 * v + c][p] = Gm[k][c] * dq[0] + Gm[k][3 + c] * dq[1] + Gm[k][6 + c] * dq[2];
+    }
+    __syncthreads();
+    // every flux point of the element
+#pragma unroll
+    for (int k = 0; k < W::IT_FX; ++k) {
+        const int x = t + k * NT;
+        int d, m, tt;
+        where(x, d, m, tt);
+        const int base = sol_of<N>(d, 0, tt % N, tt / N), st = stride_of<N>(d), fl = m + (N + 1) * tt;
+        const float kr = kr_of<KR>(F, krl[k]);
+        if (k < W::IT_FACE && x < W::NFACE) {
+            const int kf = k < W::IT_FACE ? k : 0, f = x / NF2;
+            const int32_t nb = L.lk[f], inf = L.inf[f];
+            const float sg = (f & 1) ? 1.0f : -1.0f;
+            const float So[3] = {sg * S[k][0], sg * S[k][1], sg * S[k][2]}, gSo = sg * gS[k];
+            float fv[5], ff[5];
+            PtState st_;
+            state_at<N>(op, L, m, base, st, st_, fo[kf]);
+            if (nb >= 0) {
+                dflux_viscous<KR>(st_, So, gSo, F, kr, 0, fv);
+                // the viscous mass flux is zero: four components per point
+                const int64_t slot = mailbox_slot<N, 4>(nb, inf, tt);
+                for (int v = 1; v < 5; ++v) st_once(&TV[slot + (v - 1) * NF2], fv[v]);
+            }
+            face_flux_own<KR>(st_, nq[kf], db[kf], nb >= 0, ((inf >> 6) - 1) == CHORUS_BC_OUTER, So, gSo, kr, fv, F, ff);
+            for (int v = 0; v < 5; ++v) L.u.ft[d][v][fl] = sg * ff[v];
+        } else if (x >= W::FP && x < W::FP + W::NINT) {
+            PtState s;
+            state_at<N>(op, L, m, base, st, s);
+            float fi[5], fv[5];
+            dflux_inviscid(s, S[k], F, fi);
+            dflux_viscous<KR>(s, S[k], gS[k], F, kr, 0, fv);
+            for (int v = 0; v < 5; ++v) L.u.ft[d][v][fl] = fi[v] - fv[v];
+        }
+    }
+    // operands of the update, loaded before the divergence (every one before
+    // the first store: the outputs may alias the inputs)
+    const bool rk = S_.mode != 0;
+    const bool useA = rk && S_.c0 != 0.0, useT = rk && S_.Tout != nullptr, useB = useT && S_.d0 != 0.0;
+    float r0v[W::IT_VP], gq[W::IT_VP][4];
+    double pst[W::IT_VP], pb[W::IT_VP];
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int it = t + k * NT < 5 * NP ? t + k * NT : 0, v = it / NP, p = it % NP;
+        const int64_t gi = ((int64_t)v * E + e) * NP + p;
+        for (int c = 0; c < 4; ++c) gq[k][c] = G.solgeo[(e * 13 + 9 + c) * NP + p];
+        r0v[k] = B.R0[gi];
+        pst[k] = useA ? S_.A[gi] : 0.0;
+        pb[k] = useB ? S_.B[gi] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int it = t + k * NT;
+        if (it >= 5 * NP) break;
+        const int v = it / NP, p = it % NP;
+        float div = 0.0f;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            int a, t1, t2;
+            split_sol<N>(d, p, a, t1, t2);
+            const int fb = (N + 1) * (t1 + N * t2);
+            float s = 0.0f;
+#pragma unroll
+            for (int mm = 0; mm <= N; ++mm) s += op.D[a][mm] * L.u.ft[d][v][fb + mm];
+            div += s;
+        }
+        const float g0 = F.GM * gq[k][1], g1 = F.GM * gq[k][2], g2 = F.GM * gq[k][3];
+        const float rp = L.f[F_RP][p], mx = L.f[F_MX][p], my = L.f[F_MY][p], mz = L.f[F_MZ][p];
+        const float M = v == 1   ? rp * g0 - 2.0f * F.om * my
+                        : v == 2 ? rp * g1 + 2.0f * F.om * mx
+                        : v == 3 ? rp * g2
+                        : v == 4 ? mx * g0 + my * g1 + mz * g2
+                                 : 0.0f;
+        const int64_t gi = ((int64_t)v * E + e) * NP + p;
+        const double Rv = (double)r0v[k] + (double)(-div * gq[k][0] - M);
+        if (!rk) {
+            S_.Pout[gi] = Rv;
+            continue;
+        }
+        // the stage input from its FP32 value and remainder (as above)
+        const double pin = (double)L.f[v][p] + (double)L.plo[v][p];
+        if (useT) S_.Tout[gi] = S_.d0 * pb[k] + S_.d1 * (pin + S_.d2 * Rv);
+        S_.Pout[gi] = S_.c0 * pst[k] + S_.c1 * (pin + S_.c2 * Rv);
+    }
+}
+
+template <int N, int NT>
+__global__ __launch_bounds__(NT) void k_lift_mixed_wide(OpsF<N> opa, GeoF G, const float *__restrict__ TV,
+                                                        MixedStage S_) {
+    using W = WideM<N, NT>;
+    constexpr int NP = W::NP, NF2 = W::NF2, MBE = 24 * NF2, IT_MB = (MBE + NT - 1) / NT;
+    __shared__ float nv[6][4][NF2];  // neighbours' viscous momentum and energy flux, 0 on boundary faces
+    __shared__ float sp[5][NP];      // new perturbation (FP32) for the traces
+    __shared__ int32_t lk[6], inf[6];
+    __shared__ OpsF<N> op;
+    const int64_t e = blockIdx.x, E = G.E;
+    const int t = threadIdx.x;
+    const bool useT = S_.mode != 0 && S_.Tout != nullptr;
+    // every global input first (unpredicated, clamped; the mailbox slots of
+    // boundary faces are never written and are selected away below)
+    float mb[IT_MB];
+    int32_t ml[IT_MB];
+#pragma unroll
+    for (int k = 0; k < IT_MB; ++k) {
+        const int it = t + k * NT < MBE ? t + k * NT : 0;
+        mb[k] = ld_once(&TV[e * MBE + it]);
+        ml[k] = G.link[e * 6 + it / (4 * NF2)];
+    }
+    double po[W::IT_VP], to[W::IT_VP];
+    float iJ[W::IT_VP];
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int it = t + k * NT < 5 * NP ? t + k * NT : 0, v = it / NP, p = it % NP;
+        const int64_t gi = ((int64_t)v * E + e) * NP + p;
+        iJ[k] = G.solgeo[(e * 13 + 9) * NP + p];
+        po[k] = S_.Pout[gi];
+        to[k] = useT ? S_.Tout[gi] : 0.0;
+    }
+    if (t < 6) {
+        lk[t] = G.link[e * 6 + t];
+        inf[t] = G.info[e * 6 + t];
+    }
+    ops_to_lds(opa, op);
+#pragma unroll
+    for (int k = 0; k < IT_MB; ++k)
+        if (t + k * NT < MBE) (&nv[0][0][0])[t + k * NT] = (ml[k] >= 0) ? mb[k] : 0.0f;
+    __syncthreads();
+    const double wP = (S_.mode == 0) ? 1.0 : S_.c1 * S_.c2, wT = S_.d1 * S_.d2;
+#pragma unroll
+    for (int k = 0; k < W::IT_VP; ++k) {
+        const int it = t + k * NT;
+        if (it >= 5 * NP) break;
+        const int v = it / NP, p = it % NP;
+        float corr = 0.0f;
+        if (v > 0) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                int a, t1, t2;
+                split_sol<N>(d, p, a, t1, t2);
+                const int pp = t1 + N * t2;
+                const float wl = -0.5f * op.D[a][0], wu = 0.5f * op.D[a][N];
+                corr += wl * nv[2 * d][v - 1][pp] + wu * nv[2 * d + 1][v - 1][pp];
+            }
+        }
+        const int64_t gi = ((int64_t)v * E + e) * NP + p;
+        const double x = -(double)(iJ[k] * corr);
+        const double pn = po[k] + wP * x;
+        S_.Pout[gi] = pn;
+        if (useT) S_.Tout[gi] = to[k] + wT * x;
+        sp[v][p] = (float)pn;
+    }
+    if (S_.mode == 0 || S_.TQout == nullptr) return;
+    __syncthreads();
+    for (int it = t; it < 30 * NF2; it += NT) {
+        const int v = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
+        const int32_t nb = lk[f];
+        if (nb < 0) continue;
+        const int d = f >> 1, m = (f & 1) ? N : 0;
+        const float tr = line_val<N>(op, sp[v], m, sol_of<N>(d, 0, pp % N, pp / N), stride_of<N>(d));
+        st_once(S_.TQout + mailbox_slot<N>(nb, inf[f], pp) + v * NF2, tr);
+    }
+}
+
 // Q = Q0 + P
 __global__ void k_pert_end(const double *__restrict__ Q0, const double *__restrict__ Pq, double *__restrict__ Q,
                            int64_t n) {
@@ -954,6 +1260,29 @@ template <> struct CfgM<6> { static constexpr int EPB = 1, NT = 256, MINW = 1; }
 template <int N> struct CfgF { static constexpr int EPB = CfgM<N>::EPB, NT = CfgM<N>::NT, MINW = CfgM<N>::MINW; };
 template <int N> struct CfgL { static constexpr int EPB = CfgM<N>::EPB, NT = CfgM<N>::NT; };
 
+// Wide passes: threads per block of the smallest meshes (NT1, minimum waves
+// per SIMD W1) and of the next larger ones (NT2, W2), and the largest meshes
+// of each and of the lift pass and set-up, in elements per CU (256).  The
+// limits lie where an SSP-RK3 step of a shell crosses (us per step, element
+// passes / wide passes with NT1 [/ NT2] threads):
+//   order 2: 56.0 / 51.5 at 5,184 hexes, 60.9 / 64.0 at 7,776; lift alone
+//            60.9 / 59.9 at 7,776, 72.7 / 80.6 at 12,288
+//   order 3: 45.9 / 29.3 at 288, 62.9 / 58.6 at 2,304, 70.7 / 83.0 at 3,600;
+//            lift alone 53.9 / 53.1 at 1,536, 62.9 / 63.8 at 2,304
+//   order 4: 45.8 / 31.6 / 36.4 at 288, 51.0 / 43.0 / 42.1 at 648, 60.5 / 61.0
+//            / 50.9 at 1,080, 63.8 / 78.0 / 60.7 at 1,536, 79.8 / - / 80.1 at
+//            2,304; lift alone 63.8 / 60.6 at 1,536, 79.8 / 79.6 at 2,304
+//   order 5: 52.9 / 33.0 / 42.3 at 162, 58.6 / 49.8 / 48.6 at 288, 68.7 / 73.1
+//            / 63.7 at 648, 85.5 / - / 89.7 at 1,080; lift alone 58.6 / 55.2 at
+//            288, 68.7 / 69.2 at 648
+//   order 6: 51.8 / 43.2 at 162, 67.0 / 74.9 at 288
+template <int N> struct CfgW;
+template <> struct CfgW<2> { static constexpr int NT1 = 64, W1 = 1, MAX1 = 20, NT2 = 64, W2 = 1, MAX2 = 0, LIFT = 28; };
+template <> struct CfgW<3> { static constexpr int NT1 = 192, W1 = 1, MAX1 = 9, NT2 = 192, W2 = 1, MAX2 = 0, LIFT = 6; };
+template <> struct CfgW<4> { static constexpr int NT1 = 320, W1 = 4, MAX1 = 2, NT2 = 192, W2 = 4, MAX2 = 6, LIFT = 6; };
+template <> struct CfgW<5> { static constexpr int NT1 = 640, W1 = 3, MAX1 = 1, NT2 = 256, W2 = 4, MAX2 = 3, LIFT = 2; };
+template <> struct CfgW<6> { static constexpr int NT1 = 832, W1 = 4, MAX1 = 1, NT2 = 832, W2 = 4, MAX2 = 0, LIFT = 1; };
+
 static GeoF geof_of(const GeoM &g) {
     GeoF o;
     o.solgeo = g.solgeo32;
@@ -978,8 +1307,28 @@ template <int N>
 static hipError_t pert_begin_t(const Mesh &m, const GeoM &g, const double *Q, double *Pq, float *TQ, hipStream_t s) {
     constexpr int EPB = CfgM<N>::EPB, NT = CfgM<N>::NT;
     const unsigned nb = (unsigned)((m.E + EPB - 1) / EPB);
+    if (m.E <= 256 * CfgW<N>::LIFT) {
+        hipLaunchKernelGGL((k_pert_begin<N, 1, CfgW<N>::NT1>), dim3((unsigned)m.E), dim3(CfgW<N>::NT1), 0, s,
+                           make_ops_t<float, N>(m.basis), geof_of(g), Q, g.Q0, Pq, TQ);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL((k_pert_begin<N, EPB, NT>), dim3(nb), dim3(NT), 0, s, make_ops_t<float, N>(m.basis),
                        geof_of(g), Q, g.Q0, Pq, TQ);
+    return hipGetLastError();
+}
+template <int N, int NT, int MINW>
+static hipError_t flux_mixed_wide_t(const Mesh &m, const GeoM &g, const PhysParams &P, const double *Pq,
+                                    const float *TQ, float *TV, const MixedStage &st, hipStream_t s) {
+    const dim3 grid((unsigned)m.E), block(NT);
+    if (P.kappa_r1 != 0.0 || P.kappa_r2 != 0.0)
+        hipLaunchKernelGGL((k_flux_mixed_wide<N, NT, MINW, KR_RADIAL>), grid, block, 0, s,
+                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), P, Pq, TQ, TV, st);
+    else if (P.kappa_r != 0.0)
+        hipLaunchKernelGGL((k_flux_mixed_wide<N, NT, MINW, KR_CONST>), grid, block, 0, s,
+                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), P, Pq, TQ, TV, st);
+    else
+        hipLaunchKernelGGL((k_flux_mixed_wide<N, NT, MINW, KR_NONE>), grid, block, 0, s,
+                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), P, Pq, TQ, TV, st);
     return hipGetLastError();
 }
 template <int N>
@@ -988,6 +1337,8 @@ static hipError_t flux_mixed_t(const Mesh &m, const GeoM &g, const PhysParams &P
     constexpr int EPB = CfgF<N>::EPB, NT = CfgF<N>::NT, MINW = CfgF<N>::MINW;
     const unsigned nb = (unsigned)((m.E + EPB - 1) / EPB);
     const MixedStage st = a;
+    if (m.E <= 256 * CfgW<N>::MAX1) return flux_mixed_wide_t<N, CfgW<N>::NT1, CfgW<N>::W1>(m, g, P, Pq, TQ, TV, st, s);
+    if (m.E <= 256 * CfgW<N>::MAX2) return flux_mixed_wide_t<N, CfgW<N>::NT2, CfgW<N>::W2>(m, g, P, Pq, TQ, TV, st, s);
     if (P.kappa_r1 != 0.0 || P.kappa_r2 != 0.0)
         hipLaunchKernelGGL((k_flux_mixed<N, EPB, NT, MINW, KR_RADIAL>), dim3(nb), dim3(NT), 0, s,
                            make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), P, Pq, TQ, TV, st);
@@ -1004,6 +1355,11 @@ static hipError_t lift_mixed_t(const Mesh &m, const GeoM &g, const float *TV, co
     constexpr int EPB = CfgL<N>::EPB, NT = CfgL<N>::NT;
     const unsigned nb = (unsigned)((m.E + EPB - 1) / EPB);
     const MixedStage st = a;
+    if (m.E <= 256 * CfgW<N>::LIFT) {
+        hipLaunchKernelGGL((k_lift_mixed_wide<N, CfgW<N>::NT1>), dim3((unsigned)m.E), dim3(CfgW<N>::NT1), 0, s,
+                           make_ops_t<float, N>(m.basis), geof_of(g), TV, st);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL((k_lift_mixed<N, EPB, NT>), dim3(nb), dim3(NT), 0, s, make_ops_t<float, N>(m.basis),
                        geof_of(g), TV, st);
     return hipGetLastError();

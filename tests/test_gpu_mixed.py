@@ -243,6 +243,44 @@ def test_mixed_ragged_last_block(ch, oracle_mod, torch_dev, N):
         assert errq <= 2e-5 * np.linalg.norm(Qr[v] - Qs[v]) + 1e-13 * np.linalg.norm(Qr[v]), (v, errq)
 
 
+@pytest.mark.parametrize("N,panel_n,radial_n", [
+    (2, 13, 5), (2, 12, 6), (2, 14, 6), (2, 14, 7), (3, 11, 2), (3, 13, 2), (3, 14, 2), (4, 9, 1), (4, 6, 3),
+    (4, 8, 4), (4, 10, 3), (5, 4, 2), (5, 9, 1), (5, 8, 2), (5, 7, 3), (6, 4, 2), (6, 5, 2)])
+def test_mixed_around_the_launch_rules(ch, oracle_mod, torch_dev, N, panel_n, radial_n):
+    """Shells on both sides of the sizes (elements per CU) where the mixed
+    passes change their launch shape: the residual with radial, constant and
+    no kappa_r, and two SSPRK(5,4) steps (every stage form)."""
+    torch = torch_dev
+    beta, n_rho = 0.7, 1.0
+    m = cubed_sphere_shell(panel_n, radial_n, beta / (1 - beta), 1 / (1 - beta))
+    om = oracle_mod.OracleMesh(m, N)
+    Q0, pars = om.polytrope(beta, n_rho)
+    Q, _ = om.polytrope(beta, n_rho, noise=uniform_noise(om.n_solpts, 9), amp=1e-3)
+    rng = np.random.default_rng(10)
+    Q[1:4] = 1e-3 * Q[0] * rng.uniform(-1, 1, size=Q[1:4].shape)
+    Q[4] += 0.5 * (Q[1:4] ** 2).sum(0) / Q[0]
+    kw = dict(GM=pars["GM"], omega=1.0, nu=1e-3, kappa=1e-3, T_top=pars["chi_o"], F_bottom=0.01)
+    cm = ch.mesh_from_arrays(m, N).upload()
+    for kr in (dict(kappa_r=1e-4, kappa_r1=3e-4, kappa_r2=1e-4), dict(kappa_r=1e-4), dict()):
+        phys = ch.physics(precision=ch.CHORUS_MIXED, integrator=ch.CHORUS_SSPRK54, **kw, **kr)
+        ws = cm.workspace(phys)
+        ch.chorus_set_background(cm, phys, _dev(torch, Q0), ws)
+        R = torch.empty_like(_dev(torch, Q))
+        ch.chorus_sd_residual(cm, phys, _dev(torch, Q), R, ws)
+        torch.cuda.synchronize()
+        op = oracle_mod.phys(**kw, **kr)
+        assert_mixed(R.cpu().numpy(), om.residual(op, Q).reshape(5, -1), om.residual(op, Q0).reshape(5, -1),
+                     "N=%d E=%d %s" % (N, om.E, kr))
+    dt = 1e-3
+    Qd = _dev(torch, Q)
+    ch.chorus_rk_step(cm, phys, Qd, dt, 2, ws)
+    torch.cuda.synchronize()
+    Qg, Qr, Qs = Qd.cpu().numpy(), om.ssp54(op, Q, dt, 2).reshape(5, -1), Q.reshape(5, -1)
+    for v in range(5):
+        err = np.linalg.norm(Qg[v] - Qr[v])
+        assert err <= 2e-5 * np.linalg.norm(Qr[v] - Qs[v]) + 1e-13 * np.linalg.norm(Qr[v]), (v, err)
+
+
 @pytest.mark.timeout(600)
 def test_mixed_vs_fp64_largest_workload(ch, torch_dev):
     """The metric's gate on the largest shell (331,776 hexes, N = 4, 21.2M
