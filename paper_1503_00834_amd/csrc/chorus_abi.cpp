@@ -886,7 +886,10 @@ static int rk_fp64(const Mesh &m, const chorus_physics *phys, const ClosureArgs 
         for (int k = 0; k < nst && e == hipSuccess; ++k) {
             const StagePlan &sp = plan[k];
             const double *qin = reg[sp.in];
-            StageArgs sa{sp.a >= 0 ? reg[sp.a] : nullptr, reg[sp.out], b.TQ, sp.c0, sp.c1, sp.c2 * dt,
+            // the traces of the final state have no reader: the next call
+            // pushes its own
+            const bool last = st == n_steps - 1 && k == nst - 1;
+            StageArgs sa{sp.a >= 0 ? reg[sp.a] : nullptr, reg[sp.out], last ? nullptr : b.TQ, sp.c0, sp.c1, sp.c2 * dt,
                          sp.b >= 0 ? reg[sp.b] : nullptr, sp.tout >= 0 ? reg[sp.tout] : nullptr, sp.d0, sp.d1,
                          sp.d2 * dt, 1, b.R0};
             e = run(1, [&] { return launch_flux64(m, G, P, qin, b.TQ, b.TV, sa, C, s); });
@@ -938,14 +941,16 @@ int chorus_rk_step(chorus_mesh_t mesh, const chorus_physics *phys, double *Q_dev
             for (int k = 0; k < nst && e == hipSuccess; ++k) {
                 const StagePlan &sp = plan[k];
                 const double *pin = reg[sp.in];
-                MixedStageArgs a{sp.a >= 0 ? reg[sp.a] : nullptr, reg[sp.out], TQm, sp.c0, sp.c1,
+                // the last stage ends in Q (both integrators' last stages
+                // write register 0 and no second register)
+                const bool last = st == n_steps - 1 && k == nst - 1;
+                MixedStageArgs a{sp.a >= 0 ? reg[sp.a] : nullptr, reg[sp.out], last ? nullptr : TQm, sp.c0, sp.c1,
                                  sp.c2 * dt, sp.b >= 0 ? reg[sp.b] : nullptr, sp.tout >= 0 ? reg[sp.tout] : nullptr,
-                                 sp.d0, sp.d1, sp.d2 * dt, 1};
+                                 sp.d0, sp.d1, sp.d2 * dt, 1, last ? g.Q0 : nullptr, last ? Q_dev : nullptr};
                 e = timed(1, s, [&] { return launch_flux_mixed(*m, g, P, pin, TQm, TVm, a, s); });
                 if (e == hipSuccess) e = timed(2, s, [&] { return launch_lift_mixed(*m, g, TVm, a, s); });
             }
         }
-        if (e == hipSuccess) e = launch_pert_end(g.Q0, reg[0], Q_dev, 5 * m->E * m->N * m->N * m->N, s);
         if (e != hipSuccess) return hip_fail(e, "rk_step (mixed)");
         if (phys->flags & CHORUS_CHECK_FINITE) return finite_check(*m, P, Q_dev, w, W, s);
         return CHORUS_OK;

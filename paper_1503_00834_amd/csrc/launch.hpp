@@ -128,7 +128,9 @@ struct GeoM {
     const float *rflux32;    // [E][3][NFL] radius at the d-flux points
 };
 
-// as StageArgs, on the perturbation P (mode 0 writes dQ/dt to Pout)
+// as StageArgs, on the perturbation P (mode 0 writes dQ/dt to Pout).  Last
+// stage of a call: the lift pass writes Qend = Q0 + Pout and leaves Pout as
+// the flux pass wrote it.
 struct MixedStageArgs {
     const double *A;
     double *Pout;
@@ -138,6 +140,8 @@ struct MixedStageArgs {
     double *Tout;
     double d0, d1, d2;
     int mode;
+    const double *Q0 = nullptr;
+    double *Qend = nullptr;
 };
 
 hipError_t launch_pert_begin(const Mesh &m, const GeoM &g, const double *Q, double *Pq, float *TQ, hipStream_t s);
@@ -155,7 +159,6 @@ hipError_t launch_bg_setup(const Mesh &m, const Geo &G, const double *Q0, const 
 // gradient of rho0 at the solution points (gout [E][3][NP])
 hipError_t launch_bg_entropy(const Mesh &m, const Geo &G, const PhysParams &P, const double *Q0, const double *TQ,
                              float *out, float *gout, hipStream_t s);
-hipError_t launch_pert_end(const double *Q0, const double *Pq, double *Q, int64_t n, hipStream_t s);
 hipError_t launch_to_float(const double *a, float *b, int64_t n, hipStream_t s);
 
 }  // namespace chorus

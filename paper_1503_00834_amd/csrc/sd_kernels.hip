@@ -37,14 +37,14 @@ namespace chorus {
 // ---------------------------------------------------------------------------
 // shared phases
 // ---------------------------------------------------------------------------
-template <int N, int EPB, int NT>
+template <int N, int EPB, int NT, bool SW = false>
 __device__ __forceinline__ void load_q(const double *__restrict__ Q, int64_t E, int64_t e0,
                                        double (*sq)[5][N * N * N]) {
     constexpr int NP = N * N * N;
     for (int it = threadIdx.x; it < EPB * 5 * NP; it += NT) {
         const int el = it / (5 * NP), r = it % (5 * NP), v = r / NP, p = r % NP;
         const int64_t e = e0 + el;
-        sq[el][v][p] = (e < E) ? Q[((int64_t)v * E + e) * NP + p] : (v == 0 || v == 4 ? 1.0 : 0.0);
+        sq[el][v][SW ? lds_sol<N>(p) : p] = (e < E) ? Q[((int64_t)v * E + e) * NP + p] : (v == 0 || v == 4 ? 1.0 : 0.0);
     }
 }
 
@@ -263,8 +263,9 @@ template <> struct Cfg64<4> { static constexpr int EPB = 1, NT = 64, MINW = 3; }
 template <> struct Cfg64<5> { static constexpr int EPB = 1, NT = 128, MINW = 3; };
 template <> struct Cfg64<6> { static constexpr int EPB = 1, NT = 256, MINW = 1; };
 
-// face traces of the element block's state (LDS) pushed to the neighbours
-template <int N, int EPB, int NT, bool SW = false>
+// face traces of the element block's state (LDS, lds_sol layout) pushed to
+// the neighbours
+template <int N, int EPB, int NT>
 __device__ __forceinline__ void push_traces64(const Ops<N> &op, const Geo &G, int64_t e0, const int32_t (*lk)[6],
                                               const int32_t (*inf)[6], const double (*sq)[5][N * N * N],
                                               double *__restrict__ TQout) {
@@ -279,7 +280,7 @@ __device__ __forceinline__ void push_traces64(const Ops<N> &op, const Geo &G, in
         for (int v = 0; v < 5; ++v) {
             double t = 0.0;
 #pragma unroll
-            for (int b = 0; b < N; ++b) t += op.I[m][b] * sq[el][v][SW ? lds_line<N>(base, b, st) : base + b * st];
+            for (int b = 0; b < N; ++b) t += op.I[m][b] * sq[el][v][lds_line<N>(base, b, st)];
             st_once(&out[v * NF2], t);
         }
     }
@@ -295,7 +296,7 @@ __global__ __launch_bounds__(NT) void k_trace_push(Ops<N> opa, Geo G, const doub
     __shared__ Ops<N> op;
     const int64_t e0 = (int64_t)blockIdx.x * EPB;
     ops_to_lds(opa, op);
-    load_q<N, EPB, NT>(Q, G.E, e0, sq);
+    load_q<N, EPB, NT, true>(Q, G.E, e0, sq);
     if ((int)threadIdx.x < EPB * 6) {
         const bool ok = e0 + threadIdx.x / 6 < G.E;
         lk[threadIdx.x / 6][threadIdx.x % 6] = ok ? G.link[e0 * 6 + threadIdx.x] : -1;
@@ -1000,7 +1001,7 @@ __global__ __launch_bounds__(NT) void k_lift64(Ops<N> opa, Geo G, const double *
     }
     if (S_.mode == 0 || S_.TQout == nullptr) return;
     __syncthreads();
-    push_traces64<N, EPB, NT, true>(op, G, e0, lk, inf, sq, S_.TQout);
+    push_traces64<N, EPB, NT>(op, G, e0, lk, inf, sq, S_.TQout);
 }
 
 // ---------------------------------------------------------------------------
