@@ -91,15 +91,13 @@ __device__ __forceinline__ void mlp_eval(const unsigned char *__restrict__ model
                                          f32x4_t (&out)[NPT]) {
     const int lane = threadIdx.x & 63, g = lane >> 4;
     const u32x4_t *fr = reinterpret_cast<const u32x4_t *>(model);
-    const float *fl = reinterpret_cast<const float *>(model + kMlpFloatOff);
+    const f32x4_t *fl = reinterpret_cast<const f32x4_t *>(model + kMlpFloatOff);
     // layer 1
     u32x4_t h1[2][NPT];
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
         const bf16x8_t a = __builtin_bit_cast(bf16x8_t, fr[mt * 64 + lane]);
-        f32x4_t b;  // bias as the accumulator's initial value
-#pragma unroll
-        for (int i = 0; i < 4; ++i) b[i] = fl[kMlpB1 + 16 * mt + 4 * g + i];
+        const f32x4_t b = fl[(kMlpB1 + 16 * mt) / 4 + g];  // bias as the accumulator's initial value
 #pragma unroll
         for (int pt = 0; pt < NPT; ++pt) {
             const f32x4_t c =
@@ -115,9 +113,7 @@ __device__ __forceinline__ void mlp_eval(const unsigned char *__restrict__ model
     for (int mt = 0; mt < 4; ++mt) {
         const bf16x8_t a0 = __builtin_bit_cast(bf16x8_t, fr[(4 + 2 * mt) * 64 + lane]);
         const bf16x8_t a1 = __builtin_bit_cast(bf16x8_t, fr[(5 + 2 * mt) * 64 + lane]);
-        f32x4_t b;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) b[i] = fl[kMlpB2 + 16 * mt + 4 * g + i];
+        const f32x4_t b = fl[(kMlpB2 + 16 * mt) / 4 + g];
 #pragma unroll
         for (int pt = 0; pt < NPT; ++pt) {
             f32x4_t c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, __builtin_bit_cast(bf16x8_t, h1[0][pt]), b, 0, 0, 0);
@@ -130,23 +126,15 @@ __device__ __forceinline__ void mlp_eval(const unsigned char *__restrict__ model
     // layer 3 (linear) and output scaling
     const bf16x8_t a0 = __builtin_bit_cast(bf16x8_t, fr[12 * 64 + lane]);
     const bf16x8_t a1 = __builtin_bit_cast(bf16x8_t, fr[13 * 64 + lane]);
+    const f32x4_t ym = fl[kMlpYMean / 4 + g], ys = fl[kMlpYStd / 4 + g], b3 = fl[kMlpB3 / 4 + g];
 #pragma unroll
     for (int pt = 0; pt < NPT; ++pt) {
         f32x4_t c = {0.f, 0.f, 0.f, 0.f};
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, __builtin_bit_cast(bf16x8_t, h2[0][pt]), c, 0, 0, 0);
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, __builtin_bit_cast(bf16x8_t, h2[1][pt]), c, 0, 0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int k = 4 * g + i;
-            out[pt][i] = fl[kMlpYMean + k] + fl[kMlpYStd + k] * (c[i] + fl[kMlpB3 + k]);
-        }
+        for (int i = 0; i < 4; ++i) out[pt][i] = ym[i] + ys[i] * (c[i] + b3[i]);
     }
-}
-
-// normalised feature -> float (FP64 arithmetic, then rounded to FP32)
-__device__ __forceinline__ float mlp_norm_feature(const unsigned char *__restrict__ model, int f, double x) {
-    const float *fl = reinterpret_cast<const float *>(model + kMlpFloatOff);
-    return (float)((x - (double)fl[kMlpXMean + f]) * (double)fl[kMlpXInv + f]);
 }
 
 }  // namespace chorus

@@ -154,52 +154,64 @@ __global__ __launch_bounds__(NT) void k_trace(Ops<N> opa, Geo G, const double *_
     }
 }
 
+// Normalised network input of one solution point (state q, gradients g), in
+// FP64 before it is rounded, as the B-operand words of the first layer: four
+// times eight features (pairs of bfloat16), 20 features and padding.  The
+// thread that forms a point's gradients has all of them in registers; when
+// each lane of the network fetched its eight features one by one through
+// per-lane selects, this took 93 of the fused pass's 694 us on 98,304 hexes.
+__device__ __forceinline__ void closure_input(const unsigned char *__restrict__ model, const double q[5],
+                                              const double g[15], u32x4_t w[3]) {
+    const f32x4_t *mean = reinterpret_cast<const f32x4_t *>(model + kMlpFloatOff + 4 * kMlpXMean);
+    const f32x4_t *inv = reinterpret_cast<const f32x4_t *>(model + kMlpFloatOff + 4 * kMlpXInv);
+    w[2] = u32x4_t{0, 0, 0, 0};
+#pragma unroll
+    for (int f4 = 0; f4 < kMlpIn / 4; ++f4) {
+        const f32x4_t mu = mean[f4], is = inv[f4];
+        float x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int f = 4 * f4 + i;
+            x[i] = (float)(((f < 5 ? q[f < 5 ? f : 0] : g[f < 5 ? 0 : f - 5]) - (double)mu[i]) * (double)is[i]);
+        }
+        w[f4 >> 1][(f4 & 1) * 2] = bf16_pair(x[0], x[1]);
+        w[f4 >> 1][(f4 & 1) * 2 + 1] = bf16_pair(x[2], x[3]);
+    }
+}
+
 // learned subgrid flux at the solution points of the block's elements (one
-// wave, all points in 16-point tiles): features (Q, grad Q) -> network ->
-// tau[k][E][NP] (global), or into the block's LDS copy stau when given
-template <int N, int EPB, int NT, typename GT>
-__device__ __forceinline__ void closure_tau(const ClosureArgs &C, int64_t E, int64_t e0,
-                                            double (*sq)[5][N * N * N], GT (*sgr)[15][N * N * N],
+// wave, all points in 16-point tiles): inputs xf (LDS, four words of eight
+// features per point) -> network -> tau[k][E][NP] (global), or into the
+// block's LDS copy stau when given, which may share space with xf
+template <int N, int EPB, int NT>
+__device__ __forceinline__ void closure_tau(const ClosureArgs &C, int64_t E, int64_t e0, const u32x4_t (*xf)[4],
                                             float (*stau)[15][N * N * N] = nullptr) {
     constexpr int NP = N * N * N, NPTS = EPB * NP, NPT = (NPTS + 15) / 16;
-    // point tiles evaluated together (fewer live accumulators than all of
-    // the block's tiles at once)
-    constexpr int TB = NPT < 2 ? NPT : 2;
     static_assert(NT == 64, "the closure runs one wave per block");
     const int lane = threadIdx.x, g = lane >> 4;
+    u32x4_t xb[NPT];
 #pragma unroll
-    for (int t0 = 0; t0 < NPT; t0 += TB) {
-        u32x4_t xb[TB];
+    for (int j = 0; j < NPT; ++j) {
+        const int pidx = 16 * j + (lane & 15);
+        const u32x4_t w = xf[pidx < NPTS ? pidx : 0][g];
+        xb[j] = pidx < NPTS ? w : u32x4_t{0, 0, 0, 0};
+    }
+    __syncthreads();
+    // all tiles together: the weights are read once (two tiles at a time take
+    // 13 us more per pass on 98,304 hexes)
+    f32x4_t out[NPT];
+    mlp_eval<NPT>(C.model, xb, out);
 #pragma unroll
-        for (int j = 0; j < TB; ++j) {
-            const int pidx = 16 * (t0 + j) + (lane & 15);
-            const int el = pidx / NP, sp = pidx % NP;
-            const bool ok = pidx < NPTS && e0 + el < E;
-            float x[8];
+    for (int j = 0; j < NPT; ++j) {
+        const int pidx = 16 * j + (lane & 15);
+        const int el = pidx / NP, sp = pidx % NP;
+        if (pidx >= NPTS || e0 + el >= E) continue;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int f = 8 * g + i;
-                double raw = 0.0;
-                if (ok && f < 5) raw = sq[el][f][lds_sol<N>(sp)];
-                else if (ok && f < 20) raw = (double)sgr[el][f - 5][lds_sol<N>(sp)];
-                x[i] = (ok && f < 20) ? mlp_norm_feature(C.model, f, raw) : 0.0f;
-            }
-            xb[j] = u32x4_t{bf16_pair(x[0], x[1]), bf16_pair(x[2], x[3]), bf16_pair(x[4], x[5]), bf16_pair(x[6], x[7])};
-        }
-        f32x4_t out[TB];
-        mlp_eval<TB>(C.model, xb, out);
-#pragma unroll
-        for (int j = 0; j < TB; ++j) {
-            const int pidx = 16 * (t0 + j) + (lane & 15);
-            const int el = pidx / NP, sp = pidx % NP;
-            if (pidx >= NPTS || e0 + el >= E) continue;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int k = 4 * g + i;
-                if (k >= kMlpOut) continue;
-                if (stau) stau[el][k][sp] = out[j][i];
-                else C.tau[((int64_t)k * E + e0 + el) * NP + sp] = out[j][i];
-            }
+        for (int i = 0; i < 4; ++i) {
+            const int k = 4 * g + i;
+            if (k >= kMlpOut) continue;
+            if (stau) stau[el][k][sp] = out[j][i];
+            else C.tau[((int64_t)k * E + e0 + el) * NP + sp] = out[j][i];
         }
     }
 }
@@ -445,27 +457,27 @@ __device__ __forceinline__ double source64(int v, double rho, double mx, double 
 // RAD: radiative diffusivity varying with radius (radius of each flux point
 // read with its geometry), else the constant P.kappa_r
 template <int N, int EPB, int NT, int PART, bool RAD>
-__global__ __launch_bounds__(NT, Cfg64<N>::MINW) void k_flux64(Ops<N> opa, Geo G, PhysParams P, const double *__restrict__ Q,
+__global__ __launch_bounds__(NT, (PART == 2 && RAD) ? 3 : Cfg64<N>::MINW) void k_flux64(Ops<N> opa, Geo G, PhysParams P, const double *__restrict__ Q,
                                                const double *__restrict__ TQ, double *__restrict__ TV,
                                                StageArgs S_, ClosureArgs C) {
     constexpr bool CL = PART != 0;
     using Sh = Sh64<N, EPB, NT>;
     constexpr int NP = Sh::NP, NF2 = Sh::NF2, NFL = Sh::NFL, NINTD = Sh::NINTD;
     __shared__ double sq[EPB][5][NP];
-    // gradients at the solution points (the network-only pass keeps them in
-    // FP32: they are network inputs, rounded to bfloat16 after
-    // normalisation)
-    __shared__ std::conditional_t<PART == 1, float, double> sgr[EPB][15][NP];
+    __shared__ double sgr[EPB][15][NP];  // gradients at the solution points (unused in PART 1)
     // the common solution is consumed by the gradients before the subgrid
     // flux (PART 2) and the first direction's fluxes are written
     __shared__ union {
         double sqs[EPB][6][5][NF2];
         struct {
             double sft[EPB][5][NFL];
-            float stau[PART == 2 ? EPB : 1][15][PART == 2 ? NP : 1];  // subgrid flux (PART 2)
+            union {
+                u32x4_t xf[CL ? EPB * NP : 1][4];                     // network inputs
+                float stau[CL ? EPB : 1][15][CL ? NP : 1];            // subgrid flux (PART 2)
+            } C;
         } F;
     } U;
-    auto &stau = U.F.stau;
+    auto &stau = U.F.C.stau;
     __shared__ int32_t lk[EPB][6], inf[EPB][6];
     __shared__ Ops<N> op;
     const int64_t e0 = (int64_t)blockIdx.x * EPB, E = G.E;
@@ -538,13 +550,14 @@ __global__ __launch_bounds__(NT, Cfg64<N>::MINW) void k_flux64(Ops<N> opa, Geo G
         for (int v = 0; v < 5; ++v) U.sqs[el][f][v][pp] = qs[v];
     }
     __syncthreads();
-    // gradients at the solution points
+    // gradients at the solution points, network inputs
+    u32x4_t xw[CL ? Sh::IT_SOL : 1][3];
 #pragma unroll
     for (int k = 0; k < Sh::IT_SOL; ++k) {
         const int it = threadIdx.x + k * NT;
         if (it >= EPB * NP) break;
         const int el = it / NP, p = it % NP;
-        double dq[3][5];
+        double dq[3][5], gr[15];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             int a, t1, t2;
@@ -560,17 +573,32 @@ __global__ __launch_bounds__(NT, Cfg64<N>::MINW) void k_flux64(Ops<N> opa, Geo G
         for (int v = 0; v < 5; ++v)
 #pragma unroll
             for (int c = 0; c < 3; ++c)
-                sgr[el][v * 3 + c][lds_sol<N>(p)] = Gm[k][c] * dq[0][v] + Gm[k][3 + c] * dq[1][v] + Gm[k][6 + c] * dq[2][v];
+                gr[v * 3 + c] = Gm[k][c] * dq[0][v] + Gm[k][3 + c] * dq[1][v] + Gm[k][6 + c] * dq[2][v];
+        if constexpr (PART != 1)
+            for (int f = 0; f < 15; ++f) sgr[el][f][lds_sol<N>(p)] = gr[f];
+        if constexpr (CL) {
+            double q[5];
+            for (int v = 0; v < 5; ++v) q[v] = sq[el][v][lds_sol<N>(p)];
+            closure_input(C.model, q, gr, xw[k]);
+        }
     }
     __syncthreads();
-    if constexpr (PART == 1) {
-        // subgrid flux at the solution points -> C.tau
-        closure_tau<N, EPB, NT>(C, E, e0, sq, sgr);
-        return;
-    }
-    if constexpr (PART == 2) {
-        // subgrid flux at the solution points -> LDS
-        closure_tau<N, EPB, NT>(C, E, e0, sq, sgr, stau);
+    if constexpr (CL) {
+        // (over the common solution, which the gradients have consumed)
+#pragma unroll
+        for (int k = 0; k < Sh::IT_SOL; ++k) {
+            const int it = threadIdx.x + k * NT;
+            if (it >= EPB * NP) break;
+            for (int w = 0; w < 3; ++w) U.F.C.xf[it][w] = xw[k][w];
+            U.F.C.xf[it][3] = u32x4_t{0, 0, 0, 0};
+        }
+        __syncthreads();
+        // subgrid flux at the solution points -> C.tau (PART 1) or LDS
+        if constexpr (PART == 1) {
+            closure_tau<N, EPB, NT>(C, E, e0, U.F.C.xf);
+            return;
+        }
+        closure_tau<N, EPB, NT>(C, E, e0, U.F.C.xf, stau);
         __syncthreads();
     }
     // face points: own viscous flux to the neighbour, own-side common flux
