@@ -260,6 +260,22 @@ __global__ __launch_bounds__(NT) void k_features(Ops<N> opa, Geo G, PhysParams P
 template <int N, int EPB, int NT>
 struct Sh64 {
     static constexpr int NP = N * N * N, NF2 = N * N, NFL = (N + 1) * N * N, NINTD = (N - 1) * N * N;
+    // LDS of the flux pass.  A point's state and gradients are one record of SR
+    // doubles, read as pairs: a wave's 16-byte LDS read takes 6.3 cycles, an
+    // 8-byte one 5.0.  Records of 22 doubles put 16 consecutive points on
+    // distinct banks; order 6, with the most line reads, is faster with the
+    // two spare doubles (1,125 against 1,230 us per step below), the others
+    // with less LDS.  Face and flux points in records of 6 (5 values) at order
+    // 6, where they fit beside three blocks per compute unit; at order 5 they
+    // cost a block (1,380 against 1,335 us) and at orders 2 and 3 they gain
+    // nothing: planes.
+    // us per RK3 step, one plane per field -> records (hexes of the mesh):
+    // N = 2 (192,000) 1,027 -> 1,010; N = 3 (98,304) 1,433 -> 1,375;
+    // N = 5 (24,000) 1,434 -> 1,335; N = 6 (12,288) 1,256 -> 1,125.
+    static constexpr bool FREC = N == 6;
+    static constexpr int SR = N == 6 ? 22 : 20, NV = FREC ? 6 : 5;
+    static constexpr __device__ int face_at(int f, int v, int pp) { return FREC ? (f * NF2 + pp) * 6 + v : (f * 5 + v) * NF2 + pp; }
+    static constexpr __device__ int flux_at(int v, int fl) { return FREC ? fl * 6 + v : v * NFL + fl; }
     static constexpr int IT_SOL = (EPB * NP + NT - 1) / NT;
     static constexpr int IT_FACE = (EPB * 6 * NF2 + NT - 1) / NT;
     static constexpr int IT_INTD = (EPB * NINTD + NT - 1) / NT;
@@ -335,6 +351,66 @@ __device__ __forceinline__ double line_interp_s(const Ops<N> &op, const T *fld, 
     return t;
 }
 
+// An element's state and gradients in LDS, one plane per field: the values
+// at flux point m of the line (base, st).
+template <int N>
+struct Planes {
+    const double (*sq)[N * N * N], (*sgr)[N * N * N];
+    __device__ __forceinline__ void state(const Ops<N> &op, int m, int base, int st, double q[5]) const {
+        for (int v = 0; v < 5; ++v) q[v] = line_interp_s<N>(op, sq[v], m, base, st);
+    }
+    __device__ __forceinline__ void all(const Ops<N> &op, int m, int base, int st, double q[5], double g[5][3]) const {
+        for (int v = 0; v < 5; ++v) {
+            q[v] = line_interp_s<N>(op, sq[v], m, base, st);
+            for (int c = 0; c < 3; ++c) g[v][c] = line_interp_s<N>(op, sgr[v * 3 + c], m, base, st);
+        }
+    }
+};
+
+// five values of a record (pairs, 16-byte aligned) or of planes PL apart
+template <bool REC, int PL>
+__device__ __forceinline__ void load5(const double *r, double x[5]) {
+    if constexpr (REC) {
+        const double2 a = *reinterpret_cast<const double2 *>(r), b = *reinterpret_cast<const double2 *>(r + 2);
+        x[0] = a.x, x[1] = a.y, x[2] = b.x, x[3] = b.y, x[4] = r[4];
+    } else {
+        for (int v = 0; v < 5; ++v) x[v] = r[v * PL];
+    }
+}
+
+// The same with one record per point (5 state values, then 15 gradients):
+// a line is read as pairs of fields.
+template <int N, int SR>
+struct Records {
+    const double (*r)[SR];
+    __device__ __forceinline__ void pair(const Ops<N> &op, int m, int base, int st, int j, double &x, double &y) const {
+        x = y = 0.0;
+#pragma unroll
+        for (int b = 0; b < N; ++b) {
+            const double2 t = *reinterpret_cast<const double2 *>(&r[base + b * st][2 * j]);
+            x += op.I[m][b] * t.x;
+            y += op.I[m][b] * t.y;
+        }
+    }
+    __device__ __forceinline__ void state(const Ops<N> &op, int m, int base, int st, double q[5]) const {
+        pair(op, m, base, st, 0, q[0], q[1]);
+        pair(op, m, base, st, 1, q[2], q[3]);
+        double t = 0.0;
+#pragma unroll
+        for (int b = 0; b < N; ++b) t += op.I[m][b] * r[base + b * st][4];
+        q[4] = t;
+    }
+    __device__ __forceinline__ void all(const Ops<N> &op, int m, int base, int st, double q[5], double g[5][3]) const {
+        double x[20];
+#pragma unroll
+        for (int j = 0; j < 10; ++j) pair(op, m, base, st, j, x[2 * j], x[2 * j + 1]);
+        for (int v = 0; v < 5; ++v) {
+            q[v] = x[v];
+            for (int c = 0; c < 3; ++c) g[v][c] = x[5 + v * 3 + c];
+        }
+    }
+};
+
 // common interface solution at a face point with the own values fo (BR1
 // average with the neighbour trace nq, wall state, or average with the
 // far-field state)
@@ -350,15 +426,15 @@ __device__ __forceinline__ void common_value64(const double fo[5], int32_t nb, i
     }
 }
 
-// the same at point pp of face f from the element's state sq in LDS
-template <int N>
-__device__ __forceinline__ void common_point64(const Ops<N> &op, const double (*sq)[N * N * N], int f, int pp,
+// the same at point pp of face f from the element's state in LDS
+template <int N, typename FS>
+__device__ __forceinline__ void common_point64(const Ops<N> &op, const FS &fs, int f, int pp,
                                                int32_t nb, int32_t info, const double nq[5], const double Sf[3],
                                                const PhysParams &P, double qs[5]) {
     const int d = f >> 1, m = (f & 1) ? N : 0;
     const int base = sol_of<N>(d, 0, pp % N, pp / N), st = stride_of<N>(d);
     double fo[5];
-    for (int v = 0; v < 5; ++v) fo[v] = line_interp_s<N>(op, sq[v], m, base, st);
+    fs.state(op, m, base, st, fo);
     common_value64(fo, nb, info, nq, Sf, P, qs);
 }
 
@@ -395,19 +471,15 @@ __device__ __forceinline__ void face_flux64(const double fo[5], const double g[5
 
 // the same at point pp of face f from the element's state, gradients and
 // (CL) subgrid flux in LDS
-template <int N, bool CL, typename GT>
-__device__ __forceinline__ void face_point64(const Ops<N> &op, const double (*sq)[N * N * N],
-                                             const GT (*sgr)[N * N * N], const float *stau, int f, int pp,
+template <int N, bool CL, typename FS>
+__device__ __forceinline__ void face_point64(const Ops<N> &op, const FS &fs, const float *stau, int f, int pp,
                                              int32_t nb, int32_t info, const double nq[5], const double Sf[3],
                                              const PhysParams &P, double kr, double *__restrict__ TV, double ffc[5]) {
     constexpr int NP = N * N * N;
     const int d = f >> 1, m = (f & 1) ? N : 0;
     const int base = sol_of<N>(d, 0, pp % N, pp / N), st = stride_of<N>(d);
     double fo[5], g[5][3];
-    for (int v = 0; v < 5; ++v) {
-        fo[v] = line_interp_s<N>(op, sq[v], m, base, st);
-        for (int c = 0; c < 3; ++c) g[v][c] = line_interp_s<N>(op, sgr[v * 3 + c], m, base, st);
-    }
+    fs.all(op, m, base, st, fo, g);
     auto ts = [&](int v) {
         double x = 0.0;
         for (int c = 0; c < 3; ++c) x += line_interp<N>(op, stau + (v * 3 + c) * NP, m, base, st) * Sf[c];
@@ -418,18 +490,14 @@ __device__ __forceinline__ void face_point64(const Ops<N> &op, const double (*sq
 
 // transformed flux along S at the interior flux point m of line (t1, t2) of
 // direction d
-template <int N, bool CL, typename GT>
-__device__ __forceinline__ void interior_point64(const Ops<N> &op, const double (*sq)[N * N * N],
-                                                 const GT (*sgr)[N * N * N], const float *stau, int d, int m,
+template <int N, bool CL, typename FS>
+__device__ __forceinline__ void interior_point64(const Ops<N> &op, const FS &fs, const float *stau, int d, int m,
                                                  int tt, const double S[3], const PhysParams &P, double kr,
                                                  double out[5]) {
     constexpr int NP = N * N * N;
     const int base = sol_of<N>(d, 0, tt % N, tt / N), st = stride_of<N>(d);
     double qf[5], g[5][3], fi[5], fv[5];
-    for (int v = 0; v < 5; ++v) {
-        qf[v] = line_interp_s<N>(op, sq[v], m, base, st);
-        for (int c = 0; c < 3; ++c) g[v][c] = line_interp_s<N>(op, sgr[v * 3 + c], m, base, st);
-    }
+    fs.all(op, m, base, st, qf, g);
     flux_inviscid(qf, S, P.gamma - 1.0, fi);
     flux_viscous(qf, g, S, P, kr, fv);
     for (int v = 0; v < 5; ++v) {
@@ -463,14 +531,14 @@ __global__ __launch_bounds__(NT, (PART == 2 && RAD) ? 3 : Cfg64<N>::MINW) void k
     constexpr bool CL = PART != 0;
     using Sh = Sh64<N, EPB, NT>;
     constexpr int NP = Sh::NP, NF2 = Sh::NF2, NFL = Sh::NFL, NINTD = Sh::NINTD;
-    __shared__ double sq[EPB][5][NP];
-    __shared__ double sgr[EPB][15][NP];  // gradients at the solution points (unused in PART 1)
+    constexpr int SR = Sh::SR;
+    __shared__ alignas(16) double rec[EPB][NP][SR];  // state, gradients at the solution points
     // the common solution is consumed by the gradients before the subgrid
     // flux (PART 2) and the first direction's fluxes are written
     __shared__ union {
-        double sqs[EPB][6][5][NF2];
+        alignas(16) double sqs[EPB][6 * NF2 * Sh::NV];
         struct {
-            double sft[EPB][5][NFL];
+            alignas(16) double sft[EPB][NFL * Sh::NV];
             union {
                 u32x4_t xf[CL ? EPB * NP : 1][4];                     // network inputs
                 float stau[CL ? EPB : 1][15][CL ? NP : 1];            // subgrid flux (PART 2)
@@ -479,7 +547,7 @@ __global__ __launch_bounds__(NT, (PART == 2 && RAD) ? 3 : Cfg64<N>::MINW) void k
     } U;
     auto &stau = U.F.C.stau;
     __shared__ int32_t lk[EPB][6], inf[EPB][6];
-    __shared__ Ops<N> op;
+    __shared__ alignas(16) Ops<N> op;
     const int64_t e0 = (int64_t)blockIdx.x * EPB, E = G.E;
     // every global input of the element block before the first wait;
     // unpredicated loads through clamped indices (items past the end read
@@ -534,7 +602,7 @@ __global__ __launch_bounds__(NT, (PART == 2 && RAD) ? 3 : Cfg64<N>::MINW) void k
     for (int k = 0; k < Sh::IT_SOL; ++k) {
         const int it = threadIdx.x + k * NT;
         if (it >= EPB * NP) break;
-        for (int v = 0; v < 5; ++v) sq[it / NP][v][lds_sol<N>(it % NP)] = qv[k][v];
+        for (int v = 0; v < 5; ++v) rec[it / NP][it % NP][v] = qv[k][v];
     }
     __syncthreads();
     // common interface solution (the own face values are formed again in
@@ -546,8 +614,8 @@ __global__ __launch_bounds__(NT, (PART == 2 && RAD) ? 3 : Cfg64<N>::MINW) void k
         const int el = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
         if (e0 + el >= E) continue;
         double qs[5];
-        common_point64<N>(op, sq[el], f, pp, lk[el][f], inf[el][f], nq[k], Sf[k], P, qs);
-        for (int v = 0; v < 5; ++v) U.sqs[el][f][v][pp] = qs[v];
+        common_point64<N>(op, Records<N, SR>{rec[el]}, f, pp, lk[el][f], inf[el][f], nq[k], Sf[k], P, qs);
+        for (int v = 0; v < 5; ++v) U.sqs[el][Sh::face_at(f, v, pp)] = qs[v];
     }
     __syncthreads();
     // gradients at the solution points, network inputs
@@ -563,11 +631,15 @@ __global__ __launch_bounds__(NT, (PART == 2 && RAD) ? 3 : Cfg64<N>::MINW) void k
             int a, t1, t2;
             split_sol<N>(d, p, a, t1, t2);
             const int base = sol_of<N>(d, 0, t1, t2), st = stride_of<N>(d), pp = t1 + N * t2;
-            for (int v = 0; v < 5; ++v) {
-                double t = op.D[a][0] * U.sqs[el][2 * d][v][pp] + op.D[a][N] * U.sqs[el][2 * d + 1][v][pp];
+            double ql[5], qr[5];
+            load5<Sh::FREC, NF2>(&U.sqs[el][Sh::face_at(2 * d, 0, pp)], ql);
+            load5<Sh::FREC, NF2>(&U.sqs[el][Sh::face_at(2 * d + 1, 0, pp)], qr);
+            for (int v = 0; v < 5; ++v) dq[d][v] = op.D[a][0] * ql[v] + op.D[a][N] * qr[v];
 #pragma unroll
-                for (int b = 0; b < N; ++b) t += op.B[a][b] * sq[el][v][lds_line<N>(base, b, st)];
-                dq[d][v] = t;
+            for (int b = 0; b < N; ++b) {
+                double q[5];
+                load5<true, 1>(rec[el][base + b * st], q);
+                for (int v = 0; v < 5; ++v) dq[d][v] += op.B[a][b] * q[v];
             }
         }
         for (int v = 0; v < 5; ++v)
@@ -575,10 +647,10 @@ __global__ __launch_bounds__(NT, (PART == 2 && RAD) ? 3 : Cfg64<N>::MINW) void k
             for (int c = 0; c < 3; ++c)
                 gr[v * 3 + c] = Gm[k][c] * dq[0][v] + Gm[k][3 + c] * dq[1][v] + Gm[k][6 + c] * dq[2][v];
         if constexpr (PART != 1)
-            for (int f = 0; f < 15; ++f) sgr[el][f][lds_sol<N>(p)] = gr[f];
+            for (int f = 0; f < 15; ++f) rec[el][p][5 + f] = gr[f];
         if constexpr (CL) {
             double q[5];
-            for (int v = 0; v < 5; ++v) q[v] = sq[el][v][lds_sol<N>(p)];
+            for (int v = 0; v < 5; ++v) q[v] = rec[el][p][v];
             closure_input(C.model, q, gr, xw[k]);
         }
     }
@@ -612,7 +684,7 @@ __global__ __launch_bounds__(NT, (PART == 2 && RAD) ? 3 : Cfg64<N>::MINW) void k
         const int el = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
         if (e0 + el >= E) continue;
         const double kr = RAD ? kappa_r_at(P, krf[k]) : krf[k];
-        face_point64<N, CL>(op, sq[el], sgr[el], CL ? &stau[el][0][0] : nullptr, f, pp, lk[el][f], inf[el][f], nq[k],
+        face_point64<N, CL>(op, Records<N, SR>{rec[el]}, CL ? &stau[el][0][0] : nullptr, f, pp, lk[el][f], inf[el][f], nq[k],
                             Sf[k], P, kr, TV, ffc[k]);
     }
     // per direction: transformed flux at the d-flux points, its derivative
@@ -633,10 +705,10 @@ __global__ __launch_bounds__(NT, (PART == 2 && RAD) ? 3 : Cfg64<N>::MINW) void k
             const int m = 1 + q % (N - 1), tt = q / (N - 1);
             if (e0 + el >= E) continue;
             double fi[5];
-            interior_point64<N, CL>(op, sq[el], sgr[el], CL ? &stau[el][0][0] : nullptr, d, m, tt, Si[cur][k], P,
+            interior_point64<N, CL>(op, Records<N, SR>{rec[el]}, CL ? &stau[el][0][0] : nullptr, d, m, tt, Si[cur][k], P,
                                     RAD ? kappa_r_at(P, kri[cur][k]) : kri[cur][k], fi);
             const int fl = m + (N + 1) * tt;
-            for (int v = 0; v < 5; ++v) U.F.sft[el][v][fl] = fi[v];
+            for (int v = 0; v < 5; ++v) U.F.sft[el][Sh::flux_at(v, fl)] = fi[v];
         }
 #pragma unroll
         for (int k = 0; k < Sh::IT_FACE; ++k) {
@@ -646,7 +718,7 @@ __global__ __launch_bounds__(NT, (PART == 2 && RAD) ? 3 : Cfg64<N>::MINW) void k
             if ((f >> 1) != d || e0 + el >= E) continue;
             const double sg = (f & 1) ? 1.0 : -1.0;
             const int fl = ((f & 1) ? N : 0) + (N + 1) * pp;
-            for (int v = 0; v < 5; ++v) U.F.sft[el][v][fl] = sg * ffc[k][v];
+            for (int v = 0; v < 5; ++v) U.F.sft[el][Sh::flux_at(v, fl)] = sg * ffc[k][v];
         }
         __syncthreads();
 #pragma unroll
@@ -657,13 +729,14 @@ __global__ __launch_bounds__(NT, (PART == 2 && RAD) ? 3 : Cfg64<N>::MINW) void k
             int a, t1, t2;
             split_sol<N>(d, p, a, t1, t2);
             const int fb = (N + 1) * (t1 + N * t2);
+            double t[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int v = 0; v < 5; ++v) {
-                double t = 0.0;
-#pragma unroll
-                for (int mm = 0; mm <= N; ++mm) t += op.D[a][mm] * U.F.sft[el][v][fb + mm];
-                div[k][v] += t;
+            for (int mm = 0; mm <= N; ++mm) {
+                double fm[5];
+                load5<Sh::FREC, NFL>(&U.F.sft[el][Sh::flux_at(0, fb + mm)], fm);
+                for (int v = 0; v < 5; ++v) t[v] += op.D[a][mm] * fm[v];
             }
+            for (int v = 0; v < 5; ++v) div[k][v] += t[v];
         }
         __syncthreads();
     }
@@ -693,8 +766,8 @@ __global__ __launch_bounds__(NT, (PART == 2 && RAD) ? 3 : Cfg64<N>::MINW) void k
         if (e >= E) continue;
         const double iJ = gq[k][0];
         const double g0 = P.GM * gq[k][1], g1 = P.GM * gq[k][2], g2 = P.GM * gq[k][3];
-        const int ps = lds_sol<N>(p);
-        const double rho = sq[el][0][ps], mx = sq[el][1][ps], my = sq[el][2][ps], mz = sq[el][3][ps];
+        const double *r = rec[el][p];
+        const double rho = r[0], mx = r[1], my = r[2], mz = r[3];
         double M[5];
         M[0] = 0.0;
         M[1] = rho * g0 - 2.0 * P.omega * my;
@@ -708,7 +781,7 @@ __global__ __launch_bounds__(NT, (PART == 2 && RAD) ? 3 : Cfg64<N>::MINW) void k
                 S_.Qout[gi] = R;
                 continue;
             }
-            const double q = sq[el][v][ps];
+            const double q = r[v];
             if (useT) S_.Tout[gi] = S_.d0 * bv[k][v] + S_.d1 * (q + S_.d2 * R);
             S_.Qout[gi] = S_.c0 * av[k][v] + S_.c1 * (q + S_.c2 * R);
         }
@@ -1110,7 +1183,7 @@ __global__ __launch_bounds__(Wide<N>::NT, 4) void k_flux64_wide(Ops<N> opa, Geo 
     __syncthreads();
     if (isf) {
         double qs[5];
-        common_point64<N>(op, sq, f, pp, lk[f], inf[f], nq, S, P, qs);
+        common_point64<N>(op, Planes<N>{sq, sgr}, f, pp, lk[f], inf[f], nq, S, P, qs);
         for (int v = 0; v < 5; ++v) U.sqs[f][v][pp] = qs[v];
     }
     __syncthreads();
@@ -1140,11 +1213,11 @@ __global__ __launch_bounds__(Wide<N>::NT, 4) void k_flux64_wide(Ops<N> opa, Geo 
     const double kr = RAD ? kappa_r_at(P, rl) : P.kappa_r;
     if (isf) {
         double ffc[5];
-        face_point64<N, false>(op, sq, sgr, nullptr, f, pp, lk[f], inf[f], nq, S, P, kr, TV, ffc);
+        face_point64<N, false>(op, Planes<N>{sq, sgr}, nullptr, f, pp, lk[f], inf[f], nq, S, P, kr, TV, ffc);
         for (int v = 0; v < 5; ++v) U.sft[d][v][fl] = sg * ffc[v];
     } else if (isi) {
         double fi[5];
-        interior_point64<N, false>(op, sq, sgr, nullptr, d, m, tt, S, P, kr, fi);
+        interior_point64<N, false>(op, Planes<N>{sq, sgr}, nullptr, d, m, tt, S, P, kr, fi);
         for (int v = 0; v < 5; ++v) U.sft[d][v][fl] = fi[v];
     }
     __syncthreads();
