@@ -195,8 +195,8 @@ __device__ __forceinline__ void dflux_viscous(const PtState &s, const float S[3]
 // ---------------------------------------------------------------------------
 // element phases (generic N; items per thread fixed at compile time)
 // ---------------------------------------------------------------------------
-// (ND: directions whose fluxes are held together)
-template <int N, int ND = 1>
+// The element of k_flux_mixed_wide, whose threads each take one field: planes
+template <int N>
 struct MixedLds {
     static constexpr int NP = N * N * N, NF2 = N * N, NFL = (N + 1) * N * N;
     float f[NFIELD][NP];          // perturbation + background fields
@@ -204,9 +204,58 @@ struct MixedLds {
     float g[NGRAD][NP];           // gradients
     union {
         float cs[5][6][NF2];       // common values of the perturbation
-        float ft[ND][5][NFL];      // transformed fluxes, written after cs is consumed
+        float ft[3][5][NFL];       // transformed fluxes, written after cs is consumed
     } u;
     int32_t lk[6], inf[6];        // neighbour element and info word per face
+};
+
+// The element of k_flux_mixed: the 7 field values (slots F_*), the gradients
+// (slot GR + 3 f + c) and the remainders (the other slots and plo34) of a
+// point in one record of 28 floats, read in quads (16 consecutive points lie
+// on distinct banks), or a plane per slot at order 4, where memory bounds the
+// pass and the quads cost registers.  us per RK3 step, planes -> records
+// (hexes of the mesh): N = 3 (98,304) 1,080 -> 1,076; N = 4 (41,472)
+// 802 -> 829; N = 5 (24,000) 1,070 -> 1,002; N = 6 (12,288) 954 -> 850 (with
+// the radial diffusivity 995 -> 974).
+template <int N>
+struct MixedEl {
+    static constexpr int NP = N * N * N, NF2 = N * N, NFL = (N + 1) * N * N, GR = 8, SLOTS = 28;
+    static constexpr bool REC = N != 4;
+    static_assert(GR + NGRAD + 2 == SLOTS, "slots of a point");
+    alignas(16) float r[NP * SLOTS];
+    float plo34[2][NP];           // remainders of F_MZ, F_EP
+    union {
+        float cs[5][6][NF2];       // common values of the perturbation
+        float ft[5][NFL];          // transformed fluxes, written after cs is consumed
+    } u;
+    int32_t lk[6], inf[6];        // neighbour element and info word per face
+    __device__ __forceinline__ float &at(int slot, int p) { return r[REC ? p * SLOTS + slot : slot * NP + p]; }
+    // FP64 perturbation minus its FP32 value (stage update)
+    __device__ __forceinline__ float &plo(int v, int p) {
+        return v == 0 ? at(NFIELD, p) : v < 3 ? at(GR + NGRAD + v - 1, p) : plo34[v - 3][p];
+    }
+    // x[i] += w slot 4 j + i of point p
+    __device__ __forceinline__ void add_quad(float w, int p, int j, float x[4]) const {
+        if constexpr (REC) {
+            const float4 t = *reinterpret_cast<const float4 *>(&r[p * SLOTS + 4 * j]);
+            x[0] += w * t.x;
+            x[1] += w * t.y;
+            x[2] += w * t.z;
+            x[3] += w * t.w;
+        } else {
+            for (int i = 0; i < 4; ++i) x[i] += w * r[(4 * j + i) * NP + p];
+        }
+    }
+    // quads J0..J1-1 at flux point m of the line (base, st)
+    template <int J0, int J1>
+    __device__ __forceinline__ void line(const OpsF<N> &op, int m, int base, int st, float *x) const {
+#pragma unroll
+        for (int i = 0; i < 4 * (J1 - J0); ++i) x[i] = 0.0f;
+#pragma unroll
+        for (int j = J0; j < J1; ++j)
+#pragma unroll
+            for (int b = 0; b < N; ++b) add_quad(op.I[m][b], base + b * st, j, x + 4 * (j - J0));
+    }
 };
 
 template <int N, int EPB, int NT>
@@ -294,7 +343,7 @@ __device__ __forceinline__ void prologue_load_metrics(const GeoF &G, int64_t e0,
 
 // move the prologue registers into the element LDS
 template <int N, int EPB, int NT>
-__device__ __forceinline__ void prologue_store(const Prologue<N, EPB, NT> &R, MixedLds<N> *L) {
+__device__ __forceinline__ void prologue_store(const Prologue<N, EPB, NT> &R, MixedEl<N> *L) {
     using Sh = Shape<N, EPB, NT>;
     constexpr int NP = Sh::NP;
 #pragma unroll
@@ -304,12 +353,12 @@ __device__ __forceinline__ void prologue_store(const Prologue<N, EPB, NT> &R, Mi
         const int el = it / NP, p = it % NP;
         for (int v = 0; v < 5; ++v) {
             const float hi = (float)R.P[k][v];
-            L[el].f[v][p] = hi;
-            L[el].plo[v][p] = (float)(R.P[k][v] - (double)hi);
+            L[el].at(v, p) = hi;
+            L[el].plo(v, p) = (float)(R.P[k][v] - (double)hi);
         }
-        L[el].f[F_R0][p] = R.bg[k][0];
-        L[el].f[F_E0][p] = R.bg[k][1];
-        for (int c = 0; c < 3; ++c) L[el].g[3 * F_R0 + c][p] = R.gb[k][c];
+        L[el].at(F_R0, p) = R.bg[k][0];
+        L[el].at(F_E0, p) = R.bg[k][1];
+        for (int c = 0; c < 3; ++c) L[el].at(MixedEl<N>::GR + 3 * F_R0 + c, p) = R.gb[k][c];
     }
     if ((int)threadIdx.x < EPB * 6) {
         L[threadIdx.x / 6].lk[threadIdx.x % 6] = R.lk;
@@ -361,7 +410,7 @@ __device__ __forceinline__ void common_value(const float pv[5], float r0, int32_
 // given: the face-flux phase reuses them
 template <int N, int EPB, int NT>
 __device__ __forceinline__ void common_values(const OpsF<N> &op, const GeoF &G, const PhysF &F, int64_t e0,
-                                              MixedLds<N> *L, const Prologue<N, EPB, NT> &R,
+                                              MixedEl<N> *L, const Prologue<N, EPB, NT> &R,
                                               float (*fo)[NFIELD], const float (*Sf)[3]) {
     using Sh = Shape<N, EPB, NT>;
     constexpr int NF2 = N * N, NFL = (N + 1) * N * N;
@@ -372,26 +421,21 @@ __device__ __forceinline__ void common_values(const OpsF<N> &op, const GeoF &G, 
         const int el = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
         const int64_t e = e0 + el;
         if (e >= G.E) continue;
-        MixedLds<N> &l = L[el];
+        MixedEl<N> &l = L[el];
         const int t1 = pp % N, t2 = pp / N;
         const int d = f >> 1, m = (f & 1) ? N : 0, base = sol_of<N>(d, 0, t1, t2), st = stride_of<N>(d);
-        float pv[5];
-        for (int v = 0; v < 5; ++v) pv[v] = line_val<N>(op, l.f[v], m, base, st);
-        const float r0 = line_val<N>(op, l.f[F_R0], m, base, st), E0 = line_val<N>(op, l.f[F_E0], m, base, st);
-        if (fo) {
-            for (int v = 0; v < 5; ++v) fo[k][v] = pv[v];
-            fo[k][F_R0] = r0;
-            fo[k][F_E0] = E0;
-        }
+        float x[8];
+        l.template line<0, 2>(op, m, base, st, x);
+        for (int v = 0; v < NFIELD; ++v) fo[k][v] = x[v];
         const int32_t nb = l.lk[f], inf = l.inf[f];
-        common_value(pv, r0, nb, inf, R.nq[k], Sf[k], F, [&](int v, float x) { l.u.cs[v][f][pp] = x; });
+        common_value(x, x[F_R0], nb, inf, R.nq[k], Sf[k], F, [&](int v, float x) { l.u.cs[v][f][pp] = x; });
     }
 }
 
 // gradients of the 5 perturbation fields at the solution points (those of
 // the background are loaded)
 template <int N, int EPB, int NT>
-__device__ __forceinline__ void gradients(const OpsF<N> &op, const GeoF &G, int64_t e0, MixedLds<N> *L,
+__device__ __forceinline__ void gradients(const OpsF<N> &op, const GeoF &G, int64_t e0, MixedEl<N> *L,
                                           const float (*gsol)[9]) {
     using Sh = Shape<N, EPB, NT>;
     constexpr int NP = N * N * N;
@@ -402,7 +446,7 @@ __device__ __forceinline__ void gradients(const OpsF<N> &op, const GeoF &G, int6
         const int el = it / NP, p = it % NP;
         const int64_t e = e0 + el;
         if (e >= G.E) continue;
-        MixedLds<N> &l = L[el];
+        MixedEl<N> &l = L[el];
         const float *Gm = gsol[k];
         float dq[3][5];
 #pragma unroll
@@ -411,18 +455,19 @@ __device__ __forceinline__ void gradients(const OpsF<N> &op, const GeoF &G, int6
             split_sol<N>(d, p, a, t1, t2);
             const int base = sol_of<N>(d, 0, t1, t2), st = stride_of<N>(d), pp = t1 + N * t2;
 #pragma unroll
-            for (int v = 0; v < 5; ++v) {
-                float s = op.D[a][0] * l.u.cs[v][2 * d][pp] + op.D[a][N] * l.u.cs[v][2 * d + 1][pp];
+            for (int v = 0; v < 5; ++v)
+                dq[d][v] = op.D[a][0] * l.u.cs[v][2 * d][pp] + op.D[a][N] * l.u.cs[v][2 * d + 1][pp];
 #pragma unroll
-                for (int b = 0; b < N; ++b) s += op.B[a][b] * l.f[v][base + b * st];
-                dq[d][v] = s;
+            for (int b = 0; b < N; ++b) {
+                l.add_quad(op.B[a][b], base + b * st, 0, dq[d]);
+                dq[d][4] += op.B[a][b] * l.at(F_EP, base + b * st);
             }
         }
 #pragma unroll
         for (int v = 0; v < 5; ++v)
 #pragma unroll
             for (int c = 0; c < 3; ++c)
-                l.g[3 * v + c][p] = Gm[c] * dq[0][v] + Gm[3 + c] * dq[1][v] + Gm[6 + c] * dq[2][v];
+                l.at(MixedEl<N>::GR + 3 * v + c, p) = Gm[c] * dq[0][v] + Gm[3 + c] * dq[1][v] + Gm[6 + c] * dq[2][v];
     }
 }
 
@@ -466,6 +511,33 @@ __device__ __forceinline__ void state_at(const OpsF<N> &op, const LDS &l, int m,
         s.gm[2][c] = I(l.g[3 * F_MZ + c]);
         s.gEp[c] = I(l.g[3 * F_EP + c]);
         s.gr0[c] = I(l.g[3 * F_R0 + c]);
+    }
+}
+
+// the same from the element of k_flux_mixed
+template <int N>
+__device__ __forceinline__ void state_at(const OpsF<N> &op, const MixedEl<N> &l, int m, int base, int st, PtState &s,
+                                         const float *vals = nullptr) {
+    constexpr int NG = MixedEl<N>::SLOTS / 4 - 2;
+    float v[8], g[4 * NG];
+    if (!vals) l.template line<0, 2>(op, m, base, st, v);
+    const float *x = vals ? vals : v;
+    s.rp = x[F_RP];
+    s.m[0] = x[F_MX];
+    s.m[1] = x[F_MY];
+    s.m[2] = x[F_MZ];
+    s.Ep = x[F_EP];
+    s.r0 = x[F_R0];
+    s.E0 = x[F_E0];
+    l.template line<2, 2 + NG>(op, m, base, st, g);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        s.grp[c] = g[3 * F_RP + c];
+        s.gm[0][c] = g[3 * F_MX + c];
+        s.gm[1][c] = g[3 * F_MY + c];
+        s.gm[2][c] = g[3 * F_MZ + c];
+        s.gEp[c] = g[3 * F_EP + c];
+        s.gr0[c] = g[3 * F_R0 + c];
     }
 }
 
@@ -582,12 +654,12 @@ using MixedStage = MixedStageArgs;
 // Pout = c0 A + c1 (P + c2 Rp) (and Tout likewise), or Pout = Rp in
 // residual mode; the lift pass adds the missing part in place.
 template <int N, int EPB, int NT, int MINW, int KR>
-__global__ __launch_bounds__(NT, MINW) void k_flux_mixed(OpsF<N> opa, GeoF G, MixedBufs B, PhysParams P,
+__global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_flux_mixed(OpsF<N> opa, GeoF G, MixedBufs B, PhysParams P,
                                                          const double *__restrict__ Pq, const float *__restrict__ TQ,
                                                          float *__restrict__ TV, MixedStage S_) {
     using Sh = Shape<N, EPB, NT>;
     constexpr int NP = Sh::NP, NF2 = Sh::NF2, NFL = Sh::NFL, NINTD = Sh::NINTD;
-    __shared__ MixedLds<N> L[EPB];
+    __shared__ MixedEl<N> L[EPB];
     __shared__ OpsF<N> op;  // 1D operators (indexed per lane: LDS, not the argument segment)
     const int64_t e0 = (int64_t)blockIdx.x * EPB;
     const PhysF F = physf_of(P);
@@ -682,14 +754,14 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed(OpsF<N> opa, GeoF G, Mi
             const int el = it / NINTD, q = it % NINTD;
             const int m = 1 + q % (N - 1), tt = q / (N - 1), t1 = tt % N, t2 = tt / N;
             if (e0 + el >= G.E) continue;
-            MixedLds<N> &l = L[el];
+            MixedEl<N> &l = L[el];
             PtState s;
             state_at<N>(op, l, m, sol_of<N>(d, 0, t1, t2), stride_of<N>(d), s);
             float fi[5], fv[5];
             dflux_inviscid(s, Si[d][k], F, fi);
             dflux_viscous<KR>(s, Si[d][k], gSi[d][k], F, kr_of<KR>(F, kri[d][k]), 0, fv);
             const int fl = m + (N + 1) * tt;
-            for (int v = 0; v < 5; ++v) l.u.ft[0][v][fl] = fi[v] - fv[v];
+            for (int v = 0; v < 5; ++v) l.u.ft[v][fl] = fi[v] - fv[v];
         }
 #pragma unroll
         for (int k = 0; k < Sh::IT_FACE; ++k) {
@@ -697,11 +769,11 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed(OpsF<N> opa, GeoF G, Mi
             if (it >= EPB * 6 * NF2) break;
             const int el = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
             if ((f >> 1) != d || e0 + el >= G.E) continue;
-            MixedLds<N> &l = L[el];
+            MixedEl<N> &l = L[el];
             const int m = (f & 1) ? N : 0;
             const float sg = (f & 1) ? 1.0f : -1.0f;
             const int fl = m + (N + 1) * pp;
-            for (int v = 0; v < 5; ++v) l.u.ft[0][v][fl] = sg * ffc[k][v];
+            for (int v = 0; v < 5; ++v) l.u.ft[v][fl] = sg * ffc[k][v];
         }
         __syncthreads();
         if (d == 2) {
@@ -726,7 +798,7 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed(OpsF<N> opa, GeoF G, Mi
             if (it >= EPB * NP) break;
             const int el = it / NP, p = it % NP;
             if (e0 + el >= G.E) continue;
-            const MixedLds<N> &l = L[el];
+            const MixedEl<N> &l = L[el];
             int a, t1, t2;
             split_sol<N>(d, p, a, t1, t2);
             const int fb = (N + 1) * (t1 + N * t2);
@@ -734,7 +806,7 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed(OpsF<N> opa, GeoF G, Mi
             for (int v = 0; v < 5; ++v) {
                 float sum = 0.0f;
 #pragma unroll
-                for (int mm = 0; mm <= N; ++mm) sum += op.D[a][mm] * l.u.ft[0][v][fb + mm];
+                for (int mm = 0; mm <= N; ++mm) sum += op.D[a][mm] * l.u.ft[v][fb + mm];
                 div[k][v] += sum;
             }
         }
@@ -748,10 +820,10 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed(OpsF<N> opa, GeoF G, Mi
         if (it >= EPB * NP) break;
         const int el = it / NP, p = it % NP;
         if (el > elmax) continue;
-        const MixedLds<N> &l = L[el];
+        MixedEl<N> &l = L[el];
         const float iJ = gq[k][0];
         const float g0 = F.GM * gq[k][1], g1 = F.GM * gq[k][2], g2 = F.GM * gq[k][3];
-        const float rp = l.f[F_RP][p], mx = l.f[F_MX][p], my = l.f[F_MY][p], mz = l.f[F_MZ][p];
+        const float rp = l.at(F_RP, p), mx = l.at(F_MX, p), my = l.at(F_MY, p), mz = l.at(F_MZ, p);
         float M[5];
         M[0] = 0.0f;
         M[1] = rp * g0 - 2.0f * F.om * my;
@@ -768,7 +840,7 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed(OpsF<N> opa, GeoF G, Mi
             }
             // the stage input from its FP32 value and FP32 remainder (48
             // significant bits: 2^-48 relative, far below the FP32 residual)
-            const double pin = (double)l.f[v][p] + (double)l.plo[v][p];
+            const double pin = (double)l.at(v, p) + (double)l.plo(v, p);
             if (useT) st_off(S_.Tout + vb, o, S_.d0 * pb[k][v] + S_.d1 * (pin + S_.d2 * Rv));
             st_off(S_.Pout + vb, o, S_.c0 * pst[k][v] + S_.c1 * (pin + S_.c2 * Rv));
         }
@@ -932,7 +1004,7 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed_wide(OpsF<N> opa, GeoF 
                                                               MixedStage S_) {
     using W = WideM<N, NT>;
     constexpr int NP = W::NP, NF2 = W::NF2, NFL = W::NFL;
-    __shared__ MixedLds<N, 3> L;
+    __shared__ MixedLds<N> L;
     __shared__ OpsF<N> op;
     const int64_t e = blockIdx.x, E = G.E;
     const int t = threadIdx.x;
@@ -1268,7 +1340,10 @@ template <> struct CfgM<2> { static constexpr int EPB = 8, NT = 64, MINW = 2; };
 template <> struct CfgM<3> { static constexpr int EPB = 2, NT = 64, MINW = 3; };
 template <> struct CfgM<4> { static constexpr int EPB = 1, NT = 64, MINW = 4; };
 template <> struct CfgM<5> { static constexpr int EPB = 1, NT = 128, MINW = 2; };
-template <> struct CfgM<6> { static constexpr int EPB = 1, NT = 256, MINW = 1; };
+// (order 6: four waves, 830 against 945 us per step with the three that 130
+// registers leave; three with the radial diffusivity, which would spill: 974
+// against 1,052)
+template <> struct CfgM<6> { static constexpr int EPB = 1, NT = 256, MINW = 4; };
 // flux pass (elements per block, threads, minimum waves per SIMD) and lift
 // pass (elements per block, threads)
 template <int N> struct CfgF { static constexpr int EPB = CfgM<N>::EPB, NT = CfgM<N>::NT, MINW = CfgM<N>::MINW; };
@@ -1283,18 +1358,18 @@ template <int N> struct CfgL { static constexpr int EPB = CfgM<N>::EPB, NT = Cfg
 //            60.9 / 59.9 at 7,776, 72.7 / 80.6 at 12,288
 //   order 3: 45.9 / 29.3 at 288, 62.9 / 58.6 at 2,304, 70.7 / 83.0 at 3,600;
 //            lift alone 53.9 / 53.1 at 1,536, 62.9 / 63.8 at 2,304
-//   order 4: 45.8 / 31.6 / 36.4 at 288, 51.0 / 43.0 / 42.1 at 648, 60.5 / 61.0
-//            / 50.9 at 1,080, 63.8 / 78.0 / 60.7 at 1,536, 79.8 / - / 80.1 at
-//            2,304; lift alone 63.8 / 60.6 at 1,536, 79.8 / 79.6 at 2,304
-//   order 5: 52.9 / 33.0 / 42.3 at 162, 58.6 / 49.8 / 48.6 at 288, 68.7 / 73.1
-//            / 63.7 at 648, 85.5 / - / 89.7 at 1,080; lift alone 58.6 / 55.2 at
-//            288, 68.7 / 69.2 at 648
-//   order 6: 51.8 / 43.2 at 162, 67.0 / 74.9 at 288
+//   order 4: 45.8 / 31.6 / 36.4 at 288, 51.0 / 43.0 / 42.1 at 648; flux alone
+//            53.8 / - / 49.2 at 1,080, 60.3 / - / 63.2 at 1,536; lift alone
+//            63.8 / 60.6 at 1,536, 79.8 / 79.6 at 2,304
+//   order 5: 52.9 / 33.0 / 42.3 at 162; flux alone 51.2 / 49.8 / 46.9 at 288,
+//            63.0 / - / 65.4 at 648; lift alone 58.6 / 55.2 at 288, 68.7 / 69.2
+//            at 648
+//   order 6: 45.3 / 42.5 at 162, 61.2 / 72.6 at 288
 template <int N> struct CfgW;
 template <> struct CfgW<2> { static constexpr int NT1 = 64, W1 = 1, MAX1 = 20, NT2 = 64, W2 = 1, MAX2 = 0, LIFT = 28; };
 template <> struct CfgW<3> { static constexpr int NT1 = 192, W1 = 1, MAX1 = 9, NT2 = 192, W2 = 1, MAX2 = 0, LIFT = 6; };
-template <> struct CfgW<4> { static constexpr int NT1 = 320, W1 = 4, MAX1 = 2, NT2 = 192, W2 = 4, MAX2 = 6, LIFT = 6; };
-template <> struct CfgW<5> { static constexpr int NT1 = 640, W1 = 3, MAX1 = 1, NT2 = 256, W2 = 4, MAX2 = 3, LIFT = 2; };
+template <> struct CfgW<4> { static constexpr int NT1 = 320, W1 = 4, MAX1 = 2, NT2 = 192, W2 = 4, MAX2 = 5, LIFT = 6; };
+template <> struct CfgW<5> { static constexpr int NT1 = 640, W1 = 3, MAX1 = 1, NT2 = 256, W2 = 4, MAX2 = 2, LIFT = 2; };
 template <> struct CfgW<6> { static constexpr int NT1 = 832, W1 = 4, MAX1 = 1, NT2 = 832, W2 = 4, MAX2 = 0, LIFT = 1; };
 
 static GeoF geof_of(const GeoM &g) {
