@@ -1119,7 +1119,8 @@ __global__ __launch_bounds__(NT) void k_lift64(Ops<N> opa, Geo G, const double *
 // directions and the faces at once; the fluxes of the three directions are
 // held in LDS together), so a phase is one round and the chain of a block is
 // a third as long: flux and lift pass of the 288-hex order-3 shell 12.7 + 4.8
-// -> 7.4 + 4.0 us, ten SSP-RK3 steps 531 -> 326 us.  The price is in the
+// -> 7.4 + 4.0 us, ten SSP-RK3 steps 531 -> 326 us; 316 us with the records of
+// the element pass for the state and gradients.  The price is in the
 // larger meshes: fewer elements in flight per CU and the solution-point
 // metrics read by five threads instead of one.  The sums run over the same
 // terms in the same order.
@@ -1142,13 +1143,14 @@ __global__ __launch_bounds__(Wide<N>::NT, 4) void k_flux64_wide(Ops<N> opa, Geo 
     using W = Wide<N>;
     static_assert(W::NFACE <= W::NT && W::FP + W::NINT <= W::NT, "one flux point per thread");
     constexpr int NP = W::NP, NF2 = W::NF2, NFL = W::NFL, NT = W::NT;
-    __shared__ double sq[5][NP], sgr[15][NP];
+    constexpr int SR = 22;
+    __shared__ alignas(16) double rec[NP][SR];
     __shared__ union {
         double sqs[6][5][NF2];
         double sft[3][5][NFL];  // written after the common solution is consumed
     } U;
     __shared__ int32_t lk[6], inf[6];
-    __shared__ Ops<N> op;
+    __shared__ alignas(16) Ops<N> op;
     const int64_t e = blockIdx.x, E = G.E;
     const int t = threadIdx.x;
     // this thread's flux point: face point (f, pp) or interior point (d, m, tt)
@@ -1180,12 +1182,12 @@ __global__ __launch_bounds__(Wide<N>::NT, 4) void k_flux64_wide(Ops<N> opa, Geo 
 #pragma unroll
     for (int k = 0; k < W::IT_VP; ++k) {
         const int it = t + k * NT;
-        if (it < 5 * NP) sq[it / NP][lds_sol<N>(it % NP)] = qv[k];
+        if (it < 5 * NP) rec[it % NP][it / NP] = qv[k];
     }
     __syncthreads();
     if (isf) {
         double qs[5];
-        common_point64<N>(op, Planes<N>{sq, sgr}, f, pp, lk[f], inf[f], nq, S, P, qs);
+        common_point64<N>(op, Records<N, SR>{rec}, f, pp, lk[f], inf[f], nq, S, P, qs);
         for (int v = 0; v < 5; ++v) U.sqs[f][v][pp] = qs[v];
     }
     __syncthreads();
@@ -1203,23 +1205,23 @@ __global__ __launch_bounds__(Wide<N>::NT, 4) void k_flux64_wide(Ops<N> opa, Geo 
             const int base = sol_of<N>(dir, 0, t1, t2), st = stride_of<N>(dir), q = t1 + N * t2;
             double s = op.D[a][0] * U.sqs[2 * dir][v][q] + op.D[a][N] * U.sqs[2 * dir + 1][v][q];
 #pragma unroll
-            for (int b = 0; b < N; ++b) s += op.B[a][b] * sq[v][lds_line<N>(base, b, st)];
+            for (int b = 0; b < N; ++b) s += op.B[a][b] * rec[base + b * st][v];
             dd[dir] = s;
         }
 #pragma unroll
         for (int c = 0; c < 3; ++c)
-            sgr[v * 3 + c][lds_sol<N>(p)] = Gm[k][c] * dd[0] + Gm[k][3 + c] * dd[1] + Gm[k][6 + c] * dd[2];
+            rec[p][5 + v * 3 + c] = Gm[k][c] * dd[0] + Gm[k][3 + c] * dd[1] + Gm[k][6 + c] * dd[2];
     }
     __syncthreads();
     // every flux point of the element at once
     const double kr = RAD ? kappa_r_at(P, rl) : P.kappa_r;
     if (isf) {
         double ffc[5];
-        face_point64<N, false>(op, Planes<N>{sq, sgr}, nullptr, f, pp, lk[f], inf[f], nq, S, P, kr, TV, ffc);
+        face_point64<N, false>(op, Records<N, SR>{rec}, nullptr, f, pp, lk[f], inf[f], nq, S, P, kr, TV, ffc);
         for (int v = 0; v < 5; ++v) U.sft[d][v][fl] = sg * ffc[v];
     } else if (isi) {
         double fi[5];
-        interior_point64<N, false>(op, Planes<N>{sq, sgr}, nullptr, d, m, tt, S, P, kr, fi);
+        interior_point64<N, false>(op, Records<N, SR>{rec}, nullptr, d, m, tt, S, P, kr, fi);
         for (int v = 0; v < 5; ++v) U.sft[d][v][fl] = fi[v];
     }
     __syncthreads();
@@ -1240,7 +1242,7 @@ __global__ __launch_bounds__(Wide<N>::NT, 4) void k_flux64_wide(Ops<N> opa, Geo 
     for (int k = 0; k < W::IT_VP; ++k) {
         const int it = t + k * NT;
         if (it >= 5 * NP) break;
-        const int v = it / NP, p = it % NP, ps = lds_sol<N>(p);
+        const int v = it / NP, p = it % NP;
         double div = 0.0;
 #pragma unroll
         for (int dir = 0; dir < 3; ++dir) {
@@ -1253,13 +1255,13 @@ __global__ __launch_bounds__(Wide<N>::NT, 4) void k_flux64_wide(Ops<N> opa, Geo 
             div += s;
         }
         const double g[3] = {P.GM * gq[k][1], P.GM * gq[k][2], P.GM * gq[k][3]};
-        const double R = -div * gq[k][0] - source64(v, sq[0][ps], sq[1][ps], sq[2][ps], sq[3][ps], g, P.omega);
+        const double R = -div * gq[k][0] - source64(v, rec[p][0], rec[p][1], rec[p][2], rec[p][3], g, P.omega);
         const int64_t gi = ((int64_t)v * E + e) * NP + p;
         if (!rk) {
             S_.Qout[gi] = R;
             continue;
         }
-        const double q = sq[v][ps];
+        const double q = rec[p][v];
         if (useT) S_.Tout[gi] = S_.d0 * bv[k] + S_.d1 * (q + S_.d2 * R);
         S_.Qout[gi] = S_.c0 * av[k] + S_.c1 * (q + S_.c2 * R);
     }
@@ -1572,10 +1574,10 @@ static hipError_t launch_trace_t(const Mesh &m, const Geo &G, const double *Q, d
 // Largest meshes, in elements per CU (256), that run the wide passes: where
 // an SSP-RK3 step of a shell was no slower with them (us per step, element
 // passes / wide passes; the flux pass of order 4 is k_flux64_n4):
-//   flux  order 2: 62.2 / 56.2 at 3,600 hexes, 67.0 / 69.0 at 5,184
-//         order 3: 52.2 / 36.2 at 288, 77.8 / 74.6 at 2,304, 89.0 / 96.3 at 3,600
-//         order 4: 38.8 / 35.1 at 162, 40.8 / 44.7 at 288
-//         order 5: 56.7 / 45.7 at 162, 68.7 / 69.5 at 288
+//   flux  order 2: 56.8 / 50.3 at 3,600 hexes, 62.1 / 62.6 at 5,184
+//         order 3: 45.6 / 31.6 at 288, 72.0 / 67.0 at 2,304, 84.0 / 92.2 at 3,600
+//         order 4: 35.0 / 30.4 at 162, 36.1 / 39.1 at 288
+//         order 5: 49.3 / 39.2 at 162, 61.5 / 59.8 at 288, 80.0 / 88.1 at 648
 //         order 6: 59.4 / 59.4 at 162, 82.2 / 101.6 at 288 (not used)
 //   lift and trace push
 //         order 2: 74.1 / 70.3 at 7,776, 95.0 / 99.4 at 12,288
@@ -1585,7 +1587,7 @@ static hipError_t launch_trace_t(const Mesh &m, const Geo &G, const double *Q, d
 //         order 6: 111.7 / 109.2 at 648, 168.8 / 167.8 at 1,080
 template <int N>
 static bool wide_flux64(const Mesh &m) {
-    constexpr int per_cu = N == 2 ? 16 : N == 3 ? 8 : N == 6 ? 0 : 1;
+    constexpr int per_cu = N == 2 ? 16 : N == 3 ? 9 : N == 6 ? 0 : 1;
     return m.E <= 256 * per_cu;
 }
 template <int N>
