@@ -195,38 +195,28 @@ __device__ __forceinline__ void dflux_viscous(const PtState &s, const float S[3]
 // ---------------------------------------------------------------------------
 // element phases (generic N; items per thread fixed at compile time)
 // ---------------------------------------------------------------------------
-// The element of k_flux_mixed_wide, whose threads each take one field: planes
-template <int N>
-struct MixedLds {
-    static constexpr int NP = N * N * N, NF2 = N * N, NFL = (N + 1) * N * N;
-    float f[NFIELD][NP];          // perturbation + background fields
-    float plo[5][NP];             // FP64 perturbation minus its FP32 value f[0..4] (stage update)
-    float g[NGRAD][NP];           // gradients
-    union {
-        float cs[5][6][NF2];       // common values of the perturbation
-        float ft[3][5][NFL];       // transformed fluxes, written after cs is consumed
-    } u;
-    int32_t lk[6], inf[6];        // neighbour element and info word per face
-};
-
-// The element of k_flux_mixed: the 7 field values (slots F_*), the gradients
-// (slot GR + 3 f + c) and the remainders (the other slots and plo34) of a
-// point in one record of 28 floats, read in quads (16 consecutive points lie
-// on distinct banks), or a plane per slot at order 4, where memory bounds the
-// pass and the quads cost registers.  us per RK3 step, planes -> records
-// (hexes of the mesh): N = 3 (98,304) 1,080 -> 1,076; N = 4 (41,472)
-// 802 -> 829; N = 5 (24,000) 1,070 -> 1,002; N = 6 (12,288) 954 -> 850 (with
-// the radial diffusivity 995 -> 974).
-template <int N>
+// The element of the flux passes: the 7 field values (slots F_*), the
+// gradients (slot GR + 3 f + c) and the remainders (the other slots and plo34)
+// of a point in one record of 28 floats (REC), read in quads (16 consecutive
+// points lie on distinct banks), or a plane per slot.  ND: directions whose
+// fluxes are held together.
+// k_flux_mixed takes records but at order 4, where memory bounds the pass and
+// the quads cost registers.  us per RK3 step, planes -> records (hexes of the
+// mesh): N = 3 (98,304) 1,080 -> 1,076; N = 4 (41,472) 802 -> 829; N = 5
+// (24,000) 1,070 -> 1,002; N = 6 (12,288) 954 -> 850 (with the radial
+// diffusivity 995 -> 974).  k_flux_mixed_wide, whose threads each take one
+// field between the flux points, takes planes but at order 2: N = 2 (288) 27.6
+// -> 27.3; N = 3 (1,536) 44.3 -> 47.3; N = 4 (648) 40.2 -> 41.4; N = 5 (288)
+// 46.3 -> 48.1; N = 6 (162) 43.0 -> 47.4.
+template <int N, int ND, bool REC>
 struct MixedEl {
     static constexpr int NP = N * N * N, NF2 = N * N, NFL = (N + 1) * N * N, GR = 8, SLOTS = 28;
-    static constexpr bool REC = N != 4;
     static_assert(GR + NGRAD + 2 == SLOTS, "slots of a point");
     alignas(16) float r[NP * SLOTS];
     float plo34[2][NP];           // remainders of F_MZ, F_EP
     union {
         float cs[5][6][NF2];       // common values of the perturbation
-        float ft[5][NFL];          // transformed fluxes, written after cs is consumed
+        float ft[ND][5][NFL];      // transformed fluxes, written after cs is consumed
     } u;
     int32_t lk[6], inf[6];        // neighbour element and info word per face
     __device__ __forceinline__ float &at(int slot, int p) { return r[REC ? p * SLOTS + slot : slot * NP + p]; }
@@ -257,6 +247,9 @@ struct MixedEl {
             for (int b = 0; b < N; ++b) add_quad(op.I[m][b], base + b * st, j, x + 4 * (j - J0));
     }
 };
+
+template <int N>
+using MixedElem = MixedEl<N, 1, N != 4>;  // of k_flux_mixed
 
 template <int N, int EPB, int NT>
 struct Shape {
@@ -343,7 +336,7 @@ __device__ __forceinline__ void prologue_load_metrics(const GeoF &G, int64_t e0,
 
 // move the prologue registers into the element LDS
 template <int N, int EPB, int NT>
-__device__ __forceinline__ void prologue_store(const Prologue<N, EPB, NT> &R, MixedEl<N> *L) {
+__device__ __forceinline__ void prologue_store(const Prologue<N, EPB, NT> &R, MixedElem<N> *L) {
     using Sh = Shape<N, EPB, NT>;
     constexpr int NP = Sh::NP;
 #pragma unroll
@@ -358,7 +351,7 @@ __device__ __forceinline__ void prologue_store(const Prologue<N, EPB, NT> &R, Mi
         }
         L[el].at(F_R0, p) = R.bg[k][0];
         L[el].at(F_E0, p) = R.bg[k][1];
-        for (int c = 0; c < 3; ++c) L[el].at(MixedEl<N>::GR + 3 * F_R0 + c, p) = R.gb[k][c];
+        for (int c = 0; c < 3; ++c) L[el].at(MixedElem<N>::GR + 3 * F_R0 + c, p) = R.gb[k][c];
     }
     if ((int)threadIdx.x < EPB * 6) {
         L[threadIdx.x / 6].lk[threadIdx.x % 6] = R.lk;
@@ -410,7 +403,7 @@ __device__ __forceinline__ void common_value(const float pv[5], float r0, int32_
 // given: the face-flux phase reuses them
 template <int N, int EPB, int NT>
 __device__ __forceinline__ void common_values(const OpsF<N> &op, const GeoF &G, const PhysF &F, int64_t e0,
-                                              MixedEl<N> *L, const Prologue<N, EPB, NT> &R,
+                                              MixedElem<N> *L, const Prologue<N, EPB, NT> &R,
                                               float (*fo)[NFIELD], const float (*Sf)[3]) {
     using Sh = Shape<N, EPB, NT>;
     constexpr int NF2 = N * N, NFL = (N + 1) * N * N;
@@ -421,7 +414,7 @@ __device__ __forceinline__ void common_values(const OpsF<N> &op, const GeoF &G, 
         const int el = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
         const int64_t e = e0 + el;
         if (e >= G.E) continue;
-        MixedEl<N> &l = L[el];
+        MixedElem<N> &l = L[el];
         const int t1 = pp % N, t2 = pp / N;
         const int d = f >> 1, m = (f & 1) ? N : 0, base = sol_of<N>(d, 0, t1, t2), st = stride_of<N>(d);
         float x[8];
@@ -435,7 +428,7 @@ __device__ __forceinline__ void common_values(const OpsF<N> &op, const GeoF &G, 
 // gradients of the 5 perturbation fields at the solution points (those of
 // the background are loaded)
 template <int N, int EPB, int NT>
-__device__ __forceinline__ void gradients(const OpsF<N> &op, const GeoF &G, int64_t e0, MixedEl<N> *L,
+__device__ __forceinline__ void gradients(const OpsF<N> &op, const GeoF &G, int64_t e0, MixedElem<N> *L,
                                           const float (*gsol)[9]) {
     using Sh = Shape<N, EPB, NT>;
     constexpr int NP = N * N * N;
@@ -446,7 +439,7 @@ __device__ __forceinline__ void gradients(const OpsF<N> &op, const GeoF &G, int6
         const int el = it / NP, p = it % NP;
         const int64_t e = e0 + el;
         if (e >= G.E) continue;
-        MixedEl<N> &l = L[el];
+        MixedElem<N> &l = L[el];
         const float *Gm = gsol[k];
         float dq[3][5];
 #pragma unroll
@@ -467,58 +460,17 @@ __device__ __forceinline__ void gradients(const OpsF<N> &op, const GeoF &G, int6
         for (int v = 0; v < 5; ++v)
 #pragma unroll
             for (int c = 0; c < 3; ++c)
-                l.at(MixedEl<N>::GR + 3 * v + c, p) = Gm[c] * dq[0][v] + Gm[3 + c] * dq[1][v] + Gm[6 + c] * dq[2][v];
+                l.at(MixedElem<N>::GR + 3 * v + c, p) = Gm[c] * dq[0][v] + Gm[3 + c] * dq[1][v] + Gm[6 + c] * dq[2][v];
     }
 }
 
 // point state at the flux point m of the line (base, st); with vals given,
 // the 7 field values are taken from there and only the gradients are
 // interpolated
-template <int N, typename LDS>
-__device__ __forceinline__ void state_at(const OpsF<N> &op, const LDS &l, int m, int base, int st,
-                                         PtState &s, const float *vals = nullptr) {
-    float w[N];
-#pragma unroll
-    for (int b = 0; b < N; ++b) w[b] = op.I[m][b];
-    auto I = [&](const float *fld) {
-        float t = 0.0f;
-#pragma unroll
-        for (int b = 0; b < N; ++b) t += w[b] * fld[base + b * st];
-        return t;
-    };
-    if (vals) {
-        s.rp = vals[F_RP];
-        s.m[0] = vals[F_MX];
-        s.m[1] = vals[F_MY];
-        s.m[2] = vals[F_MZ];
-        s.Ep = vals[F_EP];
-        s.r0 = vals[F_R0];
-        s.E0 = vals[F_E0];
-    } else {
-        s.rp = I(l.f[F_RP]);
-        s.m[0] = I(l.f[F_MX]);
-        s.m[1] = I(l.f[F_MY]);
-        s.m[2] = I(l.f[F_MZ]);
-        s.Ep = I(l.f[F_EP]);
-        s.r0 = I(l.f[F_R0]);
-        s.E0 = I(l.f[F_E0]);
-    }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        s.grp[c] = I(l.g[3 * F_RP + c]);
-        s.gm[0][c] = I(l.g[3 * F_MX + c]);
-        s.gm[1][c] = I(l.g[3 * F_MY + c]);
-        s.gm[2][c] = I(l.g[3 * F_MZ + c]);
-        s.gEp[c] = I(l.g[3 * F_EP + c]);
-        s.gr0[c] = I(l.g[3 * F_R0 + c]);
-    }
-}
-
-// the same from the element of k_flux_mixed
-template <int N>
-__device__ __forceinline__ void state_at(const OpsF<N> &op, const MixedEl<N> &l, int m, int base, int st, PtState &s,
+template <int N, typename EL>
+__device__ __forceinline__ void state_at(const OpsF<N> &op, const EL &l, int m, int base, int st, PtState &s,
                                          const float *vals = nullptr) {
-    constexpr int NG = MixedEl<N>::SLOTS / 4 - 2;
+    constexpr int NG = EL::SLOTS / 4 - 2;
     float v[8], g[4 * NG];
     if (!vals) l.template line<0, 2>(op, m, base, st, v);
     const float *x = vals ? vals : v;
@@ -659,7 +611,7 @@ __global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_fl
                                                          float *__restrict__ TV, MixedStage S_) {
     using Sh = Shape<N, EPB, NT>;
     constexpr int NP = Sh::NP, NF2 = Sh::NF2, NFL = Sh::NFL, NINTD = Sh::NINTD;
-    __shared__ MixedEl<N> L[EPB];
+    __shared__ MixedElem<N> L[EPB];
     __shared__ OpsF<N> op;  // 1D operators (indexed per lane: LDS, not the argument segment)
     const int64_t e0 = (int64_t)blockIdx.x * EPB;
     const PhysF F = physf_of(P);
@@ -754,14 +706,14 @@ __global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_fl
             const int el = it / NINTD, q = it % NINTD;
             const int m = 1 + q % (N - 1), tt = q / (N - 1), t1 = tt % N, t2 = tt / N;
             if (e0 + el >= G.E) continue;
-            MixedEl<N> &l = L[el];
+            MixedElem<N> &l = L[el];
             PtState s;
             state_at<N>(op, l, m, sol_of<N>(d, 0, t1, t2), stride_of<N>(d), s);
             float fi[5], fv[5];
             dflux_inviscid(s, Si[d][k], F, fi);
             dflux_viscous<KR>(s, Si[d][k], gSi[d][k], F, kr_of<KR>(F, kri[d][k]), 0, fv);
             const int fl = m + (N + 1) * tt;
-            for (int v = 0; v < 5; ++v) l.u.ft[v][fl] = fi[v] - fv[v];
+            for (int v = 0; v < 5; ++v) l.u.ft[0][v][fl] = fi[v] - fv[v];
         }
 #pragma unroll
         for (int k = 0; k < Sh::IT_FACE; ++k) {
@@ -769,11 +721,11 @@ __global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_fl
             if (it >= EPB * 6 * NF2) break;
             const int el = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
             if ((f >> 1) != d || e0 + el >= G.E) continue;
-            MixedEl<N> &l = L[el];
+            MixedElem<N> &l = L[el];
             const int m = (f & 1) ? N : 0;
             const float sg = (f & 1) ? 1.0f : -1.0f;
             const int fl = m + (N + 1) * pp;
-            for (int v = 0; v < 5; ++v) l.u.ft[v][fl] = sg * ffc[k][v];
+            for (int v = 0; v < 5; ++v) l.u.ft[0][v][fl] = sg * ffc[k][v];
         }
         __syncthreads();
         if (d == 2) {
@@ -798,7 +750,7 @@ __global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_fl
             if (it >= EPB * NP) break;
             const int el = it / NP, p = it % NP;
             if (e0 + el >= G.E) continue;
-            const MixedEl<N> &l = L[el];
+            const MixedElem<N> &l = L[el];
             int a, t1, t2;
             split_sol<N>(d, p, a, t1, t2);
             const int fb = (N + 1) * (t1 + N * t2);
@@ -806,7 +758,7 @@ __global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_fl
             for (int v = 0; v < 5; ++v) {
                 float sum = 0.0f;
 #pragma unroll
-                for (int mm = 0; mm <= N; ++mm) sum += op.D[a][mm] * l.u.ft[v][fb + mm];
+                for (int mm = 0; mm <= N; ++mm) sum += op.D[a][mm] * l.u.ft[0][v][fb + mm];
                 div[k][v] += sum;
             }
         }
@@ -820,7 +772,7 @@ __global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_fl
         if (it >= EPB * NP) break;
         const int el = it / NP, p = it % NP;
         if (el > elmax) continue;
-        MixedEl<N> &l = L[el];
+        MixedElem<N> &l = L[el];
         const float iJ = gq[k][0];
         const float g0 = F.GM * gq[k][1], g1 = F.GM * gq[k][2], g2 = F.GM * gq[k][3];
         const float rp = l.at(F_RP, p), mx = l.at(F_MX, p), my = l.at(F_MY, p), mz = l.at(F_MZ, p);
@@ -1004,7 +956,8 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed_wide(OpsF<N> opa, GeoF 
                                                               MixedStage S_) {
     using W = WideM<N, NT>;
     constexpr int NP = W::NP, NF2 = W::NF2, NFL = W::NFL;
-    __shared__ MixedLds<N> L;
+    using EL = MixedEl<N, 3, N == 2>;
+    __shared__ EL L;
     __shared__ OpsF<N> op;
     const int64_t e = blockIdx.x, E = G.E;
     const int t = threadIdx.x;
@@ -1070,21 +1023,20 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed_wide(OpsF<N> opa, GeoF 
         if (it >= 5 * NP) break;
         const int v = it / NP, p = it % NP;
         const float hi = (float)pv[k];
-        L.f[v][p] = hi;
-        L.plo[v][p] = (float)(pv[k] - (double)hi);
-        if (v < 2) L.f[F_R0 + v][p] = bg[k];
-        else L.g[3 * F_R0 + v - 2][p] = bg[k];
+        L.at(v, p) = hi;
+        L.plo(v, p) = (float)(pv[k] - (double)hi);
+        L.at(v < 2 ? F_R0 + v : EL::GR + 3 * F_R0 + v - 2, p) = bg[k];
     }
     __syncthreads();
     // common values; the own face values of the 7 fields are kept
-    float fo[W::IT_FACE][NFIELD];
+    float fo[W::IT_FACE][8];
 #pragma unroll
     for (int k = 0; k < W::IT_FACE; ++k) {
         const int it = t + k * NT;
         if (it >= W::NFACE) break;
         const int f = it / NF2, pp = it % NF2, d = f >> 1, m = (f & 1) ? N : 0;
         const int base = sol_of<N>(d, 0, pp % N, pp / N), st = stride_of<N>(d);
-        for (int v = 0; v < NFIELD; ++v) fo[k][v] = line_val<N>(op, L.f[v], m, base, st);
+        L.template line<0, 2>(op, m, base, st, fo[k]);
         common_value(fo[k], fo[k][F_R0], L.lk[f], L.inf[f], nq[k], S[k], F,
                      [&](int v, float x) { L.u.cs[v][f][pp] = x; });
     }
@@ -1103,12 +1055,12 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed_wide(OpsF<N> opa, GeoF 
             const int base = sol_of<N>(d, 0, t1, t2), st = stride_of<N>(d), pp = t1 + N * t2;
             float s = op.D[a][0] * L.u.cs[v][2 * d][pp] + op.D[a][N] * L.u.cs[v][2 * d + 1][pp];
 #pragma unroll
-            for (int b = 0; b < N; ++b) s += op.B[a][b] * L.f[v][base + b * st];
+            for (int b = 0; b < N; ++b) s += op.B[a][b] * L.at(v, base + b * st);
             dq[d] = s;
         }
 #pragma unroll
         for (int c = 0; c < 3; ++c)
-            L.g[3 * v + c][p] = Gm[k][c] * dq[0] + Gm[k][3 + c] * dq[1] + Gm[k][6 + c] * dq[2];
+            L.at(EL::GR + 3 * v + c, p) = Gm[k][c] * dq[0] + Gm[k][3 + c] * dq[1] + Gm[k][6 + c] * dq[2];
     }
     __syncthreads();
     // every flux point of the element
@@ -1177,7 +1129,7 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed_wide(OpsF<N> opa, GeoF 
             div += s;
         }
         const float g0 = F.GM * gq[k][1], g1 = F.GM * gq[k][2], g2 = F.GM * gq[k][3];
-        const float rp = L.f[F_RP][p], mx = L.f[F_MX][p], my = L.f[F_MY][p], mz = L.f[F_MZ][p];
+        const float rp = L.at(F_RP, p), mx = L.at(F_MX, p), my = L.at(F_MY, p), mz = L.at(F_MZ, p);
         const float M = v == 1   ? rp * g0 - 2.0f * F.om * my
                         : v == 2 ? rp * g1 + 2.0f * F.om * mx
                         : v == 3 ? rp * g2
@@ -1190,7 +1142,7 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed_wide(OpsF<N> opa, GeoF 
             continue;
         }
         // the stage input from its FP32 value and remainder (as above)
-        const double pin = (double)L.f[v][p] + (double)L.plo[v][p];
+        const double pin = (double)L.at(v, p) + (double)L.plo(v, p);
         if (useT) S_.Tout[gi] = S_.d0 * pb[k] + S_.d1 * (pin + S_.d2 * Rv);
         S_.Pout[gi] = S_.c0 * pst[k] + S_.c1 * (pin + S_.c2 * Rv);
     }
@@ -1356,19 +1308,19 @@ template <int N> struct CfgL { static constexpr int EPB = CfgM<N>::EPB, NT = Cfg
 // passes / wide passes with NT1 [/ NT2] threads):
 //   order 2: 56.0 / 51.5 at 5,184 hexes, 60.9 / 64.0 at 7,776; lift alone
 //            60.9 / 59.9 at 7,776, 72.7 / 80.6 at 12,288
-//   order 3: 45.9 / 29.3 at 288, 62.9 / 58.6 at 2,304, 70.7 / 83.0 at 3,600;
-//            lift alone 53.9 / 53.1 at 1,536, 62.9 / 63.8 at 2,304
+//   order 3: flux alone 41.4 / 29.0 at 288, 60.5 / 57.7 at 2,304, 67.7 / 75.2
+//            at 3,600; lift alone 53.9 / 53.1 at 1,536, 62.9 / 63.8 at 2,304
 //   order 4: 45.8 / 31.6 / 36.4 at 288, 51.0 / 43.0 / 42.1 at 648; flux alone
-//            53.8 / - / 49.2 at 1,080, 60.3 / - / 63.2 at 1,536; lift alone
-//            63.8 / 60.6 at 1,536, 79.8 / 79.6 at 2,304
-//   order 5: 52.9 / 33.0 / 42.3 at 162; flux alone 51.2 / 49.8 / 46.9 at 288,
-//            63.0 / - / 65.4 at 648; lift alone 58.6 / 55.2 at 288, 68.7 / 69.2
+//            53.9 / - / 49.5 at 1,080, 60.8 / - / 58.8 at 1,536, 78.6 / - /
+//            81.4 at 2,304; lift alone 63.8 / 60.6 at 1,536, 79.8 / 79.6 at 2,304
+//   order 5: 52.9 / 33.0 / 42.3 at 162; flux alone 51.1 / 49.8 / 46.3 at 288,
+//            63.0 / - / 63.1 at 648; lift alone 58.6 / 55.2 at 288, 68.7 / 69.2
 //            at 648
-//   order 6: 45.3 / 42.5 at 162, 61.2 / 72.6 at 288
+//   order 6: 45.3 / 43.1 at 162, 60.7 / 73.5 at 288
 template <int N> struct CfgW;
 template <> struct CfgW<2> { static constexpr int NT1 = 64, W1 = 1, MAX1 = 20, NT2 = 64, W2 = 1, MAX2 = 0, LIFT = 28; };
 template <> struct CfgW<3> { static constexpr int NT1 = 192, W1 = 1, MAX1 = 9, NT2 = 192, W2 = 1, MAX2 = 0, LIFT = 6; };
-template <> struct CfgW<4> { static constexpr int NT1 = 320, W1 = 4, MAX1 = 2, NT2 = 192, W2 = 4, MAX2 = 5, LIFT = 6; };
+template <> struct CfgW<4> { static constexpr int NT1 = 320, W1 = 4, MAX1 = 2, NT2 = 192, W2 = 4, MAX2 = 6, LIFT = 6; };
 template <> struct CfgW<5> { static constexpr int NT1 = 640, W1 = 3, MAX1 = 1, NT2 = 256, W2 = 4, MAX2 = 2, LIFT = 2; };
 template <> struct CfgW<6> { static constexpr int NT1 = 832, W1 = 4, MAX1 = 1, NT2 = 832, W2 = 4, MAX2 = 0, LIFT = 1; };
 
