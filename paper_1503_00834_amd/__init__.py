@@ -352,7 +352,8 @@ def chorus_kernel_timing(enable):
 # kernel kinds of chorus_kernel_times: the face traces that start a call,
 # the first pass of a stage (FP64: flux pass k_flux64; mixed: flux pass
 # k_flux_mixed) and the second pass (FP64: lift pass k_lift64; mixed:
-# lift pass k_lift_mixed)
+# lift pass k_lift_mixed); the names stand for every form of a pass
+# (k_flux64_n4, k_..._wide)
 KERNEL_KINDS = ("trace", "pass1", "pass2")
 KERNEL_NAMES = {"fp64": {"trace": "k_trace_push", "pass1": "k_flux64", "pass2": "k_lift64"},
                 "mixed": {"trace": "k_pert_begin", "pass1": "k_flux_mixed", "pass2": "k_lift_mixed"}}

@@ -10,7 +10,10 @@
 //                 (pushed to the neighbours), fluxes at the interior flux
 //                 points, divergence, source, and the stage combination with
 //                 this partial residual
-//              (order 4: k_flux64_n4, the line operators as matrix products)
+//              (order 4: k_flux64_n4, the line operators as matrix products;
+//              meshes that leave most of the chip idle: k_flux64_wide, one
+//              element per block of several waves, and likewise
+//              k_lift64_wide and k_trace_push_wide)
 //   k_lift64   neighbours' viscous face fluxes -> the missing residual part
 //              added in place; face traces of the new state pushed to the
 //              neighbours for the next stage.
@@ -353,22 +356,6 @@ __device__ __forceinline__ double line_interp_s(const Ops<N> &op, const T *fld, 
     return t;
 }
 
-// An element's state and gradients in LDS, one plane per field: the values
-// at flux point m of the line (base, st).
-template <int N>
-struct Planes {
-    const double (*sq)[N * N * N], (*sgr)[N * N * N];
-    __device__ __forceinline__ void state(const Ops<N> &op, int m, int base, int st, double q[5]) const {
-        for (int v = 0; v < 5; ++v) q[v] = line_interp_s<N>(op, sq[v], m, base, st);
-    }
-    __device__ __forceinline__ void all(const Ops<N> &op, int m, int base, int st, double q[5], double g[5][3]) const {
-        for (int v = 0; v < 5; ++v) {
-            q[v] = line_interp_s<N>(op, sq[v], m, base, st);
-            for (int c = 0; c < 3; ++c) g[v][c] = line_interp_s<N>(op, sgr[v * 3 + c], m, base, st);
-        }
-    }
-};
-
 // five values of a record (pairs, 16-byte aligned) or of planes PL apart
 template <bool REC, int PL>
 __device__ __forceinline__ void load5(const double *r, double x[5]) {
@@ -380,8 +367,9 @@ __device__ __forceinline__ void load5(const double *r, double x[5]) {
     }
 }
 
-// The same with one record per point (5 state values, then 15 gradients):
-// a line is read as pairs of fields.
+// An element's state and gradients in LDS, one record per point (5 state
+// values, then 15 gradients): the values at flux point m of the line (base,
+// st), read as pairs of fields.
 template <int N, int SR>
 struct Records {
     const double (*r)[SR];
@@ -530,13 +518,12 @@ __device__ __forceinline__ double source64(int v, double rho, double mx, double 
 template <int N, int EPB, int NT, int PART, bool RAD>
 __global__ __launch_bounds__(NT, PART == 2 && RAD ? 3 : N == 5 && RAD ? 2 : Cfg64<N>::MINW)
 void k_flux64(Ops<N> opa, Geo G, PhysParams P, const double *__restrict__ Q,
-                                               const double *__restrict__ TQ, double *__restrict__ TV,
-                                               StageArgs S_, ClosureArgs C) {
+              const double *__restrict__ TQ, double *__restrict__ TV, StageArgs S_, ClosureArgs C) {
     constexpr bool CL = PART != 0;
     using Sh = Sh64<N, EPB, NT>;
     constexpr int NP = Sh::NP, NF2 = Sh::NF2, NFL = Sh::NFL, NINTD = Sh::NINTD;
-    constexpr int SR = Sh::SR;
-    __shared__ alignas(16) double rec[EPB][NP][SR];  // state, gradients at the solution points
+    constexpr int SR = PART == 1 ? 6 : Sh::SR;
+    __shared__ alignas(16) double rec[EPB][NP][SR];  // state, gradients (not in PART 1) at the solution points
     // the common solution is consumed by the gradients before the subgrid
     // flux (PART 2) and the first direction's fluxes are written
     __shared__ union {
@@ -688,8 +675,8 @@ void k_flux64(Ops<N> opa, Geo G, PhysParams P, const double *__restrict__ Q,
         const int el = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
         if (e0 + el >= E) continue;
         const double kr = RAD ? kappa_r_at(P, krf[k]) : krf[k];
-        face_point64<N, CL>(op, Records<N, SR>{rec[el]}, CL ? &stau[el][0][0] : nullptr, f, pp, lk[el][f], inf[el][f], nq[k],
-                            Sf[k], P, kr, TV, ffc[k]);
+        face_point64<N, CL>(op, Records<N, SR>{rec[el]}, CL ? &stau[el][0][0] : nullptr, f, pp, lk[el][f],
+                            inf[el][f], nq[k], Sf[k], P, kr, TV, ffc[k]);
     }
     // per direction: transformed flux at the d-flux points, its derivative
     // added to the divergence at the solution points

@@ -21,6 +21,11 @@
 //   * source:    M(P) (linear).
 // FP32 rounding therefore scales with the perturbation, and the hydrostatic
 // and isentropic cancellations of the background stay in FP64.
+//
+// k_flux_mixed and k_lift_mixed take one element (several at orders 2 and 3)
+// per block of one wave or a few; k_flux_mixed_wide and k_lift_mixed_wide
+// spread an element over a block of several waves for meshes that leave most
+// of the chip idle.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
