@@ -64,21 +64,23 @@ struct MixedBufs {
 };
 
 struct PhysF {
-    float gm1, gam, R, cp, icp, GM, om, nu, kappa, kappa_r, RT_top;  // RT_top <= 0: off
+    float gm1, gam, cp, icp, cpR, GM, om, nu, kappaR, kappa_r, RT_top;  // cpR = cp/R, kappaR = kappa/R; RT_top <= 0: off
     float kappa_r1, kappa_r2;                                    // kappa_r(r) = kappa_r + kappa_r1 r + kappa_r2 r^2
 };
 
-__device__ __forceinline__ PhysF physf_of(const PhysParams &P) {
+// (on the host: converted in the kernel it took 50 vector instructions per
+// wave, two FP64 divisions among them)
+static PhysF physf_of(const PhysParams &P) {
     PhysF f;
     f.gm1 = (float)(P.gamma - 1.0);
     f.gam = (float)P.gamma;
-    f.R = (float)P.R_gas;
     f.cp = (float)P.cp;
     f.icp = (float)(1.0 / P.cp);
+    f.cpR = (float)(P.cp / P.R_gas);
     f.GM = (float)P.GM;
     f.om = (float)P.omega;
     f.nu = (float)P.nu;
-    f.kappa = (float)P.kappa;
+    f.kappaR = (float)(P.kappa / P.R_gas);
     f.kappa_r = (float)P.kappa_r;
     f.RT_top = (P.T_top > 0.0) ? (float)(P.R_gas * P.T_top) : -1.0f;
     f.kappa_r1 = (float)P.kappa_r1;
@@ -147,7 +149,7 @@ __device__ __forceinline__ void dflux_viscous(const PtState &s, const float S[3]
     const float gr0S = s.gr0[0] * S[0] + s.gr0[1] * S[1] + s.gr0[2] * S[2];
     const float grpS = s.grp[0] * S[0] + s.grp[1] * S[1] + s.grp[2] * S[2];
     const float grhoS = gr0S + grpS;
-    const float uS = u[0] * S[0] + u[1] * S[1] + u[2] * S[2];
+    const float uS = (s.m[0] * S[0] + s.m[1] * S[1] + s.m[2] * S[2]) * inv;
     const float ug = u[0] * grho[0] + u[1] * grho[1] + u[2] * grho[2];
     float Y[3];
     for (int a = 0; a < 3; ++a) Y[a] = s.gm[a][0] * S[0] + s.gm[a][1] * S[1] + s.gm[a][2] * S[2];
@@ -175,23 +177,22 @@ __device__ __forceinline__ void dflux_viscous(const PtState &s, const float S[3]
         return;
     }
     // p' and grad p' . S (m0 = 0, u0 = 0)
-    const float uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-    const float pp = F.gm1 * (s.Ep - 0.5f * uu * rho);
+    const float mm = s.m[0] * s.m[0] + s.m[1] * s.m[1] + s.m[2] * s.m[2], ke = 0.5f * mm * inv;
+    const float pp = F.gm1 * (s.Ep - ke);
     const float p0 = F.gm1 * s.E0, p = p0 + pp;
     const float gEpS = s.gEp[0] * S[0] + s.gEp[1] * S[1] + s.gEp[2] * S[2];
-    const float gpS = F.gm1 * (gEpS - (u[0] * Y[0] + u[1] * Y[1] + u[2] * Y[2]) + 0.5f * uu * grhoS);
+    const float gpS = F.gm1 * (gEpS - (u[0] * Y[0] + u[1] * Y[1] + u[2] * Y[2]) + ke * inv * grhoS);
     // (grad S - grad S0).S / c_p with grad p0 . S / p0 = gamma (gS0S / c_p
     // + grad rho0 . S / rho0), the background entropy gradient's definition
     const float igp = rcp(F.gam * p), ir0 = rcp(s.r0);
     const float dgS = igp * (gpS - F.gam * pp * (gS0S * F.icp + gr0S * ir0)) - inv * (grpS - gr0S * s.rp * ir0);
     // rho T grad S . S - rho0 T0 grad S0 . S = (p' gS0S + p c_p dgS) / R
-    const float iR = rcp(F.R);
-    const float eS = F.kappa * (pp * gS0S + p * F.cp * dgS) * iR;
+    const float eS = F.kappaR * (pp * gS0S + p * F.cp * dgS);
     // rho c_p grad T . S difference: c_p/R (grad p' . S - [p grad rho' . S / rho + grad rho0 . S (p/rho - p0/rho0)])
     float eT = 0.0f;
     if constexpr (KR != KR_NONE) {
         const float dpr = (pp * s.r0 - p0 * s.rp) * inv * ir0;
-        eT = kr * F.cp * iR * (gpS - (p * grpS * inv + gr0S * dpr));
+        eT = kr * F.cpR * (gpS - (p * grpS * inv + gr0S * dpr));
     }
     const float work = (wall == 0) ? (u[0] * tS[0] + u[1] * tS[1] + u[2] * tS[2]) : 0.0f;
     out[4] = work + eS + eT;
@@ -274,6 +275,21 @@ struct Shape {
 // count) load element 0's data through a clamped index: no load is
 // predicated (a guarded load compiles to a branch that waits for it at
 // once) and those items are never stored.
+//
+// Every address is a block-uniform base (scalar registers) plus a 32-bit
+// lane offset in bytes plus a constant: one vector register serves all the
+// loads of an array, where 64-bit lane addresses took a vector add each.
+template <typename T>
+__device__ __forceinline__ T ld_at(const T *base, uint32_t bytes, int c = 0) {
+    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + bytes + c * (int)sizeof(T));
+}
+// element of item it (of n per element) within the block, clamped to the last
+// element (elmax)
+template <int EPB>
+__device__ __forceinline__ uint32_t el_of(int it, int n, int elmax) {
+    return EPB == 1 ? 0 : min(it / n, elmax);
+}
+
 template <int N, int EPB, int NT>
 struct Prologue {
     using Sh = Shape<N, EPB, NT>;
@@ -289,7 +305,8 @@ struct Prologue {
 
 template <int N, int EPB, int NT>
 __device__ __forceinline__ void prologue_load(const double *Pq, const MixedBufs &B, const GeoF &G,
-                                              const float *__restrict__ TQ, int64_t e0, Prologue<N, EPB, NT> &R) {
+                                              const float *__restrict__ TQ, int64_t e0, int elmax,
+                                              Prologue<N, EPB, NT> &R) {
     using Sh = Shape<N, EPB, NT>;
     constexpr int NP = Sh::NP, NF2 = Sh::NF2;
     const int64_t E = G.E;
@@ -299,43 +316,39 @@ __device__ __forceinline__ void prologue_load(const double *Pq, const MixedBufs 
     {
         const int it = threadIdx.x;
         const bool okl = it < EPB * 6 && e0 + it / 6 < E;
-        const int32_t lk = G.link[okl ? e0 * 6 + it : 0], inf = G.info[okl ? e0 * 6 + it : 0];
+        const uint32_t o = okl ? 4 * it : 0;
+        const int32_t lk = ld_at(G.link + e0 * 6, o), inf = ld_at(G.info + e0 * 6, o);
         R.lk = okl ? lk : -1;
         R.inf = okl ? inf : 0;
     }
 #pragma unroll
     for (int k = 0; k < Sh::IT_SOL; ++k) {
         const int it = threadIdx.x + k * NT;
-        const int el = it / NP, p = it % NP;
-        const int64_t e = (it < EPB * NP && e0 + el < E) ? e0 + el : 0;
-        for (int v = 0; v < 5; ++v) R.P[k][v] = Pq[((int64_t)v * E + e) * NP + p];
-        R.bg[k][0] = B.bg[(e * 2 + 0) * NP + p];
-        R.bg[k][1] = B.bg[(e * 2 + 1) * NP + p];
-        for (int t = 0; t < 3; ++t) R.gb[k][t] = B.gbg[(e * 3 + t) * NP + p];
+        const uint32_t el = el_of<EPB>(it, NP, elmax), p = it % NP;
+        for (int v = 0; v < 5; ++v) R.P[k][v] = ld_at(Pq + (v * E + e0) * NP, 8 * (el * NP + p));
+        for (int t = 0; t < 2; ++t) R.bg[k][t] = ld_at(B.bg + e0 * 2 * NP, 4 * (el * 2 * NP + p), t * NP);
+        for (int t = 0; t < 3; ++t) R.gb[k][t] = ld_at(B.gbg + e0 * 3 * NP, 4 * (el * 3 * NP + p), t * NP);
     }
 #pragma unroll
     for (int k = 0; k < Sh::IT_FACE; ++k) {
         const int it = threadIdx.x + k * NT;
-        const int el = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
-        const int64_t e = (it < EPB * 6 * NF2 && e0 + el < E) ? e0 + el : 0;
-        const int64_t base = e * 6 + f;
-        for (int v = 0; v < 5; ++v) R.nq[k][v] = TQ[(base * 5 + v) * NF2 + pp];
-        R.db[k][0] = B.dbg[(base * 2 + 0) * NF2 + pp];
-        R.db[k][1] = B.dbg[(base * 2 + 1) * NF2 + pp];
+        const uint32_t el = el_of<EPB>(it, 6 * NF2, elmax), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
+        const uint32_t ef = el * 6 + f;
+        for (int v = 0; v < 5; ++v) R.nq[k][v] = ld_at(TQ + e0 * Sh::MB, 4 * (ef * 5 * NF2 + pp), v * NF2);
+        for (int t = 0; t < 2; ++t) R.db[k][t] = ld_at(B.dbg + e0 * Sh::DB, 4 * (ef * 2 * NF2 + pp), t * NF2);
     }
 }
 
 // the solution-point metrics (first used by the gradients)
 template <int N, int EPB, int NT>
-__device__ __forceinline__ void prologue_load_metrics(const GeoF &G, int64_t e0, Prologue<N, EPB, NT> &R) {
+__device__ __forceinline__ void prologue_load_metrics(const GeoF &G, int64_t e0, int elmax, Prologue<N, EPB, NT> &R) {
     using Sh = Shape<N, EPB, NT>;
     constexpr int NP = Sh::NP;
 #pragma unroll
     for (int k = 0; k < Sh::IT_SOL; ++k) {
         const int it = threadIdx.x + k * NT;
-        const int el = it / NP, p = it % NP;
-        const int64_t e = (it < EPB * NP && e0 + el < G.E) ? e0 + el : 0;
-        for (int t = 0; t < 9; ++t) R.gs[k][t] = G.solgeo[(e * 13 + t) * NP + p];
+        const uint32_t el = el_of<EPB>(it, NP, elmax), p = it % NP;
+        for (int t = 0; t < 9; ++t) R.gs[k][t] = ld_at(G.solgeo + e0 * 13 * NP, 4 * (el * 13 * NP + p), t * NP);
     }
 }
 
@@ -611,7 +624,7 @@ using MixedStage = MixedStageArgs;
 // Pout = c0 A + c1 (P + c2 Rp) (and Tout likewise), or Pout = Rp in
 // residual mode; the lift pass adds the missing part in place.
 template <int N, int EPB, int NT, int MINW, int KR>
-__global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_flux_mixed(OpsF<N> opa, GeoF G, MixedBufs B, PhysParams P,
+__global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_flux_mixed(OpsF<N> opa, GeoF G, MixedBufs B, PhysF F,
                                                          const double *__restrict__ Pq, const float *__restrict__ TQ,
                                                          float *__restrict__ TV, MixedStage S_) {
     using Sh = Shape<N, EPB, NT>;
@@ -619,37 +632,36 @@ __global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_fl
     __shared__ MixedElem<N> L[EPB];
     __shared__ OpsF<N> op;  // 1D operators (indexed per lane: LDS, not the argument segment)
     const int64_t e0 = (int64_t)blockIdx.x * EPB;
-    const PhysF F = physf_of(P);
     ops_to_lds(opa, op);
     // every global input of the element block, issued before the first wait
     // (unpredicated, clamped indices: see Prologue), in the order of first use
     Prologue<N, EPB, NT> R;
-    prologue_load<N, EPB, NT>(Pq, B, G, TQ, e0, R);
+    const int elmax = (G.E - 1 - e0 < EPB - 1) ? (int)(G.E - 1 - e0) : EPB - 1;
+    prologue_load<N, EPB, NT>(Pq, B, G, TQ, e0, elmax, R);
+    const float *fgb = G.fluxgeo + e0 * 9 * NFL, *gsb = B.gS0 + e0 * 3 * NFL, *rfb = G.rflux + e0 * 3 * NFL;
     float Sf[Sh::IT_FACE][3], gSf[Sh::IT_FACE], krf[Sh::IT_FACE];
 #pragma unroll
     for (int k = 0; k < Sh::IT_FACE; ++k) {
         const int it = threadIdx.x + k * NT;
-        const int el = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
-        const int64_t e = (it < EPB * 6 * NF2 && e0 + el < G.E) ? e0 + el : 0;
-        const int d = f >> 1, fl = ((f & 1) ? N : 0) + (N + 1) * pp;
+        const uint32_t el = el_of<EPB>(it, 6 * NF2, elmax), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
+        const uint32_t d = f >> 1, fl = ((f & 1) ? N : 0) + (N + 1) * pp, o = 4 * ((el * 3 + d) * NFL + fl);
         // along +xi_d here; the face phase turns them outward
-        for (int c = 0; c < 3; ++c) Sf[k][c] = G.fluxgeo[((e * 3 + d) * 3 + c) * NFL + fl];
-        gSf[k] = B.gS0[(e * 3 + d) * NFL + fl];
-        krf[k] = (KR == KR_RADIAL) ? G.rflux[(e * 3 + d) * NFL + fl] : 0.0f;
+        for (int c = 0; c < 3; ++c) Sf[k][c] = ld_at(fgb, 4 * ((el * 3 + d) * 3 * NFL + fl), c * NFL);
+        gSf[k] = ld_at(gsb, o);
+        krf[k] = (KR == KR_RADIAL) ? ld_at(rfb, o) : 0.0f;
     }
-    prologue_load_metrics<N, EPB, NT>(G, e0, R);
+    prologue_load_metrics<N, EPB, NT>(G, e0, elmax, R);
     float Si[3][Sh::IT_INTD][3], gSi[3][Sh::IT_INTD], kri[3][Sh::IT_INTD];
 #pragma unroll
     for (int d = 0; d < 3; ++d)
 #pragma unroll
         for (int k = 0; k < Sh::IT_INTD; ++k) {
             const int it = threadIdx.x + k * NT;
-            const int el = it / NINTD, q = it % NINTD;
-            const int fl = 1 + q % (N - 1) + (N + 1) * (q / (N - 1));
-            const int64_t e = (it < EPB * NINTD && e0 + el < G.E) ? e0 + el : 0;
-            for (int c = 0; c < 3; ++c) Si[d][k][c] = G.fluxgeo[((e * 3 + d) * 3 + c) * NFL + fl];
-            gSi[d][k] = B.gS0[(e * 3 + d) * NFL + fl];
-            kri[d][k] = (KR == KR_RADIAL) ? G.rflux[(e * 3 + d) * NFL + fl] : 0.0f;
+            const uint32_t el = el_of<EPB>(it, NINTD, elmax), q = it % NINTD;
+            const uint32_t fl = 1 + q % (N - 1) + (N + 1) * (q / (N - 1)), o = 4 * (el * 3 * NFL + fl);
+            for (int c = 0; c < 3; ++c) Si[d][k][c] = ld_at(fgb, 4 * (el * 9 * NFL + fl), (d * 3 + c) * NFL);
+            gSi[d][k] = ld_at(gsb, o, d * NFL);
+            kri[d][k] = (KR == KR_RADIAL) ? ld_at(rfb, o, d * NFL) : 0.0f;
         }
     prologue_store<N, EPB, NT>(R, L);
     __syncthreads();
@@ -701,7 +713,6 @@ __global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_fl
     double pst[Sh::IT_SOL][5], pb[Sh::IT_SOL][5];
     const bool rk = S_.mode != 0;
     const bool useA = rk && S_.c0 != 0.0, useT = rk && S_.Tout != nullptr, useB = useT && S_.d0 != 0.0;
-    const int elmax = (G.E - 1 - e0 < EPB - 1) ? (int)(G.E - 1 - e0) : EPB - 1;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
 #pragma unroll
@@ -738,9 +749,8 @@ __global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_fl
 #pragma unroll
             for (int k = 0; k < Sh::IT_SOL; ++k) {
                 const int it = threadIdx.x + k * NT;
-                const int el = min(it / NP, elmax), p = it % NP;
-                for (int c = 0; c < 4; ++c) gq[k][c] = ld_off(sgb, (uint32_t)((el * 13 + 9 + c) * NP + p));
-                const uint32_t o = (uint32_t)(el * NP + p);
+                const uint32_t el = el_of<EPB>(it, NP, elmax), p = it % NP, o = el * NP + p;
+                for (int c = 0; c < 4; ++c) gq[k][c] = ld_at(sgb, 4 * (el * 13 * NP + p), (9 + c) * NP);
                 for (int v = 0; v < 5; ++v) {
                     const int64_t vb = ((int64_t)v * G.E + e0) * NP;
                     r0v[k][v] = ld_off(B.R0 + vb, o);
@@ -955,7 +965,7 @@ struct WideM {
 };
 
 template <int N, int NT, int MINW, int KR>
-__global__ __launch_bounds__(NT, MINW) void k_flux_mixed_wide(OpsF<N> opa, GeoF G, MixedBufs B, PhysParams P,
+__global__ __launch_bounds__(NT, MINW) void k_flux_mixed_wide(OpsF<N> opa, GeoF G, MixedBufs B, PhysF F,
                                                               const double *__restrict__ Pq,
                                                               const float *__restrict__ TQ, float *__restrict__ TV,
                                                               MixedStage S_) {
@@ -966,7 +976,6 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed_wide(OpsF<N> opa, GeoF 
     __shared__ OpsF<N> op;
     const int64_t e = blockIdx.x, E = G.E;
     const int t = threadIdx.x;
-    const PhysF F = physf_of(P);
     // every global input before the first wait (unpredicated, clamped)
     double pv[W::IT_VP];
     float Gm[W::IT_VP][9], bg[W::IT_VP];
@@ -1368,13 +1377,13 @@ static hipError_t flux_mixed_wide_t(const Mesh &m, const GeoM &g, const PhysPara
     const dim3 grid((unsigned)m.E), block(NT);
     if (P.kappa_r1 != 0.0 || P.kappa_r2 != 0.0)
         hipLaunchKernelGGL((k_flux_mixed_wide<N, NT, MINW, KR_RADIAL>), grid, block, 0, s,
-                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), P, Pq, TQ, TV, st);
+                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), physf_of(P), Pq, TQ, TV, st);
     else if (P.kappa_r != 0.0)
         hipLaunchKernelGGL((k_flux_mixed_wide<N, NT, MINW, KR_CONST>), grid, block, 0, s,
-                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), P, Pq, TQ, TV, st);
+                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), physf_of(P), Pq, TQ, TV, st);
     else
         hipLaunchKernelGGL((k_flux_mixed_wide<N, NT, MINW, KR_NONE>), grid, block, 0, s,
-                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), P, Pq, TQ, TV, st);
+                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), physf_of(P), Pq, TQ, TV, st);
     return hipGetLastError();
 }
 template <int N>
@@ -1387,13 +1396,13 @@ static hipError_t flux_mixed_t(const Mesh &m, const GeoM &g, const PhysParams &P
     if (m.E <= 256 * CfgW<N>::MAX2) return flux_mixed_wide_t<N, CfgW<N>::NT2, CfgW<N>::W2>(m, g, P, Pq, TQ, TV, st, s);
     if (P.kappa_r1 != 0.0 || P.kappa_r2 != 0.0)
         hipLaunchKernelGGL((k_flux_mixed<N, EPB, NT, MINW, KR_RADIAL>), dim3(nb), dim3(NT), 0, s,
-                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), P, Pq, TQ, TV, st);
+                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), physf_of(P), Pq, TQ, TV, st);
     else if (P.kappa_r != 0.0)
         hipLaunchKernelGGL((k_flux_mixed<N, EPB, NT, MINW, KR_CONST>), dim3(nb), dim3(NT), 0, s,
-                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), P, Pq, TQ, TV, st);
+                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), physf_of(P), Pq, TQ, TV, st);
     else
         hipLaunchKernelGGL((k_flux_mixed<N, EPB, NT, MINW, KR_NONE>), dim3(nb), dim3(NT), 0, s,
-                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), P, Pq, TQ, TV, st);
+                           make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), physf_of(P), Pq, TQ, TV, st);
     return hipGetLastError();
 }
 template <int N>
