@@ -53,6 +53,56 @@ __device__ __forceinline__ void ops_to_lds(const OpsT<T, N> &src, OpsT<T, N> &ds
     for (int i = threadIdx.x; i < NW; i += blockDim.x) d[i] = s[i];
 }
 
+// The same in two steps, for a block that issues further loads in between:
+// loads return in order, so the words of a table loaded first are there
+// before the rest.  (Lanes past the end store the last word again: under a
+// guard the compiler moves the load to the store.)
+template <int NT, typename T, int N>
+struct OpsWords {
+    static constexpr int NW = (int)(sizeof(OpsT<T, N>) / sizeof(uint32_t)), IT = (NW + NT - 1) / NT;
+    uint32_t w[IT];
+    __device__ __forceinline__ void load(const OpsT<T, N> &src) {
+        const uint32_t *s = reinterpret_cast<const uint32_t *>(&src);
+#pragma unroll
+        for (int k = 0; k < IT; ++k) w[k] = s[min((int)threadIdx.x + k * NT, NW - 1)];
+    }
+    __device__ __forceinline__ void store(OpsT<T, N> &dst) const {
+        uint32_t *d = reinterpret_cast<uint32_t *>(&dst);
+#pragma unroll
+        for (int k = 0; k < IT; ++k) d[min((int)threadIdx.x + k * NT, NW - 1)] = w[k];
+    }
+};
+
+// Operator tables and face links of a block's EPB elements, loaded before its
+// other inputs and stored (link -1 past the last element) once those are
+// issued: a table copied at once, or after the other loads, costs the block a
+// trip to memory of its own, and a link loaded last waits for everything.
+// us per RK3 step before -> after: FP64 order 2, 3,600 hexes 50.5 -> 47.2;
+// order 3, 98,304 hexes 1,385 -> 1,338; order 5, 24,000 hexes 1,333 -> 1,293;
+// mixed order 3, 2,304 hexes 57.6 -> 51.4; order 4, 1,536 hexes 59.4 -> 54.6,
+// 331,776 hexes 6,140 -> 5,970.
+template <int EPB, int NT, typename T, int N>
+struct BlockTables {
+    static_assert(EPB * 6 <= NT, "one link per thread");
+    OpsWords<NT, T, N> ow;
+    int32_t l, i;
+    __device__ __forceinline__ static int item() { return min((int)threadIdx.x, EPB * 6 - 1); }
+    __device__ __forceinline__ void load(const OpsT<T, N> &src, const int32_t *link, const int32_t *info, int64_t e0,
+                                         int64_t E) {
+        ow.load(src);
+        const bool ok = EPB == 1 || e0 + item() / 6 < E;
+        l = link[ok ? e0 * 6 + item() : 0];
+        i = info[ok ? e0 * 6 + item() : 0];
+        l = ok ? l : -1;
+        i = ok ? i : 0;
+    }
+    __device__ __forceinline__ void store(OpsT<T, N> &op, int32_t *lk, int32_t *inf) const {
+        ow.store(op);
+        lk[item()] = l;
+        inf[item()] = i;
+    }
+};
+
 // line through solution point (a along d; t1 < t2 the tangential indices).
 // Written with arithmetic selects: d is often lane dependent (face points),
 // and nested conditionals on it compiled to divergent branches recomputed

@@ -277,7 +277,9 @@ struct Sh64 {
     // N = 5 (24,000) 1,434 -> 1,335; N = 6 (12,288) 1,256 -> 1,125.
     static constexpr bool FREC = N == 6;
     static constexpr int SR = N == 6 ? 22 : 20, NV = FREC ? 6 : 5;
-    static constexpr __device__ int face_at(int f, int v, int pp) { return FREC ? (f * NF2 + pp) * 6 + v : (f * 5 + v) * NF2 + pp; }
+    static constexpr __device__ int face_at(int f, int v, int pp) {
+        return FREC ? (f * NF2 + pp) * 6 + v : (f * 5 + v) * NF2 + pp;
+    }
     static constexpr __device__ int flux_at(int v, int fl) { return FREC ? fl * 6 + v : v * NFL + fl; }
     static constexpr int IT_SOL = (EPB * NP + NT - 1) / NT;
     static constexpr int IT_FACE = (EPB * 6 * NF2 + NT - 1) / NT;
@@ -328,13 +330,10 @@ __global__ __launch_bounds__(NT) void k_trace_push(Ops<N> opa, Geo G, const doub
     __shared__ int32_t lk[EPB][6], inf[EPB][6];
     __shared__ Ops<N> op;
     const int64_t e0 = (int64_t)blockIdx.x * EPB;
-    ops_to_lds(opa, op);
+    BlockTables<EPB, NT, double, N> bt;
+    bt.load(opa, G.link, G.info, e0, G.E);
     load_q<N, EPB, NT, true>(Q, G.E, e0, sq);
-    if ((int)threadIdx.x < EPB * 6) {
-        const bool ok = e0 + threadIdx.x / 6 < G.E;
-        lk[threadIdx.x / 6][threadIdx.x % 6] = ok ? G.link[e0 * 6 + threadIdx.x] : -1;
-        inf[threadIdx.x / 6][threadIdx.x % 6] = ok ? G.info[e0 * 6 + threadIdx.x] : 0;
-    }
+    bt.store(op, &lk[0][0], &inf[0][0]);
     __syncthreads();
     push_traces64<N, EPB, NT>(op, G, e0, lk, inf, sq, TQ);
 }
@@ -540,6 +539,8 @@ void k_flux64(Ops<N> opa, Geo G, PhysParams P, const double *__restrict__ Q,
     __shared__ int32_t lk[EPB][6], inf[EPB][6];
     __shared__ alignas(16) Ops<N> op;
     const int64_t e0 = (int64_t)blockIdx.x * EPB, E = G.E;
+    BlockTables<EPB, NT, double, N> bt;
+    bt.load(opa, G.link, G.info, e0, E);
     // every global input of the element block before the first wait;
     // unpredicated loads through clamped indices (items past the end read
     // element 0 and are never stored)
@@ -580,15 +581,7 @@ void k_flux64(Ops<N> opa, Geo G, PhysParams P, const double *__restrict__ Q,
         }
     };
     if constexpr (PART != 1) load_si(0, 0);
-    {
-        const bool okl = (int)threadIdx.x < EPB * 6 && e0 + threadIdx.x / 6 < E;
-        const int32_t l = G.link[okl ? e0 * 6 + threadIdx.x : 0], i = G.info[okl ? e0 * 6 + threadIdx.x : 0];
-        if ((int)threadIdx.x < EPB * 6) {
-            lk[threadIdx.x / 6][threadIdx.x % 6] = okl ? l : -1;
-            inf[threadIdx.x / 6][threadIdx.x % 6] = okl ? i : 0;
-        }
-    }
-    ops_to_lds(opa, op);
+    bt.store(op, &lk[0][0], &inf[0][0]);
 #pragma unroll
     for (int k = 0; k < Sh::IT_SOL; ++k) {
         const int it = threadIdx.x + k * NT;
@@ -1018,13 +1011,8 @@ __global__ __launch_bounds__(NT) void k_lift64(Ops<N> opa, Geo G, const double *
     const bool useT = S_.mode != 0 && S_.Tout != nullptr;
     // every global input first (unpredicated, clamped; the mailbox slots of
     // boundary faces are never written and are selected away below)
-    int32_t rl, ri;
-    {
-        const bool okl = (int)threadIdx.x < EPB * 6 && e0 + threadIdx.x / 6 < E;
-        const int32_t l = G.link[okl ? e0 * 6 + threadIdx.x : 0], i = G.info[okl ? e0 * 6 + threadIdx.x : 0];
-        rl = okl ? l : -1;
-        ri = okl ? i : 0;
-    }
+    BlockTables<EPB, NT, double, N> bt;
+    bt.load(opa, G.link, G.info, e0, E);
     double mb[IT_MB];
 #pragma unroll
     for (int k = 0; k < IT_MB; ++k) {
@@ -1047,11 +1035,7 @@ __global__ __launch_bounds__(NT) void k_lift64(Ops<N> opa, Geo G, const double *
             r0[k][v] = bal ? S_.R0[gi] : 0.0;
         }
     }
-    ops_to_lds(opa, op);
-    if ((int)threadIdx.x < EPB * 6) {
-        lk[threadIdx.x / 6][threadIdx.x % 6] = rl;
-        inf[threadIdx.x / 6][threadIdx.x % 6] = ri;
-    }
+    bt.store(op, &lk[0][0], &inf[0][0]);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < IT_MB; ++k) {
@@ -1148,6 +1132,8 @@ __global__ __launch_bounds__(Wide<N>::NT, 4) void k_flux64_wide(Ops<N> opa, Geo 
     const int ii = isi ? t - W::FP : 0, dq = ii / ((N - 1) * NF2), iq = ii % ((N - 1) * NF2);
     const int d = isf ? f >> 1 : dq, m = isf ? ((f & 1) ? N : 0) : 1 + iq % (N - 1), tt = isf ? pp : iq / (N - 1);
     const int fl = m + (N + 1) * tt;
+    BlockTables<1, NT, double, N> bt;
+    bt.load(opa, G.link, G.info, e, E);
     // every global input before the first wait (unpredicated, clamped)
     double qv[W::IT_VP], Gm[W::IT_VP][9], nq[5], S[3];
 #pragma unroll
@@ -1160,14 +1146,7 @@ __global__ __launch_bounds__(Wide<N>::NT, 4) void k_flux64_wide(Ops<N> opa, Geo 
     const double sg = (isf && !(f & 1)) ? -1.0 : 1.0;
     for (int c = 0; c < 3; ++c) S[c] = sg * G.fluxgeo[((e * 3 + d) * 3 + c) * NFL + fl];
     const double rl = RAD ? G.rflux[(e * 3 + d) * NFL + fl] : 0.0;
-    {
-        const int32_t l = G.link[e * 6 + (t < 6 ? t : 0)], i = G.info[e * 6 + (t < 6 ? t : 0)];
-        if (t < 6) {
-            lk[t] = l;
-            inf[t] = i;
-        }
-    }
-    ops_to_lds(opa, op);
+    bt.store(op, lk, inf);
 #pragma unroll
     for (int k = 0; k < W::IT_VP; ++k) {
         const int it = t + k * NT;
@@ -1280,13 +1259,11 @@ __global__ __launch_bounds__(Wide<N>::NT) void k_trace_push_wide(Ops<N> opa, Geo
     __shared__ int32_t lk[6], inf[6];
     __shared__ Ops<N> op;
     const int64_t e = blockIdx.x;
-    ops_to_lds(opa, op);
-    if (threadIdx.x < 6) {
-        lk[threadIdx.x] = G.link[e * 6 + threadIdx.x];
-        inf[threadIdx.x] = G.info[e * 6 + threadIdx.x];
-    }
+    BlockTables<1, Wide<N>::NT, double, N> bt;
+    bt.load(opa, G.link, G.info, e, G.E);
     for (int it = threadIdx.x; it < 5 * NP; it += Wide<N>::NT)
         sq[it / NP][lds_sol<N>(it % NP)] = Q[((int64_t)(it / NP) * G.E + e) * NP + it % NP];
+    bt.store(op, lk, inf);
     __syncthreads();
     push_traces64_wide<N>(op, lk, inf, sq, TQ);
 }
@@ -1303,6 +1280,8 @@ __global__ __launch_bounds__(Wide<N>::NT) void k_lift64_wide(Ops<N> opa, Geo G, 
     const int64_t e = blockIdx.x, E = G.E;
     const int t = threadIdx.x;
     const bool useT = S_.mode != 0 && S_.Tout != nullptr, bal = S_.R0 != nullptr;
+    BlockTables<1, W::NT, double, N> bt;
+    bt.load(opa, G.link, G.info, e, E);
     // every global input first (unpredicated, clamped; the mailbox slots of
     // boundary faces are never written and are selected away below)
     double mb[IT_MB];
@@ -1323,11 +1302,7 @@ __global__ __launch_bounds__(Wide<N>::NT) void k_lift64_wide(Ops<N> opa, Geo G, 
         to[k] = useT ? S_.Tout[gi] : 0.0;
         r0[k] = bal ? S_.R0[gi] : 0.0;
     }
-    if (t < 6) {
-        lk[t] = G.link[e * 6 + t];
-        inf[t] = G.info[e * 6 + t];
-    }
-    ops_to_lds(opa, op);
+    bt.store(op, lk, inf);
 #pragma unroll
     for (int k = 0; k < IT_MB; ++k)
         if (t + k * NT < MBE) (&nv[0][0][0])[t + k * NT] = (ml[k] >= 0) ? mb[k] : 0.0;

@@ -224,7 +224,6 @@ struct MixedEl {
         float cs[5][6][NF2];       // common values of the perturbation
         float ft[ND][5][NFL];      // transformed fluxes, written after cs is consumed
     } u;
-    int32_t lk[6], inf[6];        // neighbour element and info word per face
     __device__ __forceinline__ float &at(int slot, int p) { return r[REC ? p * SLOTS + slot : slot * NP + p]; }
     // FP64 perturbation minus its FP32 value (stage update)
     __device__ __forceinline__ float &plo(int v, int p) {
@@ -276,12 +275,23 @@ struct Shape {
 // predicated (a guarded load compiles to a branch that waits for it at
 // once) and those items are never stored.
 //
-// Every address is a block-uniform base (scalar registers) plus a 32-bit
+// Most addresses are a block-uniform base (scalar registers) plus a 32-bit
 // lane offset in bytes plus a constant: one vector register serves all the
 // loads of an array, where 64-bit lane addresses took a vector add each.
+// The pass issues vector instructions for most of its time at order 4; with
+// this, the physics constants converted on the host and the viscous flux's
+// kinetic terms in the form of the inviscid ones it has 5 % fewer (2,401 ->
+// 2,273): 6.21 -> 6.14 ms per RK3 step on 331,776 hexes.
 template <typename T>
 __device__ __forceinline__ T ld_at(const T *base, uint32_t bytes, int c = 0) {
     return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + bytes + c * (int)sizeof(T));
+}
+// whether item it = threadIdx.x + k NT lies past the TOTAL items of the block
+// (known to be false for the rounds that are full: a guard there is a branch
+// under which the compiler moves the loads of its body)
+template <int NT, int TOTAL>
+__device__ __forceinline__ bool past(int k, int it) {
+    return (k + 1) * NT > TOTAL && it >= TOTAL;
 }
 // element of item it (of n per element) within the block, clamped to the last
 // element (elmax)
@@ -300,7 +310,6 @@ struct Prologue {
     // neighbour data at this thread's face items (face item it: el, f, pp):
     // perturbation trace, background jump
     float nq[Sh::IT_FACE][5], db[Sh::IT_FACE][2];
-    int32_t lk, inf;
 };
 
 template <int N, int EPB, int NT>
@@ -311,16 +320,7 @@ __device__ __forceinline__ void prologue_load(const double *Pq, const MixedBufs 
     constexpr int NP = Sh::NP, NF2 = Sh::NF2;
     const int64_t E = G.E;
     // issued in the order of first use, so that each phase waits only for
-    // its own inputs: links, the LDS fields, the neighbour traces (common
-    // values)
-    {
-        const int it = threadIdx.x;
-        const bool okl = it < EPB * 6 && e0 + it / 6 < E;
-        const uint32_t o = okl ? 4 * it : 0;
-        const int32_t lk = ld_at(G.link + e0 * 6, o), inf = ld_at(G.info + e0 * 6, o);
-        R.lk = okl ? lk : -1;
-        R.inf = okl ? inf : 0;
-    }
+    // its own inputs: the LDS fields, the neighbour traces (common values)
 #pragma unroll
     for (int k = 0; k < Sh::IT_SOL; ++k) {
         const int it = threadIdx.x + k * NT;
@@ -360,7 +360,7 @@ __device__ __forceinline__ void prologue_store(const Prologue<N, EPB, NT> &R, Mi
 #pragma unroll
     for (int k = 0; k < Sh::IT_SOL; ++k) {
         const int it = threadIdx.x + k * NT;
-        if (it >= EPB * NP) break;
+        if (past<NT, EPB * NP>(k, it)) break;
         const int el = it / NP, p = it % NP;
         for (int v = 0; v < 5; ++v) {
             const float hi = (float)R.P[k][v];
@@ -370,10 +370,6 @@ __device__ __forceinline__ void prologue_store(const Prologue<N, EPB, NT> &R, Mi
         L[el].at(F_R0, p) = R.bg[k][0];
         L[el].at(F_E0, p) = R.bg[k][1];
         for (int c = 0; c < 3; ++c) L[el].at(MixedElem<N>::GR + 3 * F_R0 + c, p) = R.gb[k][c];
-    }
-    if ((int)threadIdx.x < EPB * 6) {
-        L[threadIdx.x / 6].lk[threadIdx.x % 6] = R.lk;
-        L[threadIdx.x / 6].inf[threadIdx.x % 6] = R.inf;
     }
 }
 
@@ -421,7 +417,8 @@ __device__ __forceinline__ void common_value(const float pv[5], float r0, int32_
 // given: the face-flux phase reuses them
 template <int N, int EPB, int NT>
 __device__ __forceinline__ void common_values(const OpsF<N> &op, const GeoF &G, const PhysF &F, int64_t e0,
-                                              MixedElem<N> *L, const Prologue<N, EPB, NT> &R,
+                                              MixedElem<N> *L, const int32_t (*lk)[6], const int32_t (*inf_)[6],
+                                              const Prologue<N, EPB, NT> &R,
                                               float (*fo)[NFIELD], const float (*Sf)[3]) {
     using Sh = Shape<N, EPB, NT>;
     constexpr int NF2 = N * N, NFL = (N + 1) * N * N;
@@ -438,7 +435,7 @@ __device__ __forceinline__ void common_values(const OpsF<N> &op, const GeoF &G, 
         float x[8];
         l.template line<0, 2>(op, m, base, st, x);
         for (int v = 0; v < NFIELD; ++v) fo[k][v] = x[v];
-        const int32_t nb = l.lk[f], inf = l.inf[f];
+        const int32_t nb = lk[el][f], inf = inf_[el][f];
         common_value(x, x[F_R0], nb, inf, R.nq[k], Sf[k], F, [&](int v, float x) { l.u.cs[v][f][pp] = x; });
     }
 }
@@ -580,8 +577,10 @@ __global__ __launch_bounds__(NT) void k_pert_begin(OpsF<N> opa, GeoF G, const do
     constexpr int NP = N * N * N, NF2 = N * N;
     __shared__ float sp[EPB][5][NP];
     __shared__ OpsF<N> op;
-    ops_to_lds(opa, op);
+    __shared__ int32_t lk[EPB][6], inf[EPB][6];
     const int64_t e0 = (int64_t)blockIdx.x * EPB;
+    BlockTables<EPB, NT, float, N> bt;
+    bt.load(opa, G.link, G.info, e0, G.E);
     for (int it = threadIdx.x; it < EPB * 5 * NP; it += NT) {
         const int el = it / (5 * NP), r = it % (5 * NP), v = r / NP, p = r % NP;
         const int64_t e = e0 + el;
@@ -594,14 +593,15 @@ __global__ __launch_bounds__(NT) void k_pert_begin(OpsF<N> opa, GeoF G, const do
         }
         sp[el][v][p] = val;
     }
+    bt.store(op, &lk[0][0], &inf[0][0]);
     __syncthreads();
     for (int it = threadIdx.x; it < EPB * 6 * NF2; it += NT) {
         const int el = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
         const int64_t e = e0 + el;
         if (e >= G.E) continue;
-        const int32_t nb = G.link[e * 6 + f];
+        const int32_t nb = lk[el][f];
         if (nb < 0) continue;
-        const int64_t slot = mailbox_slot<N>(nb, G.info[e * 6 + f], pp);
+        const int64_t slot = mailbox_slot<N>(nb, inf[el][f], pp);
         const int d = f >> 1, m = (f & 1) ? N : 0, base = sol_of<N>(d, 0, pp % N, pp / N), st = stride_of<N>(d);
         for (int v = 0; v < 5; ++v) TQ[slot + v * NF2] = line_val<N>(op, sp[el][v], m, base, st);
     }
@@ -624,15 +624,17 @@ using MixedStage = MixedStageArgs;
 // Pout = c0 A + c1 (P + c2 Rp) (and Tout likewise), or Pout = Rp in
 // residual mode; the lift pass adds the missing part in place.
 template <int N, int EPB, int NT, int MINW, int KR>
-__global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_flux_mixed(OpsF<N> opa, GeoF G, MixedBufs B, PhysF F,
-                                                         const double *__restrict__ Pq, const float *__restrict__ TQ,
-                                                         float *__restrict__ TV, MixedStage S_) {
+__global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW)
+void k_flux_mixed(OpsF<N> opa, GeoF G, MixedBufs B, PhysF F, const double *__restrict__ Pq,
+                  const float *__restrict__ TQ, float *__restrict__ TV, MixedStage S_) {
     using Sh = Shape<N, EPB, NT>;
     constexpr int NP = Sh::NP, NF2 = Sh::NF2, NFL = Sh::NFL, NINTD = Sh::NINTD;
     __shared__ MixedElem<N> L[EPB];
     __shared__ OpsF<N> op;  // 1D operators (indexed per lane: LDS, not the argument segment)
+    __shared__ int32_t lk[EPB][6], inf_[EPB][6];  // neighbour element and info word per face
     const int64_t e0 = (int64_t)blockIdx.x * EPB;
-    ops_to_lds(opa, op);
+    BlockTables<EPB, NT, float, N> bt;
+    bt.load(opa, G.link, G.info, e0, G.E);
     // every global input of the element block, issued before the first wait
     // (unpredicated, clamped indices: see Prologue), in the order of first use
     Prologue<N, EPB, NT> R;
@@ -663,10 +665,11 @@ __global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_fl
             gSi[d][k] = ld_at(gsb, o, d * NFL);
             kri[d][k] = (KR == KR_RADIAL) ? ld_at(rfb, o, d * NFL) : 0.0f;
         }
+    bt.store(op, &lk[0][0], &inf_[0][0]);
     prologue_store<N, EPB, NT>(R, L);
     __syncthreads();
     float fo[Sh::IT_FACE][NFIELD];
-    common_values<N, EPB, NT>(op, G, F, e0, L, R, fo, Sf);
+    common_values<N, EPB, NT>(op, G, F, e0, L, lk, inf_, R, fo, Sf);
     __syncthreads();
     gradients<N, EPB, NT>(op, G, e0, L, R.gs);
     __syncthreads();
@@ -681,7 +684,7 @@ __global__ __launch_bounds__(NT, N == 6 && KR == KR_RADIAL ? 3 : MINW) void k_fl
         const int el = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
         const int64_t e = e0 + el;
         if (e >= G.E) continue;
-        const int32_t nb = L[el].lk[f], inf = L[el].inf[f];
+        const int32_t nb = lk[el][f], inf = inf_[el][f];
         const int d = f >> 1, m = (f & 1) ? N : 0, t1 = pp % N, t2 = pp / N;
         const float sg = (f & 1) ? 1.0f : -1.0f;
         const float So[3] = {sg * Sf[k][0], sg * Sf[k][1], sg * Sf[k][2]}, gSo = sg * gSf[k];
@@ -832,6 +835,8 @@ __device__ __forceinline__ double state_of(double q0, double p) {
 // (S_.Qend) in the place of P and pushes no traces (the next call forms P and
 // its traces from Q): a pass over Q0, P and Q and a trace push less per call
 // (0.44 ms and 0.1 ms on 331,776 hexes).
+// (its tables are copied at once: BlockTables makes no difference here but at
+// order 2, 803 -> 820 us per RK3 step on 192,000 hexes)
 template <int N, int EPB, int NT, bool END>
 __global__ __launch_bounds__(NT) void k_lift_mixed(OpsF<N> opa, GeoF G, const float *__restrict__ TV, MixedStage S_) {
     constexpr int NP = N * N * N, NF2 = N * N;
@@ -974,8 +979,11 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed_wide(OpsF<N> opa, GeoF 
     using EL = MixedEl<N, 3, N == 2>;
     __shared__ EL L;
     __shared__ OpsF<N> op;
+    __shared__ int32_t lk[6], inf_[6];
     const int64_t e = blockIdx.x, E = G.E;
     const int t = threadIdx.x;
+    BlockTables<1, NT, float, N> bt;
+    bt.load(opa, G.link, G.info, e, E);
     // every global input before the first wait (unpredicated, clamped)
     double pv[W::IT_VP];
     float Gm[W::IT_VP][9], bg[W::IT_VP];
@@ -1023,14 +1031,7 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed_wide(OpsF<N> opa, GeoF 
         const int p = (t + k * NT) % NP;
         for (int c = 0; c < 9; ++c) Gm[k][c] = G.solgeo[(e * 13 + c) * NP + p];
     }
-    {
-        const int32_t lk = G.link[e * 6 + (t < 6 ? t : 0)], inf = G.info[e * 6 + (t < 6 ? t : 0)];
-        if (t < 6) {
-            L.lk[t] = lk;
-            L.inf[t] = inf;
-        }
-    }
-    ops_to_lds(opa, op);
+    bt.store(op, lk, inf_);
 #pragma unroll
     for (int k = 0; k < W::IT_VP; ++k) {
         const int it = t + k * NT;
@@ -1051,7 +1052,7 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed_wide(OpsF<N> opa, GeoF 
         const int f = it / NF2, pp = it % NF2, d = f >> 1, m = (f & 1) ? N : 0;
         const int base = sol_of<N>(d, 0, pp % N, pp / N), st = stride_of<N>(d);
         L.template line<0, 2>(op, m, base, st, fo[k]);
-        common_value(fo[k], fo[k][F_R0], L.lk[f], L.inf[f], nq[k], S[k], F,
+        common_value(fo[k], fo[k][F_R0], lk[f], inf_[f], nq[k], S[k], F,
                      [&](int v, float x) { L.u.cs[v][f][pp] = x; });
     }
     __syncthreads();
@@ -1087,7 +1088,7 @@ __global__ __launch_bounds__(NT, MINW) void k_flux_mixed_wide(OpsF<N> opa, GeoF 
         const float kr = kr_of<KR>(F, krl[k]);
         if (k < W::IT_FACE && x < W::NFACE) {
             const int kf = k < W::IT_FACE ? k : 0, f = x / NF2;
-            const int32_t nb = L.lk[f], inf = L.inf[f];
+            const int32_t nb = lk[f], inf = inf_[f];
             const float sg = (f & 1) ? 1.0f : -1.0f;
             const float So[3] = {sg * S[k][0], sg * S[k][1], sg * S[k][2]}, gSo = sg * gS[k];
             float fv[5], ff[5];
@@ -1174,6 +1175,8 @@ __global__ __launch_bounds__(NT) void k_lift_mixed_wide(OpsF<N> opa, GeoF G, con
     const int64_t e = blockIdx.x, E = G.E;
     const int t = threadIdx.x;
     const bool useT = S_.mode != 0 && S_.Tout != nullptr;
+    BlockTables<1, NT, float, N> bt;
+    bt.load(opa, G.link, G.info, e, E);
     // every global input first (unpredicated, clamped; the mailbox slots of
     // boundary faces are never written and are selected away below)
     float mb[IT_MB];
@@ -1195,11 +1198,7 @@ __global__ __launch_bounds__(NT) void k_lift_mixed_wide(OpsF<N> opa, GeoF G, con
         to[k] = useT ? S_.Tout[gi] : 0.0;
         q0[k] = END ? S_.Q0[gi] : 0.0;
     }
-    if (t < 6) {
-        lk[t] = G.link[e * 6 + t];
-        inf[t] = G.info[e * 6 + t];
-    }
-    ops_to_lds(opa, op);
+    bt.store(op, lk, inf);
 #pragma unroll
     for (int k = 0; k < IT_MB; ++k)
         if (t + k * NT < MBE) (&nv[0][0][0])[t + k * NT] = (ml[k] >= 0) ? mb[k] : 0.0f;
