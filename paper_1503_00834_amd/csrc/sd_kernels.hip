@@ -1092,8 +1092,8 @@ __global__ __launch_bounds__(NT) void k_lift64(Ops<N> opa, Geo G, const double *
 // directions and the faces at once; the fluxes of the three directions are
 // held in LDS together), so a phase is one round and the chain of a block is
 // a third as long: flux and lift pass of the 288-hex order-3 shell 12.7 + 4.8
-// -> 7.4 + 4.0 us, ten SSP-RK3 steps 531 -> 326 us; 316 us with the records of
-// the element pass for the state and gradients.  The price is in the
+// -> 7.4 + 4.0 us, ten SSP-RK3 steps 531 -> 326 us; 306 us with the records of
+// the element pass for the state and gradients and the early table loads.  The price is in the
 // larger meshes: fewer elements in flight per CU and the solution-point
 // metrics read by five threads instead of one.  The sums run over the same
 // terms in the same order.
@@ -1538,10 +1538,10 @@ static hipError_t launch_trace_t(const Mesh &m, const Geo &G, const double *Q, d
 // Largest meshes, in elements per CU (256), that run the wide passes: where
 // an SSP-RK3 step of a shell was no slower with them (us per step, element
 // passes / wide passes; the flux pass of order 4 is k_flux64_n4):
-//   flux  order 2: 56.8 / 50.3 at 3,600 hexes, 62.1 / 62.6 at 5,184
-//         order 3: 45.6 / 31.6 at 288, 72.0 / 67.0 at 2,304, 84.0 / 92.2 at 3,600
-//         order 4: 35.0 / 30.4 at 162, 36.1 / 39.1 at 288
-//         order 5: 49.3 / 39.2 at 162, 61.5 / 59.8 at 288, 80.0 / 88.1 at 648
+//   flux  order 2: 53.8 / 47.1 at 3,600 hexes, 58.3 / 58.9 at 5,184
+//         order 3: 43.1 / 30.5 at 288, 68.0 / 63.8 at 2,304, 77.9 / 87.7 at 3,600
+//         order 4: 34.4 / 29.5 at 162, 35.5 / 38.4 at 288
+//         order 5: 47.5 / 38.0 at 162, 59.7 / 58.9 at 288, 77.5 / 86.6 at 648
 //         order 6: 59.4 / 59.4 at 162, 82.2 / 101.6 at 288 (not used)
 //   lift and trace push
 //         order 2: 74.1 / 70.3 at 7,776, 95.0 / 99.4 at 12,288

@@ -1321,15 +1321,15 @@ template <int N> struct CfgL { static constexpr int EPB = CfgM<N>::EPB, NT = Cfg
 // passes / wide passes with NT1 [/ NT2] threads):
 //   order 2: 56.0 / 51.5 at 5,184 hexes, 60.9 / 64.0 at 7,776; lift alone
 //            60.9 / 59.9 at 7,776, 72.7 / 80.6 at 12,288
-//   order 3: flux alone 41.4 / 29.0 at 288, 60.5 / 57.7 at 2,304, 67.7 / 75.2
-//            at 3,600; lift alone 53.9 / 53.1 at 1,536, 62.9 / 63.8 at 2,304
+//   order 3: flux alone 39.3 / 26.7 at 288, 59.3 / 52.0 at 2,304, 67.4 / 67.3
+//            at 3,600, 83.1 / 85.9 at 5,184; lift alone 53.9 / 53.1 at 1,536, 62.9 / 63.8 at 2,304
 //   order 4: 45.8 / 31.6 / 36.4 at 288, 51.0 / 43.0 / 42.1 at 648; flux alone
-//            53.9 / - / 49.5 at 1,080, 60.8 / - / 58.8 at 1,536, 78.6 / - /
-//            81.4 at 2,304; lift alone 63.8 / 60.6 at 1,536, 79.8 / 79.6 at 2,304
-//   order 5: 52.9 / 33.0 / 42.3 at 162; flux alone 51.1 / 49.8 / 46.3 at 288,
-//            63.0 / - / 63.1 at 648; lift alone 58.6 / 55.2 at 288, 68.7 / 69.2
+//            49.6 / - / 45.9 at 1,080, 55.0 / - / 54.3 at 1,536, 74.1 / - /
+//            78.2 at 2,304; lift alone 63.8 / 60.6 at 1,536, 79.8 / 79.6 at 2,304
+//   order 5: 52.9 / 33.0 / 42.3 at 162; flux alone 48.1 / - / 44.5 at 288,
+//            60.3 / - / 61.5 at 648; lift alone 58.6 / 55.2 at 288, 68.7 / 69.2
 //            at 648
-//   order 6: 45.3 / 43.1 at 162, 60.7 / 73.5 at 288
+//   order 6: 43.4 / 41.3 at 162, 58.9 / 72.1 at 288
 template <int N> struct CfgW;
 template <> struct CfgW<2> { static constexpr int NT1 = 64, W1 = 1, MAX1 = 20, NT2 = 64, W2 = 1, MAX2 = 0, LIFT = 28; };
 template <> struct CfgW<3> { static constexpr int NT1 = 192, W1 = 1, MAX1 = 9, NT2 = 192, W2 = 1, MAX2 = 0, LIFT = 6; };
