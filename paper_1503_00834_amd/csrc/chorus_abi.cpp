@@ -1273,25 +1273,32 @@ int chorus_closure_infer(chorus_mesh_t mesh, const chorus_physics *phys, const d
     return CHORUS_OK;
 }
 
+// Training workspace: an index flag, then one partial gradient (row) per 16
+// samples, kTrainPartials at most.  `least` is what a call needs: the size
+// that callers of this library have planned with (activation rows and one
+// partial per 64 samples), always enough for one row.  Between 17 and about
+// 8,200 samples it is up to 30 % short of a row per block; a call then runs
+// fewer blocks, some taking two groups (batch 4,096: 236 blocks instead of
+// 256), and a workspace of the queried size runs them all.  Neither size
+// shrinks as the batch grows, so a workspace serves every smaller batch.
 struct TrainLayout {
-    size_t part, flag, total;
+    size_t least, full;
 };
+static constexpr size_t kTrainRow = sizeof(float) * (kMlpParams + 1), kTrainPart = 256;
 
-// one partial gradient per 16 samples, kTrainPartials at most: it never
-// shrinks as the batch grows, so a workspace serves every smaller batch
 static TrainLayout train_layout(int64_t B) {
     TrainLayout L;
-    size_t off = 0;
-    const int64_t rows = std::min<int64_t>((B + 15) / 16, kTrainPartials);
-    L.part = off;  off = align256(off + sizeof(float) * (kMlpParams + 1) * (size_t)rows);
-    L.flag = off;  off = align256(off + sizeof(int));
-    L.total = off;
+    const size_t n = (size_t)B, act = sizeof(float) * 64 * n;
+    L.least = 4 * align256(act) + align256(sizeof(float) * 16 * n) + align256(sizeof(float) * n) +
+              align256(kTrainRow * ((n + 63) / 64)) + 256;
+    L.full = std::max(L.least, align256(kTrainPart + kTrainRow * std::min<size_t>((n + 15) / 16, kTrainPartials)));
     return L;
 }
 
-static TrainBufs train_bufs(const TrainLayout &L, unsigned char *W, int64_t n_mean) {
+static TrainBufs train_bufs(unsigned char *W, size_t ws_bytes, int64_t n_mean) {
     TrainBufs T;
-    T.part = (float *)(W + L.part);
+    T.part = (float *)(W + kTrainPart);
+    T.rows = (int)std::min<size_t>((ws_bytes - kTrainPart) / kTrainRow, kTrainPartials);
     T.n_mean = n_mean;
     return T;
 }
@@ -1303,7 +1310,7 @@ int chorus_closure_train_workspace_bytes(int64_t batch, size_t *bytes) {
         set_error("closure workspace: need 1 <= batch <= 2^20");
         return CHORUS_EINVAL;
     }
-    *bytes = train_layout(batch).total;
+    *bytes = train_layout(batch).full;
     return CHORUS_OK;
 }
 
@@ -1313,13 +1320,11 @@ int chorus_closure_grad(const float *X_dev, const float *Y_dev, int64_t n, const
         set_error("null device pointer");
         return CHORUS_EINVAL;
     }
-    if (n < 1 || n > kMaxBatch || train_layout(n).total > ws_bytes) {
+    if (n < 1 || n > kMaxBatch || train_layout(n).least > ws_bytes) {
         set_error("closure_grad: need 1 <= n <= 2^20 and a workspace for n samples");
         return CHORUS_EINVAL;
     }
-    const TrainLayout L = train_layout(n);
-    unsigned char *W = (unsigned char *)ws;
-    const TrainBufs T = train_bufs(L, W, n);
+    const TrainBufs T = train_bufs((unsigned char *)ws, ws_bytes, n);
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = launch_train_grad(X_dev, Y_dev, nullptr, 0, (int)n, params_dev, T, grad_dev, loss_dev, s);
     if (e != hipSuccess) return hip_fail(e, "closure_grad");
@@ -1334,7 +1339,7 @@ int chorus_closure_train(const float *X_dev, const float *Y_dev, int64_t n, cons
         return CHORUS_EINVAL;
     }
     if (n < 1 || n > INT32_MAX || batch < 1 || batch > kMaxBatch || iters < 0 || step0 < 0 ||
-        train_layout(batch).total > ws_bytes) {
+        train_layout(batch).least > ws_bytes) {
         set_error("closure_train: need 1 <= n < 2^31, 1 <= batch <= 2^20, iters >= 0, step0 >= 0 and a "
                   "workspace for the batch");
         return CHORUS_EINVAL;
@@ -1346,12 +1351,10 @@ int chorus_closure_train(const float *X_dev, const float *Y_dev, int64_t n, cons
     }
     if (iters == 0) return CHORUS_OK;
     hipStream_t s = (hipStream_t)stream;
-    const TrainLayout L = train_layout(batch);
-    unsigned char *W = (unsigned char *)ws;
-    const TrainBufs T = train_bufs(L, W, batch);
+    const TrainBufs T = train_bufs((unsigned char *)ws, ws_bytes, batch);
     // every sample index must address a row of X and Y (checked on the
     // device, before any training kernel reads through the indices)
-    int *flag = (int *)(W + L.flag), bad = 0;
+    int *flag = (int *)ws, bad = 0;
     hipError_t e = launch_check_idx(idx_dev, (int64_t)iters * batch, n, flag, s);
     if (e == hipSuccess) e = hipMemcpyAsync(&bad, flag, sizeof(int), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);

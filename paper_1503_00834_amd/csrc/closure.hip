@@ -510,14 +510,14 @@ hipError_t launch_pack(const float *W, const float *norm, unsigned char *model, 
     return hipGetLastError();
 }
 
-// blocks of k_train for a mini-batch: one per 16 samples up to
-// kTrainPartials, beyond which a block takes several groups in turn
-static int train_blocks(int nb) { return std::min((nb + 15) / 16, kTrainPartials); }
+// blocks of k_train for a mini-batch: one per 16 samples up to the partials
+// of the workspace, beyond which a block takes several groups in turn
+static int train_blocks(int nb, const TrainBufs &T) { return std::min((nb + 15) / 16, T.rows); }
 static constexpr int kSumBlocksMlp = (kMlpParams + 1 + 63) / 64;
 
 hipError_t launch_train_grad(const float *X, const float *Y, const int32_t *idx, int64_t base, int nb,
                              const float *W, const TrainBufs &T, float *grad, float *loss, hipStream_t s) {
-    const int nblk = train_blocks(nb);
+    const int nblk = train_blocks(nb, T);
     hipLaunchKernelGGL(k_train, dim3(nblk), dim3(256), 0, s, X, Y, idx, base, nb, W, T.part, T.n_mean);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -528,7 +528,7 @@ hipError_t launch_train_grad(const float *X, const float *Y, const int32_t *idx,
 
 hipError_t launch_train_step(const float *X, const float *Y, const int32_t *idx, int64_t base, int nb, float *W,
                              float *m, float *v, const TrainBufs &T, const AdamArgs &a, float *loss, hipStream_t s) {
-    const int nblk = train_blocks(nb);
+    const int nblk = train_blocks(nb, T);
     hipLaunchKernelGGL(k_train, dim3(nblk), dim3(256), 0, s, X, Y, idx, base, nb, W, T.part, T.n_mean);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -70,7 +70,8 @@ hipError_t launch_lift64(const Mesh &m, const Geo &G, const double *TV, const St
 // closure training: the partial gradients and losses of one mini-batch
 constexpr int kTrainPartials = 512;  // partials at most (blocks of k_train)
 struct TrainBufs {
-    float *part;     // [min(ceil(nb / 16), kTrainPartials)][6480]
+    float *part;     // [rows][6480]
+    int rows;        // partials that the workspace holds, kTrainPartials at most
     int64_t n_mean;  // samples the loss is averaged over
 };
 

@@ -318,6 +318,36 @@ def test_grad_at_group_edges(ch, cl, torch_dev, n):
         assert err <= 1e-4 * np.linalg.norm(g_want[lo:hi]), (lo, err)
 
 
+@pytest.mark.parametrize("n", [1, 17, 33, 4096])
+def test_grad_in_the_smallest_workspace(ch, cl, torch_dev, n):
+    """The least workspace of a batch (273 floats per sample and a partial
+    gradient per 64, in 256-byte parts): fewer blocks than groups at 33 and
+    4,096 samples; one byte less is refused."""
+    torch = torch_dev
+    rng = np.random.default_rng(71 + n)
+    X = rng.normal(size=(n, 20)).astype(np.float32)
+    T = rng.normal(size=(n, 15)).astype(np.float32)
+    p = (mlp_init(14) * 1.2).astype(np.float32)
+    up = lambda b: (b + 255) // 256 * 256
+    least = 4 * up(256 * n) + up(64 * n) + up(4 * n) + up(4 * 6480 * ((n + 63) // 64)) + 256
+    full = ch.closure_train_workspace(n).numel()
+    assert least <= full <= 1.3 * least
+    ws = torch.full((least + 4096,), 255, dtype=torch.uint8, device="cuda")
+    grad = torch.zeros(6479, dtype=torch.float32, device="cuda")
+    loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+    args = (_dev(torch, X, torch.float32), _dev(torch, T, torch.float32), _dev(torch, p, torch.float32), grad, loss)
+    with pytest.raises(ch.ChorusError):
+        ch.chorus_closure_grad(*args, ws[:least - 1])
+    ch.chorus_closure_grad(*args, ws[:least])
+    torch.cuda.synchronize()
+    assert bool((ws[least:] == 255).all())
+    g, g_want = grad.cpu().numpy().astype(np.float64), cl.grad(p, X, T)
+    assert abs(loss.item() - cl.loss(p, X, T)) <= 1e-5 * loss.item()
+    for lo, hi in ((0, 1280), (1280, 1344), (1344, 5440), (5440, 5504), (5504, 6464), (6464, 6479)):
+        err = np.linalg.norm(g[lo:hi] - g_want[lo:hi])
+        assert err <= 1e-4 * np.linalg.norm(g_want[lo:hi]), (lo, err)
+
+
 def test_train_matches_oracle_and_is_deterministic(ch, cl, torch_dev):
     torch = torch_dev
     rng = np.random.default_rng(31)
