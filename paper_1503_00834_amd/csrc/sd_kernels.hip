@@ -43,11 +43,19 @@ namespace chorus {
 template <int N, int EPB, int NT, bool SW = false>
 __device__ __forceinline__ void load_q(const double *__restrict__ Q, int64_t E, int64_t e0,
                                        double (*sq)[5][N * N * N]) {
-    constexpr int NP = N * N * N;
-    for (int it = threadIdx.x; it < EPB * 5 * NP; it += NT) {
-        const int el = it / (5 * NP), r = it % (5 * NP), v = r / NP, p = r % NP;
-        const int64_t e = e0 + el;
-        sq[el][v][SW ? lds_sol<N>(p) : p] = (e < E) ? Q[((int64_t)v * E + e) * NP + p] : (v == 0 || v == 4 ? 1.0 : 0.0);
+    // (every load before the first store; items past the end repeat the last)
+    constexpr int NP = N * N * N, TOT = EPB * 5 * NP, IT = (TOT + NT - 1) / NT;
+    double q[IT];
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+        const int it = min((int)threadIdx.x + k * NT, TOT - 1), v = it % (5 * NP) / NP;
+        const int64_t e = e0 + it / (5 * NP);
+        q[k] = Q[((int64_t)v * E + (EPB == 1 || e < E ? e : 0)) * NP + it % NP];
+    }
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+        const int it = min((int)threadIdx.x + k * NT, TOT - 1), el = it / (5 * NP), v = it % (5 * NP) / NP, p = it % NP;
+        sq[el][v][SW ? lds_sol<N>(p) : p] = (EPB == 1 || e0 + el < E) ? q[k] : (v == 0 || v == 4 ? 1.0 : 0.0);
     }
 }
 
@@ -139,8 +147,10 @@ __global__ __launch_bounds__(NT) void k_trace(Ops<N> opa, Geo G, const double *_
     __shared__ double sq[EPB][5][NP];
     const int64_t e0 = (int64_t)blockIdx.x * EPB;
     __shared__ Ops<N> op;
-    ops_to_lds(opa, op);
+    OpsWords<NT, double, N> ow;
+    ow.load(opa);
     load_q<N, EPB, NT>(Q, G.E, e0, sq);
+    ow.store(op);
     __syncthreads();
     for (int it = threadIdx.x; it < EPB * 6 * NF2; it += NT) {
         const int el = it / (6 * NF2), r = it % (6 * NF2), f = r / NF2, pp = r % NF2;
@@ -229,8 +239,10 @@ __global__ __launch_bounds__(NT) void k_features(Ops<N> opa, Geo G, PhysParams P
     __shared__ double sgr[EPB][15][NP];
     const int64_t e0 = (int64_t)blockIdx.x * EPB;
     __shared__ Ops<N> op;
-    ops_to_lds(opa, op);
+    OpsWords<NT, double, N> ow;
+    ow.load(opa);
     load_q<N, EPB, NT>(Q, G.E, e0, sq);
+    ow.store(op);
     __syncthreads();
     common_solution<N, EPB, NT>(op, G, P, TQ, e0, sq, sqs);
     __syncthreads();
