@@ -339,7 +339,8 @@ int chorus_closure_train_workspace_bytes(int64_t batch, size_t *bytes);
 /* Mean-squared-error loss over n samples (X_dev [n][20] normalised inputs,
  * Y_dev [n][15] normalised targets) and its gradient with respect to the
  * parameter vector: grad_dev [CHORUS_MLP_NPARAM], loss_dev [1] (device,
- * FP32, fixed summation order).  n <= the workspace's batch. */
+ * FP32, in a summation order that n alone fixes, whatever the workspace's
+ * size).  n <= the workspace's batch. */
 int chorus_closure_grad(const float *X_dev, const float *Y_dev, int64_t n, const float *params_dev,
                         float *grad_dev, float *loss_dev, void *ws, size_t ws_bytes, void *stream);
 /* `iters` Adam steps (Kingma & Ba 2015) on mini-batches: iteration i uses

@@ -1273,14 +1273,16 @@ int chorus_closure_infer(chorus_mesh_t mesh, const chorus_physics *phys, const d
     return CHORUS_OK;
 }
 
-// Training workspace: an index flag, then one partial gradient (row) per 16
-// samples, kTrainPartials at most.  `least` is what a call needs: the size
-// that callers of this library have planned with (activation rows and one
-// partial per 64 samples), always enough for one row.  Between 17 and about
-// 8,200 samples it is up to 30 % short of a row per block; a call then runs
-// fewer blocks, some taking two groups (batch 4,096: 236 blocks instead of
-// 256), and a workspace of the queried size runs them all.  Neither size
-// shrinks as the batch grows, so a workspace serves every smaller batch.
+// Training workspace: an index flag, then partial gradients (rows), one per
+// share of 16 samples, kTrainPartials shares at most.  `least` is what a call
+// needs: the size that callers of this library have planned with (activation
+// rows and one partial per 64 samples).  Between 17 and 8,853 samples it holds
+// fewer rows than there are shares (one of two at 17 samples, 236 of 256 at
+// 4,096; kTrainExtra short at most and never by more than half): there some
+// blocks work through two shares, with the same results
+// (launch_train_partials).  One of the queried size holds a row per share.
+// Neither size shrinks as the batch grows, so a workspace serves every smaller
+// batch.
 struct TrainLayout {
     size_t least, full;
 };
@@ -1295,11 +1297,17 @@ static TrainLayout train_layout(int64_t B) {
     return L;
 }
 
-static TrainBufs train_bufs(unsigned char *W, size_t ws_bytes, int64_t n_mean) {
+static int train_rows(size_t ws_bytes) {
+    return (int)std::min<size_t>((ws_bytes - kTrainPart) / kTrainRow, kTrainPartials);
+}
+
+static TrainBufs train_bufs(unsigned char *W, size_t ws_bytes, int64_t batch) {
     TrainBufs T;
     T.part = (float *)(W + kTrainPart);
-    T.rows = (int)std::min<size_t>((ws_bytes - kTrainPart) / kTrainRow, kTrainPartials);
-    T.n_mean = n_mean;
+    T.rows = train_rows(ws_bytes);
+    T.blocks = (int)std::min<int64_t>((batch + 15) / 16, kTrainPartials);
+    T.sums = std::min(T.blocks, train_rows(train_layout(batch).least));
+    T.n_mean = batch;
     return T;
 }
 

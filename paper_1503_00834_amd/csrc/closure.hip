@@ -12,8 +12,9 @@
 //   k_wgrad_sum  the blocks' partials summed (the gradient alone)
 //   k_wgrad_sum_adam  the partials summed and the Adam update (Kingma & Ba
 //                2015, with bias correction) applied at once (training)
-// (every sum in a fixed order: the matrix-core products in their instruction
-// order, the partials as eight interleaved running sums, then pairwise)
+// (every sum in an order that the batch size alone fixes: the matrix-core
+// products in their instruction order, the partials as eight interleaved
+// running sums, then pairwise)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -115,6 +116,11 @@ __device__ __forceinline__ int slot_unit(int tile, int u, int t) {
     return tile * kTileStride + (u >> 2) * kGrpStride + 4 * t + (u & 3);
 }
 
+// accumulated weight gradients of a share (see k_train)
+struct TrainSums {
+    f32x4_t W2[5], W1[2], W3[2];
+};
+
 // Forward, backward and weight gradients of one mini-batch.  A block of four
 // waves takes 16 samples at a time (blocks stride over the 16-sample groups);
 // wave w owns the hidden units 16 w .. 16 w + 15 of both hidden layers, so a
@@ -130,7 +136,9 @@ __device__ __forceinline__ int slot_unit(int tile, int u, int t) {
 // dZ1^T X, dW3 = dY^T H2 (row tile w each; dW3: column tile w), the bias
 // gradients with a column of ones (feature 20 of the padded X; one more
 // column tile for dW2 and dW3), the loss in the padding row 15 of dY^T.  Each
-// block writes its partial sums part[block][kMlpParams + 1].
+// of the nblk shares of the groups (every nblk-th) has its own partial sums.  A
+// block writes those of share blockIdx.x to part[block][kMlpParams + 1]; with
+// TWO it adds those of share blockIdx.x + gridDim.x, if there is one.
 //
 // What bounds it: a batch of 4,096 is 256 groups, one block per CU, and each
 // layer waits for the one before, so it is a chain of about 80 matrix
@@ -139,10 +147,11 @@ __device__ __forceinline__ int slot_unit(int tile, int u, int t) {
 // gradients sent through memory to a second kernel for the weight gradients,
 // took 13.4 + 11.6 us at batch 4,096; an iteration with its partial sums and
 // Adam went from 28.0 to 14.3 us.
-__global__ __launch_bounds__(256) void k_train(const float *__restrict__ X, const float *__restrict__ Y,
+template <bool TWO>
+__global__ __launch_bounds__(256, 2) void k_train(const float *__restrict__ X, const float *__restrict__ Y,
                                                const int32_t *__restrict__ idx, int64_t base, int nb,
                                                const float *__restrict__ W, float *__restrict__ part_all,
-                                               int64_t n_mean) {
+                                               int64_t n_mean, int nblk) {
     __shared__ __align__(16) float sH1[4 * kTileStride], sH2[4 * kTileStride], sZ1[4 * kTileStride],
         sZ2[4 * kTileStride], sYp[4 * 256], sdY[kTileStride], sloss[16];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
@@ -171,146 +180,170 @@ __global__ __launch_bounds__(256) void k_train(const float *__restrict__ X, cons
 #pragma unroll
     for (int i = 0; i < 4; ++i) b3[i] = (4 * g + i < kMlpOut) ? W[kB3 + 4 * g + i] : 0.0f;
     const f32x4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    f32x4_t gW2[5], gW1[2], gW3[2];
-#pragma unroll
-    for (int q = 0; q < 5; ++q) gW2[q] = zero;
-    gW1[0] = gW1[1] = gW3[0] = gW3[1] = zero;
     const float sc = 2.0f / ((float)n_mean * (float)kMlpOut);
-    for (int grp = blockIdx.x; grp < ngrp; grp += gridDim.x) {
-        // this lane's sample as a column (t) and, for dW1, as a K step;
-        // lanes past the batch compute on its first sample with zero weight
-        const int t = 16 * grp + c;
-        const bool ok = t < nb;
-        const int64_t s = idx ? (int64_t)idx[base + (ok ? t : 0)] : base + (ok ? t : 0);
-        int64_t sk[4];
+    const auto work = [&](int share) {
+        TrainSums G;
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const int tk = 16 * grp + 4 * ks + g;
-            sk[ks] = idx ? (int64_t)idx[base + (tk < nb ? tk : 0)] : base + (tk < nb ? tk : 0);
+        for (int q = 0; q < 5; ++q) G.W2[q] = zero;
+        G.W1[0] = G.W1[1] = G.W3[0] = G.W3[1] = zero;
+        for (int grp = share; grp < ngrp; grp += nblk) {
+            // this lane's sample as a column (t) and, for dW1, as a K step;
+            // lanes past the batch compute on its first sample with zero weight
+            const int t = 16 * grp + c;
+            const bool ok = t < nb;
+            const int64_t s = idx ? (int64_t)idx[base + (ok ? t : 0)] : base + (ok ? t : 0);
+            int64_t sk[4];
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const int tk = 16 * grp + 4 * ks + g;
+                sk[ks] = idx ? (int64_t)idx[base + (tk < nb ? tk : 0)] : base + (tk < nb ? tk : 0);
+            }
+            float x1[5], xk[4][2], yt[4];
+#pragma unroll
+            for (int ks = 0; ks < 5; ++ks) x1[ks] = X[s * kMlpIn + 4 * ks + g];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) yt[i] = Y[s * kMlpOut + (4 * g + i < kMlpOut ? 4 * g + i : 0)];
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                xk[ks][0] = X[sk[ks] * kMlpIn + c];
+                xk[ks][1] = X[sk[ks] * kMlpIn + (c < 4 ? 16 + c : 0)];
+                if (c >= 4) xk[ks][1] = (c == 4) ? 1.0f : 0.0f;
+            }
+            // layer 1
+            f32x4_t h1 = b1, p1, h2 = b2, p2;
+#pragma unroll
+            for (int ks = 0; ks < 5; ++ks) h1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[ks], x1[ks], h1, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float h, gp;
+                gelu_and_prime(h1[i], h, gp);
+                h1[i] = h;
+                p1[i] = gp;
+            }
+            *reinterpret_cast<f32x4_t *>(sH1 + slot_of(w, g, c)) = h1;
+            __syncthreads();
+            // layer 2
+#pragma unroll
+            for (int kt = 0; kt < 4; ++kt) {
+                const f32x4_t b = *reinterpret_cast<const f32x4_t *>(sH1 + slot_of(kt, g, c));
+#pragma unroll
+                for (int ki = 0; ki < 4; ++ki) h2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a2f[kt][ki], b[ki], h2, 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float h, gp;
+                gelu_and_prime(h2[i], h, gp);
+                h2[i] = h;
+                p2[i] = gp;
+            }
+            *reinterpret_cast<f32x4_t *>(sH2 + slot_of(w, g, c)) = h2;
+            // layer 3: each wave its own units' part of the outputs 4 g + i (row
+            // 15 padding), summed over the waves in a fixed order
+            f32x4_t yp = zero;
+#pragma unroll
+            for (int ki = 0; ki < 4; ++ki) yp = __builtin_amdgcn_mfma_f32_16x16x4f32(a3f[ki], h2[ki], yp, 0, 0, 0);
+            *reinterpret_cast<f32x4_t *>(sYp + 256 * w + 4 * lane) = yp;
+            __syncthreads();
+            f32x4_t q[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const f32x4_t *>(sYp + 256 * u + 4 * lane);
+            const f32x4_t y = ((q[0] + q[1]) + (q[2] + q[3])) + b3;
+            f32x4_t dy;
+            float l = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float e = (ok && 4 * g + i < kMlpOut) ? y[i] - yt[i] : 0.0f;
+                l += e * e;
+                dy[i] = sc * e;
+            }
+            if (w == 0) {
+                // the sample's loss: the four lane groups in a fixed order
+                const float l1 = __shfl_xor(l, 16), l2 = __shfl_xor(l, 32), l3 = __shfl_xor(l, 48);
+                *reinterpret_cast<f32x4_t *>(sdY + slot_of(0, g, c)) = dy;
+                if (g == 0) sloss[c] = (l + l1) + (l2 + l3);
+            }
+            // back through layer 3 and layer 2
+            f32x4_t dz2 = zero, dz1 = zero;
+#pragma unroll
+            for (int ki = 0; ki < 4; ++ki) dz2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a3b[ki], dy[ki], dz2, 0, 0, 0);
+            dz2 *= p2;
+            *reinterpret_cast<f32x4_t *>(sZ2 + slot_of(w, g, c)) = dz2;
+            __syncthreads();
+#pragma unroll
+            for (int kt = 0; kt < 4; ++kt) {
+                const f32x4_t b = *reinterpret_cast<const f32x4_t *>(sZ2 + slot_of(kt, g, c));
+#pragma unroll
+                for (int ki = 0; ki < 4; ++ki)
+                    dz1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a2b[4 * kt + ki], b[ki], dz1, 0, 0, 0);
+            }
+            dz1 *= p1;
+            // (read back by this wave alone)
+            *reinterpret_cast<f32x4_t *>(sZ1 + slot_of(w, g, c)) = dz1;
+            __builtin_amdgcn_wave_barrier();
+            // weight gradients over the group's samples
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const int tk = 4 * ks + g;
+                const float z2 = sZ2[slot_unit(w, c, tk)], one = (c == 0) ? 1.0f : 0.0f;
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt)
+                    G.W2[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(z2, sH1[slot_unit(nt, c, tk)], G.W2[nt], 0, 0, 0);
+                G.W2[4] = __builtin_amdgcn_mfma_f32_16x16x4f32(z2, one, G.W2[4], 0, 0, 0);
+                const float ys = (c < kMlpOut) ? sdY[slot_unit(0, c, tk)] : sloss[tk];
+                G.W3[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(ys, sH2[slot_unit(w, c, tk)], G.W3[0], 0, 0, 0);
+                if (w == 0) G.W3[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(ys, one, G.W3[1], 0, 0, 0);
+                const float z1 = sZ1[slot_unit(w, c, tk)];
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt)
+                    G.W1[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(z1, xk[ks][nt], G.W1[nt], 0, 0, 0);
+            }
+            __syncthreads();  // the next group rewrites the LDS images
         }
-        float x1[5], xk[4][2], yt[4];
+        return G;
+    };
+    TrainSums G = work(blockIdx.x);
+    if constexpr (TWO) {
+        if ((int)(blockIdx.x + gridDim.x) < nblk) {
+            const TrainSums H = work(blockIdx.x + gridDim.x);
 #pragma unroll
-        for (int ks = 0; ks < 5; ++ks) x1[ks] = X[s * kMlpIn + 4 * ks + g];
+            for (int q = 0; q < 5; ++q) G.W2[q] += H.W2[q];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) yt[i] = Y[s * kMlpOut + (4 * g + i < kMlpOut ? 4 * g + i : 0)];
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            xk[ks][0] = X[sk[ks] * kMlpIn + c];
-            xk[ks][1] = X[sk[ks] * kMlpIn + (c < 4 ? 16 + c : 0)];
-            if (c >= 4) xk[ks][1] = (c == 4) ? 1.0f : 0.0f;
+            for (int q = 0; q < 2; ++q) {
+                G.W1[q] += H.W1[q];
+                G.W3[q] += H.W3[q];
+            }
         }
-        // layer 1
-        f32x4_t h1 = b1, p1, h2 = b2, p2;
-#pragma unroll
-        for (int ks = 0; ks < 5; ++ks) h1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[ks], x1[ks], h1, 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float h, gp;
-            gelu_and_prime(h1[i], h, gp);
-            h1[i] = h;
-            p1[i] = gp;
-        }
-        *reinterpret_cast<f32x4_t *>(sH1 + slot_of(w, g, c)) = h1;
-        __syncthreads();
-        // layer 2
-#pragma unroll
-        for (int kt = 0; kt < 4; ++kt) {
-            const f32x4_t b = *reinterpret_cast<const f32x4_t *>(sH1 + slot_of(kt, g, c));
-#pragma unroll
-            for (int ki = 0; ki < 4; ++ki) h2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a2f[kt][ki], b[ki], h2, 0, 0, 0);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float h, gp;
-            gelu_and_prime(h2[i], h, gp);
-            h2[i] = h;
-            p2[i] = gp;
-        }
-        *reinterpret_cast<f32x4_t *>(sH2 + slot_of(w, g, c)) = h2;
-        // layer 3: each wave its own units' part of the outputs 4 g + i (row
-        // 15 padding), summed over the waves in a fixed order
-        f32x4_t yp = zero;
-#pragma unroll
-        for (int ki = 0; ki < 4; ++ki) yp = __builtin_amdgcn_mfma_f32_16x16x4f32(a3f[ki], h2[ki], yp, 0, 0, 0);
-        *reinterpret_cast<f32x4_t *>(sYp + 256 * w + 4 * lane) = yp;
-        __syncthreads();
-        f32x4_t q[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const f32x4_t *>(sYp + 256 * u + 4 * lane);
-        const f32x4_t y = ((q[0] + q[1]) + (q[2] + q[3])) + b3;
-        f32x4_t dy;
-        float l = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float e = (ok && 4 * g + i < kMlpOut) ? y[i] - yt[i] : 0.0f;
-            l += e * e;
-            dy[i] = sc * e;
-        }
-        if (w == 0) {
-            // the sample's loss: the four lane groups in a fixed order
-            const float l1 = __shfl_xor(l, 16), l2 = __shfl_xor(l, 32), l3 = __shfl_xor(l, 48);
-            *reinterpret_cast<f32x4_t *>(sdY + slot_of(0, g, c)) = dy;
-            if (g == 0) sloss[c] = (l + l1) + (l2 + l3);
-        }
-        // back through layer 3 and layer 2
-        f32x4_t dz2 = zero, dz1 = zero;
-#pragma unroll
-        for (int ki = 0; ki < 4; ++ki) dz2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a3b[ki], dy[ki], dz2, 0, 0, 0);
-        dz2 *= p2;
-        *reinterpret_cast<f32x4_t *>(sZ2 + slot_of(w, g, c)) = dz2;
-        __syncthreads();
-#pragma unroll
-        for (int kt = 0; kt < 4; ++kt) {
-            const f32x4_t b = *reinterpret_cast<const f32x4_t *>(sZ2 + slot_of(kt, g, c));
-#pragma unroll
-            for (int ki = 0; ki < 4; ++ki)
-                dz1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a2b[4 * kt + ki], b[ki], dz1, 0, 0, 0);
-        }
-        dz1 *= p1;
-        // (read back by this wave alone)
-        *reinterpret_cast<f32x4_t *>(sZ1 + slot_of(w, g, c)) = dz1;
-        __builtin_amdgcn_wave_barrier();
-        // weight gradients over the group's samples
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const int tk = 4 * ks + g;
-            const float z2 = sZ2[slot_unit(w, c, tk)], one = (c == 0) ? 1.0f : 0.0f;
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
-                gW2[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(z2, sH1[slot_unit(nt, c, tk)], gW2[nt], 0, 0, 0);
-            gW2[4] = __builtin_amdgcn_mfma_f32_16x16x4f32(z2, one, gW2[4], 0, 0, 0);
-            const float ys = (c < kMlpOut) ? sdY[slot_unit(0, c, tk)] : sloss[tk];
-            gW3[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(ys, sH2[slot_unit(w, c, tk)], gW3[0], 0, 0, 0);
-            if (w == 0) gW3[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(ys, one, gW3[1], 0, 0, 0);
-            const float z1 = sZ1[slot_unit(w, c, tk)];
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-                gW1[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(z1, xk[ks][nt], gW1[nt], 0, 0, 0);
-        }
-        __syncthreads();  // the next group rewrites the LDS images
     }
     float *part = part_all + (int64_t)blockIdx.x * (kMlpParams + 1);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int j = 16 * w + 4 * g + i;
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) part[kW2 + j * kMlpHid + 16 * nt + c] = gW2[nt][i];
-        if (c == 0) part[kB2 + j] = gW2[4][i];
-        part[kW1 + j * kMlpIn + c] = gW1[0][i];
-        if (c < 4) part[kW1 + j * kMlpIn + 16 + c] = gW1[1][i];
-        if (c == 4) part[kB1 + j] = gW1[1][i];
+        for (int nt = 0; nt < 4; ++nt) part[kW2 + j * kMlpHid + 16 * nt + c] = G.W2[nt][i];
+        if (c == 0) part[kB2 + j] = G.W2[4][i];
+        part[kW1 + j * kMlpIn + c] = G.W1[0][i];
+        if (c < 4) part[kW1 + j * kMlpIn + 16 + c] = G.W1[1][i];
+        if (c == 4) part[kB1 + j] = G.W1[1][i];
         const int k = 4 * g + i;
-        if (k < kMlpOut) part[kW3 + k * kMlpHid + 16 * w + c] = gW3[0][i];
-        if (w == 0 && c == 0) part[k < kMlpOut ? kB3 + k : kMlpParams] = gW3[1][i];
+        if (k < kMlpOut) part[kW3 + k * kMlpHid + 16 * w + c] = G.W3[0][i];
+        if (w == 0 && c == 0) part[k < kMlpOut ? kB3 + k : kMlpParams] = G.W3[1][i];
     }
 }
 
 // sum over the blocks' partials of 64 consecutive quantities (one per lane:
-// whole cache lines) in a fixed order: wave r of the block sums partials r,
-// r + 8, ... in turn, the eight sums combined pairwise; valid in wave 0
-__device__ __forceinline__ float partial_sum(int nchunk, const float *__restrict__ part, int q, float (*red)[64]) {
+// whole cache lines) in a fixed order: partial c < nextra takes partial c +
+// nchunk first; wave r of the block sums partials r, r + 8, ... in turn, the
+// eight sums combined pairwise; valid in wave 0
+__device__ __forceinline__ float partial_sum(int nchunk, int nextra, const float *__restrict__ part, int q,
+                                             float (*red)[64]) {
     const int r = threadIdx.x >> 6, lane = threadIdx.x & 63;
     float a = 0.0f;
+    float x[kTrainExtra / 8];
+#pragma unroll
+    for (int u = 0; u < kTrainExtra / 8; ++u) {
+        const int c = r + 8 * u;
+        x[u] = part[(int64_t)(c < nextra ? c + nchunk : 0) * (kMlpParams + 1) + q];
+    }
     // 16 partials per wave and round, every load of a round issued first
     for (int c0 = r; c0 < nchunk; c0 += 128) {
         float v[16];
@@ -320,8 +353,11 @@ __device__ __forceinline__ float partial_sum(int nchunk, const float *__restrict
             v[u] = part[(int64_t)(c < nchunk ? c : c0) * (kMlpParams + 1) + q];
         }
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
-            if (c0 + 8 * u < nchunk) a += v[u];
+        for (int u = 0; u < 16; ++u) {
+            const int c = c0 + 8 * u;
+            if (u < kTrainExtra / 8 && c < nextra) v[u] += x[u < kTrainExtra / 8 ? u : 0];
+            if (c < nchunk) a += v[u];
+        }
     }
     red[r][lane] = a;
     __syncthreads();
@@ -330,11 +366,11 @@ __device__ __forceinline__ float partial_sum(int nchunk, const float *__restrict
 }
 
 // one lane per quantity (parameter, or the loss for q = kMlpParams)
-__global__ __launch_bounds__(512) void k_wgrad_sum(int nchunk, const float *__restrict__ part, int64_t n_mean,
-                                                   float *__restrict__ grad, float *__restrict__ loss) {
+__global__ __launch_bounds__(512) void k_wgrad_sum(int nchunk, int nextra, const float *__restrict__ part,
+                                                   int64_t n_mean, float *__restrict__ grad, float *__restrict__ loss) {
     __shared__ float red[8][64];
     const int qq = blockIdx.x * 64 + (int)(threadIdx.x & 63), q = qq <= kMlpParams ? qq : kMlpParams;
-    const float s = partial_sum(nchunk, part, q, red);
+    const float s = partial_sum(nchunk, nextra, part, q, red);
     if (threadIdx.x >= 64 || qq > kMlpParams) return;
     if (q < kMlpParams) grad[q] = s;
     else loss[0] = s / ((float)n_mean * (float)kMlpOut);
@@ -349,12 +385,12 @@ __device__ __forceinline__ void adam_update(float *__restrict__ W, float *__rest
     W[q] -= a.lr * (mq * a.inv_bc1) / (sqrtf(vq * a.inv_bc2) + a.eps);
 }
 
-__global__ __launch_bounds__(512) void k_wgrad_sum_adam(int nchunk, const float *__restrict__ part, int64_t n_mean,
-                                                        float *__restrict__ W, float *__restrict__ m,
+__global__ __launch_bounds__(512) void k_wgrad_sum_adam(int nchunk, int nextra, const float *__restrict__ part,
+                                                        int64_t n_mean, float *__restrict__ W, float *__restrict__ m,
                                                         float *__restrict__ v, AdamArgs a, float *__restrict__ loss) {
     __shared__ float red[8][64];
     const int qq = blockIdx.x * 64 + (int)(threadIdx.x & 63), q = qq <= kMlpParams ? qq : kMlpParams;
-    const float s = partial_sum(nchunk, part, q, red);
+    const float s = partial_sum(nchunk, nextra, part, q, red);
     if (threadIdx.x >= 64 || qq > kMlpParams) return;
     if (q < kMlpParams) adam_update(W, m, v, s, a, q);
     else loss[0] = s / ((float)n_mean * (float)kMlpOut);
@@ -510,30 +546,42 @@ hipError_t launch_pack(const float *W, const float *norm, unsigned char *model, 
     return hipGetLastError();
 }
 
-// blocks of k_train for a mini-batch: one per 16 samples up to the partials
-// of the workspace, beyond which a block takes several groups in turn
-static int train_blocks(int nb, const TrainBufs &T) { return std::min((nb + 15) / 16, T.rows); }
+// The groups of a mini-batch go to T.blocks shares (one group each up to
+// kTrainPartials) that are summed as T.sums partials, the first (blocks - sums)
+// of which take a second share's: both numbers follow from the batch alone.
+// Where the workspace holds a row for every share, each is a block of k_train
+// and the sum adds the second rows; where it does not, the first blocks work
+// through two shares: the same sums.
+static hipError_t launch_train_partials(const float *X, const float *Y, const int32_t *idx, int64_t base, int nb,
+                                        const float *W, const TrainBufs &T, int &nextra, hipStream_t s) {
+    nextra = T.rows >= T.blocks ? T.blocks - T.sums : 0;
+    if (T.sums + nextra == T.blocks)
+        hipLaunchKernelGGL(k_train<false>, dim3(T.blocks), dim3(256), 0, s, X, Y, idx, base, nb, W, T.part, T.n_mean,
+                           T.blocks);
+    else
+        hipLaunchKernelGGL(k_train<true>, dim3(T.sums), dim3(256), 0, s, X, Y, idx, base, nb, W, T.part, T.n_mean,
+                           T.blocks);
+    return hipGetLastError();
+}
 static constexpr int kSumBlocksMlp = (kMlpParams + 1 + 63) / 64;
 
 hipError_t launch_train_grad(const float *X, const float *Y, const int32_t *idx, int64_t base, int nb,
                              const float *W, const TrainBufs &T, float *grad, float *loss, hipStream_t s) {
-    const int nblk = train_blocks(nb, T);
-    hipLaunchKernelGGL(k_train, dim3(nblk), dim3(256), 0, s, X, Y, idx, base, nb, W, T.part, T.n_mean);
-    hipError_t e = hipGetLastError();
+    int nextra = 0;
+    hipError_t e = launch_train_partials(X, Y, idx, base, nb, W, T, nextra, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wgrad_sum, dim3(kSumBlocksMlp), dim3(512), 0, s, nblk, (const float *)T.part, T.n_mean, grad,
-                       loss);
+    hipLaunchKernelGGL(k_wgrad_sum, dim3(kSumBlocksMlp), dim3(512), 0, s, T.sums, nextra, (const float *)T.part,
+                       T.n_mean, grad, loss);
     return hipGetLastError();
 }
 
 hipError_t launch_train_step(const float *X, const float *Y, const int32_t *idx, int64_t base, int nb, float *W,
                              float *m, float *v, const TrainBufs &T, const AdamArgs &a, float *loss, hipStream_t s) {
-    const int nblk = train_blocks(nb, T);
-    hipLaunchKernelGGL(k_train, dim3(nblk), dim3(256), 0, s, X, Y, idx, base, nb, W, T.part, T.n_mean);
-    hipError_t e = hipGetLastError();
+    int nextra = 0;
+    hipError_t e = launch_train_partials(X, Y, idx, base, nb, W, T, nextra, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_wgrad_sum_adam, dim3(kSumBlocksMlp), dim3(512), 0, s, nblk, (const float *)T.part, T.n_mean, W,
-                       m, v, a, loss);
+    hipLaunchKernelGGL(k_wgrad_sum_adam, dim3(kSumBlocksMlp), dim3(512), 0, s, T.sums, nextra, (const float *)T.part,
+                       T.n_mean, W, m, v, a, loss);
     return hipGetLastError();
 }
 

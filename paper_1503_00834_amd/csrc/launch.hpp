@@ -68,10 +68,13 @@ hipError_t launch_lift64(const Mesh &m, const Geo &G, const double *TV, const St
                          hipStream_t s);
 
 // closure training: the partial gradients and losses of one mini-batch
-constexpr int kTrainPartials = 512;  // partials at most (blocks of k_train)
+constexpr int kTrainPartials = 512;  // shares of a mini-batch at most
+constexpr int kTrainExtra = 40;      // blocks - sums at most
 struct TrainBufs {
     float *part;     // [rows][6480]
     int rows;        // partials that the workspace holds, kTrainPartials at most
+    int blocks;      // shares: one per 16 samples, kTrainPartials at most
+    int sums;        // partials of the final sum: the rows of the smallest workspace, blocks at most
     int64_t n_mean;  // samples the loss is averaged over
 };
 

@@ -348,6 +348,44 @@ def test_grad_in_the_smallest_workspace(ch, cl, torch_dev, n):
         assert err <= 1e-4 * np.linalg.norm(g_want[lo:hi]), (lo, err)
 
 
+def _least_train_workspace(n):
+    """Bytes a batch of n samples needs: 273 floats per sample and a partial
+    gradient of 6,480 floats per 64, in 256-byte parts."""
+    up = lambda b: (b + 255) // 256 * 256
+    return 4 * up(256 * n) + up(64 * n) + up(4 * n) + up(4 * 6480 * ((n + 63) // 64)) + 256
+
+
+@pytest.mark.parametrize("n", [16, 17, 33, 1000, 4096, 8188, 8853, 17000])
+def test_training_does_not_depend_on_the_workspace_size(ch, cl, torch_dev, n):
+    """The batch alone fixes the order of the sums: gradients, losses and an
+    Adam trajectory are bitwise the same in the smallest workspace (rows for
+    fewer blocks than the batch has from 17 to 8,853 samples, 40 too few at
+    8,188), in one with a row more, in one of the queried size and in one of a
+    larger batch; and the gradient is the oracle's."""
+    torch = torch_dev
+    rng = np.random.default_rng(81 + n)
+    X = _dev(torch, rng.normal(size=(n, 20)), torch.float32)
+    T = _dev(torch, rng.normal(size=(n, 15)), torch.float32)
+    p = _dev(torch, mlp_init(14) * 1.2, torch.float32)
+    idx = torch.from_numpy(rng.integers(0, n, 3 * n).astype(np.int32)).cuda()
+    least = _least_train_workspace(n)
+    full = ch.closure_train_workspace(n).numel()
+    outs = []
+    for size in (least, least + 4 * 6480, full, _least_train_workspace(1 << 16)):
+        ws = torch.full((size,), 255, dtype=torch.uint8, device="cuda")
+        grad, loss = torch.zeros(6479, device="cuda"), torch.zeros(1, device="cuda")
+        ch.chorus_closure_grad(X, T, p, grad, loss, ws)
+        q, m, v, L = p.clone(), torch.zeros_like(p), torch.zeros_like(p), torch.zeros(3, device="cuda")
+        ch.chorus_closure_train(X, T, idx, n, 3, q, m, v, 0, (1e-3, 0.9, 0.999, 1e-8), L, ws)
+        torch.cuda.synchronize()
+        outs.append((grad, loss, q, m, v, L))
+    for other in outs[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(outs[0], other))
+    g, want = outs[0][0].cpu().numpy().astype(np.float64), cl.grad(*(t.cpu().numpy() for t in (p, X, T)))
+    for lo, hi in ((0, 1280), (1280, 1344), (1344, 5440), (5440, 5504), (5504, 6464), (6464, 6479)):
+        assert np.linalg.norm(g[lo:hi] - want[lo:hi]) <= 1e-4 * np.linalg.norm(want[lo:hi]), lo
+
+
 def test_train_matches_oracle_and_is_deterministic(ch, cl, torch_dev):
     torch = torch_dev
     rng = np.random.default_rng(31)
