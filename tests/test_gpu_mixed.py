@@ -243,6 +243,56 @@ def test_mixed_ragged_last_block(ch, oracle_mod, torch_dev, N):
         assert errq <= 2e-5 * np.linalg.norm(Qr[v] - Qs[v]) + 1e-13 * np.linalg.norm(Qr[v]), (v, errq)
 
 
+@pytest.mark.parametrize("N,epb,size", [(2, 8, (13, 7)), (2, 8, (15, 7)), (3, 2, (13, 13, 15))])
+def test_mixed_ragged_last_block_on_large_meshes(ch, oracle_mod, torch_dev, N, epb, size):
+    """Element counts that the element passes' blocks (epb elements) do not
+    divide, above the sizes of the wide flux pass (20 and 9 elements per CU of
+    256; the second and third above the wide lift pass too): shells at order 2,
+    a slab between an inner and an outer wall at order 3; residual and two
+    SSPRK(5,4) steps, the last block on its own too."""
+    from chorus_inputs import walled_slab_mesh
+    torch = torch_dev
+    rng = np.random.default_rng(10)
+    if len(size) == 2:
+        beta = 0.7
+        m = cubed_sphere_shell(*size, beta / (1 - beta), 1 / (1 - beta))
+        om = oracle_mod.OracleMesh(m, N)
+        Q0, pars = om.polytrope(beta, 1.0)
+        GM, T_top = pars["GM"], pars["chi_o"]
+    else:
+        m = walled_slab_mesh(*size, (1.0, 1.1, 0.9), 1, 2)
+        om = oracle_mod.OracleMesh(m, N)
+        x = om.solpts()[0].reshape(3, om.E, om.np)
+        Q0 = np.zeros((5, om.E, om.np))
+        Q0[0], Q0[4] = 1.3 - 0.3 * x[0], 2.5 - 0.5 * x[0]
+        GM, T_top = 0.0, 1.3
+    assert om.E % epb != 0 and om.E > 256 * {2: 20, 3: 9}[N]
+    Q = Q0.copy()
+    Q[0] *= np.exp(-1e-3 * rng.uniform(-1, 1, size=Q[0].shape))
+    Q[1:4] = 1e-3 * Q[0] * rng.uniform(-1, 1, size=Q[1:4].shape)
+    Q[4] += 0.5 * (Q[1:4] ** 2).sum(0) / Q[0]
+    kw = dict(GM=GM, omega=1.0, nu=1e-3, kappa=1e-3, kappa_r=1e-4, T_top=T_top, F_bottom=0.01)
+    phys = ch.physics(precision=ch.CHORUS_MIXED, integrator=ch.CHORUS_SSPRK54, **kw)
+    cm = ch.mesh_from_arrays(m, N).upload()
+    ws = cm.workspace(phys)
+    ch.chorus_set_background(cm, phys, _dev(torch, Q0), ws)
+    R, Qd, dt = torch.empty_like(_dev(torch, Q)), _dev(torch, Q), 1e-3
+    ch.chorus_sd_residual(cm, phys, Qd, R, ws)
+    ch.chorus_rk_step(cm, phys, Qd, dt, 2, ws)
+    torch.cuda.synchronize()
+    op = oracle_mod.phys(**kw)
+    Rg, Rr, Rb = R.cpu().numpy(), om.residual(op, Q).reshape(5, -1), om.residual(op, Q0).reshape(5, -1)
+    assert_mixed(Rg, Rr, Rb, "N=%d E=%d" % (N, om.E))
+    Qg, Qr, Qs = Qd.cpu().numpy(), om.ssp54(op, Q, dt, 2).reshape(5, -1), Q.reshape(5, -1)
+    last = slice((om.E - om.E % epb) * om.np, om.E * om.np)
+    for v in range(5):
+        assert np.abs(Rg[v, last] - Rr[v, last]).max() <= 1e-4 * np.abs(Rr[v] - Rb[v]).max() + \
+            1e-6 * np.abs(Rb[v]).max(), v
+        for part in (slice(None), last):
+            err = np.linalg.norm(Qg[v, part] - Qr[v, part])
+            assert err <= 2e-5 * np.linalg.norm(Qr[v, part] - Qs[v, part]) + 1e-13 * np.linalg.norm(Qr[v, part]), (v, err)
+
+
 @pytest.mark.parametrize("N,panel_n,radial_n", [
     (2, 13, 5), (2, 12, 6), (2, 14, 6), (2, 14, 7), (3, 11, 2), (3, 13, 2), (3, 14, 2), (4, 9, 1), (4, 6, 3),
     (4, 8, 4), (4, 10, 3), (5, 4, 2), (5, 9, 1), (5, 8, 2), (5, 7, 3), (6, 4, 2), (6, 5, 2)])
