@@ -69,6 +69,45 @@ def test_balanced_fp64_matches_oracle(ch, oracle_mod, torch_dev, N):
     assert_parity(Rg, ref, pert, "balanced fp64 N=%d" % N)
 
 
+@pytest.mark.parametrize("N,panel_n,radial_n", [(3, 13, 3), (4, 13, 2), (6, 9, 2)])
+def test_balanced_fp64_on_large_meshes(ch, oracle_mod, torch_dev, N, panel_n, radial_n):
+    """The same in the element passes (shells above 10, 7 and 3 elements per
+    CU of 256), and one SSPRK(5,4) step, whose fourth stage writes two
+    registers: the oracle's stage sums with R(Q) - R(Q0) written out."""
+    from test_gpu_parity import assert_parity, perturbed_oracle, ulp_perturb
+    torch = torch_dev
+    beta, dt = 0.7, 1e-3
+    m = cubed_sphere_shell(panel_n, radial_n, beta / (1 - beta), 1 / (1 - beta))
+    om = oracle_mod.OracleMesh(m, N)
+    assert om.E > 256 * {3: 10, 4: 7, 6: 3}[N]
+    Q0, pars = om.polytrope(beta, 1.0)
+    Q, _ = om.polytrope(beta, 1.0, noise=uniform_noise(om.n_solpts, 4), amp=1e-3)
+    rng = np.random.default_rng(5)
+    Q[1:4] = 1e-3 * Q[0] * rng.uniform(-1, 1, size=Q[1:4].shape)
+    Q[4] += 0.5 * (Q[1:4] ** 2).sum(0) / Q[0]
+    kw = dict(GM=pars["GM"], omega=1.0, nu=1e-3, kappa=1e-3, kappa_r=1e-4, T_top=pars["chi_o"], F_bottom=0.01)
+    phys = ch.physics(flags=ch.CHORUS_BALANCED, integrator=ch.CHORUS_SSPRK54, **kw)
+    cm = ch.mesh_from_arrays(m, N).upload()
+    Rg, ws = _balanced_residual(ch, torch, cm, phys, Q0, Q)
+    Qd = _dev(torch, Q)
+    ch.chorus_rk_step(cm, phys, Qd, dt, 1, ws)
+    torch.cuda.synchronize()
+    op = oracle_mod.phys(**kw)
+    alpha, bet = oracle_mod.ssp54_table()
+
+    def both(mesh, q, q0):
+        r0 = mesh.residual(op, q0)
+        u, L = [q], []
+        for i in range(5):
+            L.append(mesh.residual(op, u[i]) - r0)
+            u.append(sum(alpha[i, k] * u[k] + dt * bet[i, k] * L[k] for k in range(i + 1)))
+        return L[0], (u[5] - q).reshape(5, -1)
+    ref, step = both(om, Q, Q0)
+    pert, pstep = both(perturbed_oracle(oracle_mod, m, N), ulp_perturb(Q), ulp_perturb(Q0, seed=9))
+    assert_parity(Rg, ref, pert, "balanced fp64 N=%d E=%d" % (N, om.E))
+    assert_parity(Qd.cpu().numpy() - Q.reshape(5, -1), step, pstep, "balanced step N=%d E=%d" % (N, om.E))
+
+
 @pytest.mark.parametrize("N", [3, 4])
 def test_balanced_mixed_matches_oracle(ch, oracle_mod, torch_dev, N):
     """Mixed: the FP32 perturbation residual alone against the oracle's

@@ -200,6 +200,44 @@ def test_closure_odd_element_count(ch, cl, oracle_mod, torch_dev):
     assert np.linalg.norm(R_cl[1:] - R_pl[1:]) > 1e-3 * np.linalg.norm(R_pl[1:])
 
 
+def test_closure_on_a_large_mesh(ch, cl, oracle_mod, torch_dev):
+    """2,873 hexes, above the wide lift pass (10 elements per CU of 256) and odd
+    (the last block of two elements holds one): the closure residual against
+    the oracle (a wrong last element would be 1.9e-2 of the closure's part, ten
+    times the bound)."""
+    torch = torch_dev
+    m = box_mesh(13, 13, 17, periodic=(True,) * 3, curve=0.01)
+    om = oracle_mod.OracleMesh(m, 3)
+    assert om.E == 2873
+    x, y, z = om.solpts()[0]
+    rho = 1 + 0.2 * np.sin(2 * np.pi * (x + y))
+    u = np.stack([0.3 * np.cos(2 * np.pi * z), -0.2 * np.sin(2 * np.pi * x), 0.25 * np.cos(2 * np.pi * y)])
+    Q = np.stack([rho, rho * u[0], rho * u[1], rho * u[2],
+                  2.5 + 0.1 * np.sin(2 * np.pi * z) + 0.5 * rho * (u ** 2).sum(0)]).reshape(5, om.E, om.np)
+    kw = dict(nu=1e-3, kappa=1e-3)
+    ph_o = oracle_mod.phys(**kw)
+    params = mlp_init(14) * 1.5
+    norm = _norm_from(cl, cl.features(om, ph_o, Q))
+    norm[40:70] *= 2e-3  # a subgrid flux of the flux's own size
+    model = ch.chorus_closure_pack(_dev(torch, params, torch.float32), _dev(torch, norm, torch.float32))
+    phys = ch.physics(closure=ch.CHORUS_CLOSURE_MLP, closure_model=model, **kw)
+    cm = ch.mesh_from_arrays(m, 3).upload()
+    ws = cm.workspace(phys)
+    Qd = _dev(torch, Q.reshape(5, -1))
+    Rd = torch.empty_like(Qd)
+    ch.chorus_sd_residual(cm, phys, Qd, Rd, ws)
+    torch.cuda.synchronize()
+    want = om.residual(ph_o, Q, cl.sgs_field(om, ph_o, Q, params, norm))
+    plain = om.residual(ph_o, Q)
+    Rg = Rd.cpu().numpy().reshape(5, om.E, om.np)
+    for v in range(5):
+        d = np.linalg.norm(want[v] - plain[v])
+        err = np.linalg.norm(Rg[v] - want[v])
+        assert err <= 2e-3 * d + 1e-11 * np.linalg.norm(want[v]), (v, err, d)
+    # the mass part of the subgrid flux (the lift's fifth component) counts
+    assert np.linalg.norm(want[0] - plain[0]) > 1e-2 * np.linalg.norm(plain[0])
+
+
 def test_closure_rk_steps_match_oracle(ch, cl, oracle_mod, torch_dev):
     """Two SSP-RK3 steps with the closure re-evaluated at every stage."""
     torch = torch_dev

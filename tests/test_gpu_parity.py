@@ -16,7 +16,7 @@ reference norm and to the floor, and which bound applied.
 import numpy as np
 import pytest
 
-from chorus_inputs import box_mesh, cubed_sphere_shell, two_element_mesh, uniform_noise
+from chorus_inputs import Hex20Mesh, box_mesh, cubed_sphere_shell, two_element_mesh, uniform_noise
 
 pytestmark = pytest.mark.gpu
 
@@ -540,6 +540,90 @@ def test_residual_parity_orientations(ch, oracle_mod, torch_dev, rot):
     Qo = Q.reshape(5, om.E, om.np)
     Rp = perturbed_oracle(oracle_mod, m, 3).residual(op, ulp_perturb(Qo))
     assert_parity(R, om.residual(op, Qo), Rp, "rot %d" % rot)
+
+
+def _joined(meshes):
+    """One mesh of several separate ones."""
+    off = np.cumsum([0] + [m.n_nodes for m in meshes])
+    cat = lambda f: np.concatenate([f(m, o) for m, o in zip(meshes, off)])
+    return Hex20Mesh(xyz=cat(lambda m, o: m.xyz), elem20=cat(lambda m, o: m.elem20 + o),
+                     face_bc=cat(lambda m, o: m.face_bc), match_id=cat(lambda m, o: m.match_id + o))
+
+
+def _parity_of_residual_and_step(ch, oracle_mod, torch, m, om, N, Q, phys, dt, what):
+    """Residual with radial kappa_r and one SSPRK(5,4) step (every stage
+    form) without it, against the oracle."""
+    phys.kappa_r1, phys.kappa_r2, phys.integrator = 2e-4, 1e-4, ch.CHORUS_SSPRK54
+    cm = ch.mesh_from_arrays(m, N).upload()
+    ref = perturbed_oracle(oracle_mod, m, N)
+    Qp = ulp_perturb(Q)
+    R = gpu_residual(ch, torch, cm, phys, Q)
+    op = ora_phys(oracle_mod, phys)
+    assert_parity(R, om.residual(op, Q), ref.residual(op, Qp), what)
+    phys.kappa_r1 = phys.kappa_r2 = 0.0
+    op = ora_phys(oracle_mod, phys)
+    Qd = torch.from_numpy(np.ascontiguousarray(Q.reshape(5, -1))).cuda()
+    ch.chorus_rk_step(cm, phys, Qd, dt, 1, cm.workspace(phys))
+    torch.cuda.synchronize()
+    Q0 = Q.reshape(5, -1)
+    assert_parity(Qd.cpu().numpy() - Q0, om.ssp54(op, Q, dt, 1).reshape(5, -1) - Q0,
+                  ref.ssp54(op, Qp, dt, 1).reshape(5, -1) - Q0, what + " step")
+
+
+@pytest.mark.parametrize("N,copies", [(2, 171), (3, 54), (4, 38), (5, 17), (6, 17)])
+def test_parity_orientations_on_large_meshes(ch, oracle_mod, torch_dev, N, copies):
+    """The 24 relative orientations in the element passes of large meshes
+    (above 32, 10, 7, 3 and 3 elements per CU of 256): separate pairs of hexes
+    and one single hex, so that the last block of several elements is partly
+    empty."""
+    one = box_mesh(1, 1, 1)
+    m = _joined([two_element_mesh(i % 24) for i in range(24 * copies)] + [one])
+    shift = np.zeros((m.n_nodes, 3))
+    nodes = two_element_mesh(0).n_nodes
+    for i in range(24 * copies + 1):
+        k = i // 24
+        shift[i * nodes:(i + 1) * nodes] = (2.0 + 0.02 * k, 3.0 - 0.01 * k, 2.5 + 0.015 * k)
+    m.xyz = m.xyz + shift
+    om = oracle_mod.OracleMesh(m, N)
+    assert om.E == 48 * copies + 1
+    assert om.E > 256 * {2: 32, 3: 10, 4: 7, 5: 3, 6: 3}[N]
+    xyz, _ = om.solpts()
+    x, y, z = xyz
+    rng = np.random.default_rng(N)
+    Q = np.stack([1 + 0.1 * np.sin(x + 2 * y), 0.1 * np.cos(z), 0.05 * np.sin(x), -0.02 * np.sin(y * z),
+                  2.5 + 0.1 * np.cos(x * y)]) * (1 + 1e-2 * rng.uniform(-1, 1, size=x.size))
+    phys = ch.physics(nu=1e-2, kappa=1e-2, kappa_r=1e-3, GM=0.5, omega=0.3, bc_state=(1, 0, 0, 0, 2.5))
+    _parity_of_residual_and_step(ch, oracle_mod, torch_dev, m, om, N, Q.reshape(5, om.E, om.np), phys, 1e-4,
+                                 "orientations N=%d E=%d" % (N, om.E))
+
+
+@pytest.mark.parametrize("N,panel_n,radial_n", [(2, 15, 7), (3, 13, 3), (4, 13, 2), (6, 9, 2)])
+def test_parity_walls_on_large_meshes(ch, oracle_mod, torch_dev, N, panel_n, radial_n):
+    """Shells above the sizes of the wide passes: inner and outer walls (wall
+    temperature, bottom flux), the panels' orientations and a moving state in
+    the element passes."""
+    m, om, Q, phys = shell_case(oracle_mod, ch, panel_n, radial_n, N)
+    assert om.E > 256 * {2: 32, 3: 10, 4: 7, 5: 3, 6: 3}[N]
+    _parity_of_residual_and_step(ch, oracle_mod, torch_dev, m, om, N, Q, phys, 1e-3,
+                                 "walls N=%d E=%d" % (N, om.E))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("N,across", [(3, 26), (4, 22), (5, 15), (6, 15)])
+def test_wall_closed_forms_on_large_meshes(ch, oracle_mod, torch_dev, monkeypatch, precision, N, across):
+    """The closed forms of the walls (traction, energy fluxes) in the element
+    passes: the same slab with more elements of the same shape along the
+    walls, to the same bounds."""
+    import closed_forms as cf
+    ny, nz = cf.SLAB["ny"], cf.SLAB["nz"]
+    L, Ly, Lz = cf.SLAB["lengths"]
+    monkeypatch.setitem(cf.SLAB, "ny", across)
+    monkeypatch.setitem(cf.SLAB, "nz", across)
+    monkeypatch.setitem(cf.SLAB, "lengths", (L, Ly * across / ny, Lz * across / nz))
+    assert cf.SLAB["nx"] * across ** 2 > 256 * {3: 10, 4: 7, 5: 3, 6: 3}[N]
+    for bc in (1, 2):
+        test_stress_free_wall_traction_gpu(ch, oracle_mod, torch_dev, precision, N, bc)
+    test_wall_energy_fluxes_gpu(ch, oracle_mod, torch_dev, precision, N)
 
 
 def test_rk3_ten_steps_parity_c1(ch, oracle_mod, torch_dev):
