@@ -10,6 +10,9 @@
 
 namespace chorus {
 
+// compute units of the MI355X, for the launch limits given in elements per CU
+constexpr int kCUs = 256;
+
 // device geometry image views
 struct Geo {
     const double *solgeo;   // [E][13][NP]
@@ -68,7 +71,12 @@ hipError_t launch_lift64(const Mesh &m, const Geo &G, const double *TV, const St
                          hipStream_t s);
 
 // closure training: the partial gradients and losses of one mini-batch
-constexpr int kTrainPartials = 512;  // shares of a mini-batch at most
+// Shares of a mini-batch at most: a block each, two of which a CU holds (206
+// registers).  us per Adam iteration with one / two / four per CU at most:
+// 8,192 samples 17.3 / 20.2 / 20.2, 16,384 24.8 / 25.4 / 31.8, 32,768 39.6 /
+// 35.8 / 41.0, 65,536 68.6 / 55.0 / 60.2, 2^20 875 / 603 / 609 (the two kernels
+// before k_train 31.5, 36.8, 51.8, 93.9, 1,380).
+constexpr int kTrainPartials = 2 * kCUs;
 constexpr int kTrainExtra = 40;      // blocks - sums at most
 struct TrainBufs {
     float *part;     // [rows][6480]

@@ -1513,10 +1513,6 @@ __global__ void k_check(const double *__restrict__ Q, int64_t n, double gm1, int
 // ---------------------------------------------------------------------------
 // host launchers
 // ---------------------------------------------------------------------------
-struct LaunchCfg {
-    int epb, nt;
-};
-
 template <int N>
 static Ops<N> make_ops(const Basis1D &b) {
     return make_ops_t<double, N>(b);
@@ -1531,13 +1527,6 @@ template <> struct Cfg<4> { static constexpr int EPB = 1, NT = 64; };
 template <> struct Cfg<5> { static constexpr int EPB = 1, NT = 128; };
 template <> struct Cfg<6> { static constexpr int EPB = 1, NT = 256; };
 
-struct Bufs {
-    const double *Q;
-    const double *TQ;
-    double *TQw;
-    double *TV;
-};
-
 template <int N>
 static hipError_t launch_trace_t(const Mesh &m, const Geo &G, const double *Q, double *TQ, hipStream_t s) {
     constexpr int EPB = Cfg<N>::EPB, NT = Cfg<N>::NT;
@@ -1547,7 +1536,7 @@ static hipError_t launch_trace_t(const Mesh &m, const Geo &G, const double *Q, d
     return hipGetLastError();
 }
 
-// Largest meshes, in elements per CU (256), that run the wide passes: where
+// Largest meshes, in elements per CU, that run the wide passes: where
 // an SSP-RK3 step of a shell was no slower with them (us per step, element
 // passes / wide passes; the flux pass of order 4 is k_flux64_n4):
 //   flux  order 2: 53.8 / 47.1 at 3,600 hexes, 58.3 / 58.9 at 5,184
@@ -1562,14 +1551,11 @@ static hipError_t launch_trace_t(const Mesh &m, const Geo &G, const double *Q, d
 //         order 5: 83.4 / 80.7 at 648, 126.2 / 126.6 at 1,080
 //         order 6: 111.7 / 109.2 at 648, 168.8 / 167.8 at 1,080
 template <int N>
-static bool wide_flux64(const Mesh &m) {
-    constexpr int per_cu = N == 2 ? 16 : N == 3 ? 9 : N == 6 ? 0 : 1;
-    return m.E <= 256 * per_cu;
-}
+constexpr int kWideFlux64 = N == 2 ? 16 : N == 3 ? 9 : N == 6 ? 0 : 1;
 template <int N>
 static bool wide_lift64(const Mesh &m) {
     constexpr int per_cu = N == 2 ? 32 : N == 3 ? 10 : N == 4 ? 7 : 3;
-    return m.E <= 256 * per_cu;
+    return m.E <= kCUs * per_cu;
 }
 
 template <int N>
@@ -1601,19 +1587,23 @@ static hipError_t launch_flux64_t(const Mesh &m, const Geo &G, const PhysParams 
             else
                 hipLaunchKernelGGL((k_flux64<N, EPB, NT, 2, false>), dim3(nb), dim3(NT), 0, s, make_ops<N>(m.basis),
                                    G, P, Q, TQ, TV, sa, C);
+            return hipGetLastError();
         } else {
             return hipErrorInvalidValue;
         }
-    } else if (wide_flux64<N>(m)) {
-        if constexpr (N == 6)
-            return hipErrorInvalidValue;  // (never: see the rule)
-        else if (rad)
-            hipLaunchKernelGGL((k_flux64_wide<N, true>), dim3((unsigned)m.E), dim3(Wide<N>::NT), 0, s,
-                               make_ops<N>(m.basis), G, P, Q, TQ, TV, sa);
-        else
-            hipLaunchKernelGGL((k_flux64_wide<N, false>), dim3((unsigned)m.E), dim3(Wide<N>::NT), 0, s,
-                               make_ops<N>(m.basis), G, P, Q, TQ, TV, sa);
-    } else if constexpr (N == 4) {
+    }
+    if constexpr (kWideFlux64<N> > 0) {
+        if (m.E <= kCUs * kWideFlux64<N>) {
+            if (rad)
+                hipLaunchKernelGGL((k_flux64_wide<N, true>), dim3((unsigned)m.E), dim3(Wide<N>::NT), 0, s,
+                                   make_ops<N>(m.basis), G, P, Q, TQ, TV, sa);
+            else
+                hipLaunchKernelGGL((k_flux64_wide<N, false>), dim3((unsigned)m.E), dim3(Wide<N>::NT), 0, s,
+                                   make_ops<N>(m.basis), G, P, Q, TQ, TV, sa);
+            return hipGetLastError();
+        }
+    }
+    if constexpr (N == 4) {
         if (rad)
             hipLaunchKernelGGL((k_flux64_n4<true>), dim3((unsigned)m.E), dim3(64), 0, s, make_ops<4>(m.basis), G, P, Q,
                                TQ, TV, sa);

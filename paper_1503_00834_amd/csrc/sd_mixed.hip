@@ -1349,16 +1349,19 @@ template <int N> struct CfgL { static constexpr int EPB = CfgM<N>::EPB, NT = Cfg
 
 // Wide passes: threads per block of the smallest meshes (NT1, minimum waves
 // per SIMD W1) and of the next larger ones (NT2, W2), and the largest meshes
-// of each and of the lift pass and set-up, in elements per CU (256).  The
-// limits lie where an SSP-RK3 step of a shell crosses (us per step, element
+// of each and of the lift pass and set-up, in elements per CU.  The limits
+// lie where an SSP-RK3 step of a shell crosses (us per step, element
 // passes / wide passes with NT1 [/ NT2] threads):
 //   order 2: 56.0 / 51.5 at 5,184 hexes, 60.9 / 64.0 at 7,776; lift alone
 //            60.9 / 59.9 at 7,776, 72.7 / 80.6 at 12,288
 //   order 3: flux alone 39.3 / 26.7 at 288, 59.3 / 52.0 at 2,304, 67.4 / 67.3
 //            at 3,600, 83.1 / 85.9 at 5,184; lift alone 53.9 / 53.1 at 1,536, 62.9 / 63.8 at 2,304
 //   order 4: 45.8 / 31.6 / 36.4 at 288, 51.0 / 43.0 / 42.1 at 648; flux alone
-//            49.6 / - / 45.9 at 1,080, 55.0 / - / 54.3 at 1,536, 74.1 / - /
-//            78.2 at 2,304; lift alone 63.8 / 60.6 at 1,536, 79.8 / 79.6 at 2,304
+//            47.7 / - / 43.8 at 864, 56.3 / - / 54.7 at 1,350, 60.3 / - / 58.5
+//            at 1,536 (six blocks of three waves per CU, all resident), 62.3 /
+//            - / 64.4 at 1,728 (a second round), 63.8 / - / 68.4 at 1,944;
+//            lift alone 60.3 / 55.2 at 1,536, 62.3 / 60.2 at 1,728, 63.8 / 65.4
+//            at 1,944, 73.0 / 70.2 at 2,304 (the line at the flux pass's)
 //   order 5: 52.9 / 33.0 / 42.3 at 162; flux alone 48.1 / - / 44.5 at 288,
 //            60.3 / - / 61.5 at 648; lift alone 58.6 / 55.2 at 288, 68.7 / 69.2
 //            at 648
@@ -1394,7 +1397,7 @@ template <int N>
 static hipError_t pert_begin_t(const Mesh &m, const GeoM &g, const double *Q, double *Pq, float *TQ, hipStream_t s) {
     constexpr int EPB = CfgM<N>::EPB, NT = CfgM<N>::NT;
     const unsigned nb = (unsigned)((m.E + EPB - 1) / EPB);
-    if (m.E <= 256 * CfgW<N>::LIFT) {
+    if (m.E <= kCUs * CfgW<N>::LIFT) {
         hipLaunchKernelGGL((k_pert_begin<N, 1, CfgW<N>::NT1>), dim3((unsigned)m.E), dim3(CfgW<N>::NT1), 0, s,
                            make_ops_t<float, N>(m.basis), geof_of(g), Q, g.Q0, Pq, TQ);
         return hipGetLastError();
@@ -1424,8 +1427,8 @@ static hipError_t flux_mixed_t(const Mesh &m, const GeoM &g, const PhysParams &P
     constexpr int EPB = CfgF<N>::EPB, NT = CfgF<N>::NT, MINW = CfgF<N>::MINW;
     const unsigned nb = (unsigned)((m.E + EPB - 1) / EPB);
     const MixedStage st = a;
-    if (m.E <= 256 * CfgW<N>::MAX1) return flux_mixed_wide_t<N, CfgW<N>::NT1, CfgW<N>::W1>(m, g, P, Pq, TQ, TV, st, s);
-    if (m.E <= 256 * CfgW<N>::MAX2) return flux_mixed_wide_t<N, CfgW<N>::NT2, CfgW<N>::W2>(m, g, P, Pq, TQ, TV, st, s);
+    if (m.E <= kCUs * CfgW<N>::MAX1) return flux_mixed_wide_t<N, CfgW<N>::NT1, CfgW<N>::W1>(m, g, P, Pq, TQ, TV, st, s);
+    if (m.E <= kCUs * CfgW<N>::MAX2) return flux_mixed_wide_t<N, CfgW<N>::NT2, CfgW<N>::W2>(m, g, P, Pq, TQ, TV, st, s);
     if (P.kappa_r1 != 0.0 || P.kappa_r2 != 0.0)
         hipLaunchKernelGGL((k_flux_mixed<N, EPB, NT, MINW, KR_RADIAL>), dim3(nb), dim3(NT), 0, s,
                            make_ops_t<float, N>(m.basis), geof_of(g), bufs_of(g), physf_of(P), Pq, TQ, TV, st);
@@ -1443,7 +1446,7 @@ static hipError_t lift_mixed_t(const Mesh &m, const GeoM &g, const float *TV, co
     const unsigned nb = (unsigned)((m.E + EPB - 1) / EPB);
     const MixedStage st = a;
     const bool end = a.Qend != nullptr;
-    if (m.E <= 256 * CfgW<N>::LIFT) {
+    if (m.E <= kCUs * CfgW<N>::LIFT) {
         constexpr int NW = CfgW<N>::NT1;
         const dim3 grid((unsigned)m.E), block(NW);
         if (end)
