@@ -141,17 +141,19 @@ struct TrainSums {
 // TWO it adds those of share blockIdx.x + gridDim.x, if there is one.
 //
 // What bounds it: a batch of 4,096 is 256 groups, one block per CU, and each
-// layer waits for the one before, so it is a chain of about 80 matrix
-// products per wave.  One wave per 16 samples that walked all four row tiles
+// layer waits for the one before: a chain of about 80 matrix products per wave,
+// 1.1 us of the 10 us of a launch.  The rest is latency (launch and ramp,
+// weights and gathered rows, four barriers, the partial rows' stores), whose
+// parts have not been timed one by one.  One wave per 16 samples that walked all four row tiles
 // (320 products in a chain on a quarter of the SIMDs), the activations and
 // gradients sent through memory to a second kernel for the weight gradients,
 // took 13.4 + 11.6 us at batch 4,096; an iteration with its partial sums and
 // Adam went from 28.0 to 14.3 us.
 template <bool TWO>
 __global__ __launch_bounds__(256, 2) void k_train(const float *__restrict__ X, const float *__restrict__ Y,
-                                               const int32_t *__restrict__ idx, int64_t base, int nb,
-                                               const float *__restrict__ W, float *__restrict__ part_all,
-                                               int64_t n_mean, int nblk) {
+                                                  const int32_t *__restrict__ idx, int64_t base, int nb,
+                                                  const float *__restrict__ W, float *__restrict__ part_all,
+                                                  int64_t n_mean, int nblk) {
     __shared__ __align__(16) float sH1[4 * kTileStride], sH2[4 * kTileStride], sZ1[4 * kTileStride],
         sZ2[4 * kTileStride], sYp[4 * 256], sdY[kTileStride], sloss[16];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;

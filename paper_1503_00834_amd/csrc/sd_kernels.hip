@@ -808,7 +808,7 @@ void k_flux64(Ops<N> opa, Geo G, PhysParams P, const double *__restrict__ Q,
 // its latency and the per-lane operator reads.  Sums run over the same terms
 // as the scalar form.
 // Measured on 41,472 hexes against the scalar form (one element per wave too,
-// 14.6 KB of LDS): 312 -> 222 us per launch, 411 -> 139 LDS and 2,245 -> 1,475
+// 14.6 KB of LDS): 312 -> 222 us per launch, 411 -> 139 LDS and 2,245 -> 1,457
 // vector instructions per wave, 12.8 KB of LDS and 160 registers (three waves
 // per SIMD).  The pass has to move 27 KB per element: 5.0 TB/s, the rate of a
 // large copy, which bounds it now.
