@@ -16,7 +16,7 @@ reference norm and to the floor, and which bound applied.
 import numpy as np
 import pytest
 
-from chorus_inputs import Hex20Mesh, box_mesh, cubed_sphere_shell, two_element_mesh, uniform_noise
+from chorus_inputs import box_mesh, cubed_sphere_shell, two_element_mesh, uniform_noise
 
 pytestmark = pytest.mark.gpu
 
@@ -544,6 +544,7 @@ def test_residual_parity_orientations(ch, oracle_mod, torch_dev, rot):
 
 def _joined(meshes):
     """One mesh of several separate ones."""
+    from chorus_inputs import Hex20Mesh
     off = np.cumsum([0] + [m.n_nodes for m in meshes])
     cat = lambda f: np.concatenate([f(m, o) for m, o in zip(meshes, off)])
     return Hex20Mesh(xyz=cat(lambda m, o: m.xyz), elem20=cat(lambda m, o: m.elem20 + o),
